@@ -217,8 +217,10 @@ def timed_search(args, F, torch, seg, al, de, fd, templates, nfft, log, interbin
     #  pass A writes the 2 x tlen complex FP32 intermediate of each template and reads the
     #  resampled series (2 x N complex FP32) once per launch (one sky per launch);
     #  pass B reads the intermediate back and writes the crossings.
-    algo = {"template_a": B * 2 * tlen * CX32 + 2 * N * CX32,
-            "template_b": B * 2 * tlen * CX32 + B * cand_per_template * CAND_BYTES}
+    # The searched bins are half of the band, so the transforms run on series decimated to
+    # 5/8 of the sampling rate: 5/8 of the points and of the samples.
+    algo = {"template_a": (B * 2 * tlen * CX32 + 2 * N * CX32) * 5 // 8,
+            "template_b": B * 2 * tlen * CX32 * 5 // 8 + B * cand_per_template * CAND_BYTES}
     roofline = None
     if not args.no_events:
         dom = max(("template_a", "template_b"), key=lambda k: kernels[k]["total_ms"] or 0.0)
@@ -481,9 +483,10 @@ def ragged_leg(args, F, torch, np, dev, log):
     t1 = time.perf_counter()
     plan.destroy()
     value = templates / ((t1 - t0) / steps)
-    # the two template passes' algorithmic bytes: 2 nfft x 8 B written and read per template,
-    # each segment with its own nfft (the per-sky stage and the candidates left out)
-    tbytes = sum(per_seg * 2 * 2 * synth.nfft_for(s.n) * 8 for s in w.segments)
+    # the two template passes' algorithmic bytes: 2 x 5/8 nfft x 8 B (the decimated transforms)
+    # written and read per template, each segment with its own nfft (the per-sky stage and the
+    # candidates left out)
+    tbytes = sum(per_seg * 2 * 2 * synth.nfft_for(s.n) * 8 * 5 // 8 for s in w.segments)
     ns = sorted(s.n for s in w.segments)
     log(f"ragged: {len(segs)} segments, {templates} templates, {value:.4g} templates/s, "
         f"{counts[-1]} candidates/step, batches {info['templates_per_launch']} x {info['skies_per_batch']}")
@@ -677,9 +680,9 @@ def main():
                    "tuning": tuned},
         "roofline": roofline, "cpu_baseline": cpu, "plain": plain,
         "f_rel_err_vs_fp64": f_err, "candidates_per_step": n_cand / args.steps, "kernels": kernels,
-        # the two template passes' algorithmic bytes (2 nfft x 8 B written and read per
+        # the two template passes' algorithmic bytes (2 x 5/8 nfft x 8 B written and read per
         # template) over the whole step's time, per-sky stage and count drain included
-        "achieved_GBs_whole_step": templates * 2 * 2 * nfft * 8 / (ms_step / 1e3) / 1e9,
+        "achieved_GBs_whole_step": templates * 2 * 2 * nfft * 8 * 5 / 8 / (ms_step / 1e3) / 1e9,
         "candidate_capacity": main_leg["candidate_capacity"], "full_drain": main_leg["full_drain"],
         "vetting": vetting,
         "interbinning": ib_summary(ib, templates, nfft),

@@ -210,8 +210,7 @@ enum SrcKind { SRC_PLAIN = 0, SRC_HALFSHIFT = 1 };
 
 // Map a linear workgroup id to (tile, item) so that each XCD (workgroups are
 // dealt round-robin over 8 XCDs) keeps a fixed subset of tiles for all items.
-__device__ __forceinline__ void xcd_tile_item(int ntiles, int& tile, int& item) {
-  const int b = blockIdx.x;
+__device__ __forceinline__ void xcd_tile_item(int b, int ntiles, int& tile, int& item) {
   if ((ntiles & 7) == 0) {
     const int per = ntiles >> 3;
     const int xcd = b & 7, r = b >> 3;
@@ -241,7 +240,7 @@ __global__ void __launch_bounds__(NT) k_fft_pass_a(const cx<T>* __restrict__ in,
   constexpr int ST = lds_stride<Q>();
   __shared__ cx<T> lds[2 * TW * ST];
   int tile, item;
-  xcd_tile_item(P / TW, tile, item);
+  xcd_tile_item(blockIdx.x, P / TW, tile, item);
   const int j10 = tile * TW;
   for (int e = threadIdx.x; e < 2 * TW * Q; e += NT) {
     const int s = e / (TW * Q), rem = e % (TW * Q);
@@ -279,7 +278,7 @@ __global__ void __launch_bounds__(NT) k_fft_pass_b(const cx<T>* __restrict__ in,
   constexpr int ST = lds_stride<P>();
   __shared__ cx<T> lds[2 * TW * ST];
   int tile, item;
-  xcd_tile_item(Q / TW, tile, item);
+  xcd_tile_item(blockIdx.x, Q / TW, tile, item);
   const int k20 = tile * TW;
   for (int e = threadIdx.x; e < 2 * TW * P; e += NT) {
     const int s = e / (TW * P), rem = e % (TW * P);
@@ -507,6 +506,11 @@ struct TmplArgs {
   double m10, m11;      // w0 and w1 components of the spindown row
   double bins_per_rad;  // nfft / (2 pi)
   int s_lo, nfft;
+  int nblk;             // first pass: tiles of the launch (its grid may be smaller and walk them)
+  // which of two launched paths does the work: one of them returns at once (NULL: no choice)
+  const int* route;
+  int route_want;
+  float ibpr, ibpi;     // interbinning of decimated transforms: exp(2 pi i DEC_M0 / L)
 };
 
 // Lattice arithmetic shared by the kernels and the host's candidate records, with
@@ -538,6 +542,109 @@ __device__ __forceinline__ void template_chirp(const TmplArgs& ta, int skyl, int
     c2 = lattice_w(s, ta.m11, ta.w_spin[sky]) * (0.5 / M_PI);
     c1 = lattice_shift_bins(lattice_w(s, ta.m10, ta.w_freq[sky]), ta.bins_per_rad) / (double)ta.nfft;
   }
+}
+
+// ------------------------------------------------------------- decimated series
+// The searched bins [0, L/2) are half of a template transform's band, so the transform can
+// run at 5/8 of the sampling rate: the resampled series is filtered once per sky position
+// to the frequencies a template needs (its band, plus a margin for the spindown chirp's
+// sweep) and sampled every 8/5 samples, and each template transforms 5 L / 8 points
+// instead of L, with the same bins k / L at the same indices k.  The filter is a
+// Kaiser-windowed sinc, centred on a quarter of the sampling rate, of gain 1 within
+// 0.25 + 0.012 and below 1e-8 beyond 0.375 - 0.012 cycles per sample of the centre, so
+// that nothing folds into the searched bins.  Output m = 5 q + p (p < 5) is the filtered
+// series at sample t = 8 (q - DEC_Q0) + 8 p / 5; the transform's bins so carry the phase
+// exp(-2 pi i k DEC_M0 / L'), which |Fa|, |Fb| and Fa Fb* do not see.
+constexpr int DEC_UP = 5, DEC_DOWN = 8;
+constexpr int DEC_T = 44;                       // filter half-width, samples
+constexpr int DEC_Q0 = 6, DEC_M0 = DEC_UP * DEC_Q0;
+constexpr int DEC_TAPS = 2 * DEC_T + DEC_DOWN;  // inputs of five outputs: 8 q' - 44 .. 8 q' + 51
+constexpr double DEC_BETA = 15.5;               // Kaiser parameter
+constexpr double DEC_SWEEP = 0.005;             // largest chirp sweep (cycles per sample) the margin takes
+static_assert(DEC_TAPS % 8 == 0 && DEC_Q0 * DEC_DOWN >= DEC_T, "filter geometry");
+constexpr int DEC_NT = 128;                     // groups of five outputs per workgroup
+
+// samples of the decimated series of n samples (whole groups of five)
+inline long dec_samples(long n) { return DEC_UP * (DEC_Q0 + (n - 1 + DEC_T) / DEC_DOWN + 1); }
+
+// Sky blockIdx.y, both series interleaved [m][a|b]; h[i][p] = filter value of input
+// 8 (q - DEC_Q0) - DEC_T + i in output p.  A thread forms one group of five outputs of one
+// series (wavefronts 0, 1: series a, 2, 3: b): 96 staged inputs, 475 taps, sums in double
+// precision (as fast as single on this chip without packed single precision), so that the
+// decimated series carries one rounding.  The taps are uniform (scalar loads); the centre
+// frequency's rotation of the inputs, (-i)^i, only swaps and negates parts, and that of
+// the outputs is a constant per p.  LDS index e sits at e + e / 8: lanes read eight inputs
+// apart, and the padding spreads them over the banks.
+template <typename T>
+__global__ void __launch_bounds__(2 * DEC_NT) k_decimate(const cx<T>* __restrict__ zt, long ldzt, int n,
+                                                         cx<T>* __restrict__ zd, long ldzd, int nq,
+                                                         const double* __restrict__ h) {
+  constexpr int NIN = DEC_DOWN * DEC_NT + DEC_TAPS - DEC_DOWN;
+  __shared__ cx<T> sz[2][NIN + NIN / 8 + 1];
+  const int s = threadIdx.x / DEC_NT, tid = threadIdx.x % DEC_NT;
+  const int q0 = blockIdx.x * DEC_NT;
+  const cx<T>* z = zt + (long)(2 * blockIdx.y + s) * ldzt;
+  const int j0 = DEC_DOWN * (q0 - DEC_Q0) - DEC_T;
+  for (int e = tid; e < NIN; e += DEC_NT) {
+    const int j = j0 + e;
+    sz[s][e + e / 8] = j >= 0 && j < n ? z[j] : mk<T>(0, 0);
+  }
+  __syncthreads();
+  const int q = q0 + tid;
+  if (q >= nq) return;
+  cx<double> acc[DEC_UP];
+#pragma unroll
+  for (int p = 0; p < DEC_UP; ++p) acc[p] = mk<double>(0.0, 0.0);
+  const cx<T>* in = sz[s] + 9 * tid;
+  for (int g = 0; g < DEC_TAPS / 8; ++g) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const cx<T> v = in[9 * g + i];
+      const double re = (double)v.re, im = (double)v.im;
+      const cx<double> x = i % 4 == 0   ? mk<double>(re, im)
+                           : i % 4 == 1 ? mk<double>(im, -re)
+                           : i % 4 == 2 ? mk<double>(-re, -im)
+                                        : mk<double>(-im, re);
+#pragma unroll
+      for (int p = 0; p < DEC_UP; ++p) {
+        const double c = h[(8 * g + i) * DEC_UP + p];
+        acc[p] = mk<double>(fma(c, x.re, acc[p].re), fma(c, x.im, acc[p].im));
+      }
+    }
+  }
+  // exp(2 pi i 0.25 t) with t = 8 p / 5 (whole turns left out): cos, sin of 2 pi 2 p / 5
+  constexpr double c1 = 0.30901699437494742410, s1 = 0.95105651629515357212;   // 2 pi / 5
+  constexpr double c2 = -0.80901699437494742410, s2 = 0.58778525229247312917;  // 4 pi / 5
+  const cx<double> rot[DEC_UP] = {mk<double>(1.0, 0.0), mk<double>(c2, s2), mk<double>(c1, -s1), mk<double>(c1, s1),
+                                  mk<double>(c2, -s2)};
+  cx<T>* out = zd + (long)blockIdx.y * 2 * ldzd + 2 * (long)DEC_UP * q + s;
+#pragma unroll
+  for (int p = 0; p < DEC_UP; ++p) {
+    const cx<double> a = cmul(acc[p], rot[p]);
+    out[2 * p] = mk<T>((T)a.re, (T)a.im);
+  }
+}
+
+// Whether the decimated series serves every template of a call: *route = 1 when no chirp
+// sweeps more than DEC_SWEEP cycles per sample over the n samples (a value that is not a
+// number fails), else 0.  One workgroup, once per call and segment: the lists are on the
+// device and the call does not wait for them.
+__global__ void __launch_bounds__(1024) k_route(const double* __restrict__ fdot, int nfdot, double dt,
+                                                const double* __restrict__ w_spin, int nsky, int s_lo, double m11,
+                                                int n, int* __restrict__ route) {
+  const double per = fdot ? dt * dt * (double)n : (double)n / M_PI;   // sweep per unit of fdot, w1
+  int bad = 0;
+  const int count = fdot ? nfdot : nsky;
+  for (int i = threadIdx.x; i < count; i += 1024) {
+    if (fdot) {
+      bad |= !(fabs(fdot[i]) * per <= DEC_SWEEP);
+    } else {
+      bad |= !(fabs(lattice_w(s_lo, m11, w_spin[i])) * per <= DEC_SWEEP);
+      bad |= !(fabs(lattice_w(s_lo + nfdot - 1, m11, w_spin[i])) * per <= DEC_SWEEP);
+    }
+  }
+  bad = __syncthreads_or(bad);
+  if (threadIdx.x == 0) *route = bad ? 0 : 1;
 }
 
 // Where pass B puts its results.

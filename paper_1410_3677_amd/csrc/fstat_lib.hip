@@ -37,6 +37,11 @@ struct SegInfo {
   // the template FFTs: tL = nfft, or nfft/2 with interbinning; tL = tP * tQ
   int tlog, tP, tQ, tL;
   double ibw = 0.0;            // interbinning weight (0 without interbinning)
+  // decimated template transforms: dL = 5 tL / 8 = tP * dQ points of dn samples; dec: the
+  // segment's bins and length allow them
+  bool dec = false;
+  int dQ = 0, dL = 0;
+  long dn = 0;
 };
 
 // The templates of one search call: nsky sky positions times nfdot spindowns, given
@@ -89,6 +94,9 @@ struct Tables {
   size_t off_hi[2][LOG_MAX + 1] = {};
   size_t off_g[2] = {0, 0};
   size_t off_stage[2] = {0, 0};
+  // decimated transforms (single precision): twiddles of 5 2^(e-3) points, stage twiddles,
+  // filter taps (double)
+  size_t off_dlo[LOG_MAX + 1] = {}, off_dhi[LOG_MAX + 1] = {}, off_dstage = 0, off_taps = 0;
   size_t bytes = 0;
 };
 
@@ -126,10 +134,12 @@ struct fstat_plan_s {
   // per-sky parameters and resampled series twice (the sky batch being prepared and the
   // one being searched), per-sky scratch, template intermediate
   size_t off_sp[2] = {0, 0}, off_part = 0, off_zt[2] = {0, 0}, off_sky = 0, off_tmpl = 0;
+  size_t off_zd[2] = {0, 0}, off_route = 0;   // decimated series, path flag of the running call
   size_t off_xs = 0;   // FP64 with interbinning: the second pass's transforms [B][tL][2]
   int nblk_max = 0;
   long n_max = 0, L_max = 0, M_max = 0;
   long TL_max = 0;             // longest template FFT
+  long dn_max = 0;             // longest decimated series (0: no segment has one)
   // tables and candidates
   Tables tab;
   CandEntry* d_cand = nullptr;
@@ -342,6 +352,16 @@ static size_t layout(fstat_plan_t p, int Sb, int B, bool commit) {
   // template intermediate [B][tL][2]
   const size_t o_tmpl = off;
   off = align256(off + (size_t)B * 2 * p->TL_max * cx);
+  // decimated series, twice like the resampled ones, and the path flag
+  size_t o_zd[2] = {0, 0}, o_route = 0;
+  if (p->dn_max) {
+    for (int k = 0; k < 2; ++k) {
+      o_zd[k] = off;
+      off = align256(off + (size_t)Sb * 2 * p->dn_max * cx);
+    }
+    o_route = off;
+    off = align256(off + sizeof(int));
+  }
   // interbinning through the tiled second pass (FP64, or P > 512): the transforms
   // themselves, for the interbinning epilogue
   const size_t o_xs = off;
@@ -350,7 +370,9 @@ static size_t layout(fstat_plan_t p, int Sb, int B, bool commit) {
     for (int k = 0; k < 2; ++k) {
       p->off_sp[k] = o_sp[k];
       p->off_zt[k] = o_zt[k];
+      p->off_zd[k] = o_zd[k];
     }
+    p->off_route = o_route;
     p->off_part = o_part;
     p->off_sky = o_sky;
     p->off_tmpl = o_tmpl;
@@ -402,6 +424,63 @@ static void fill_tables(std::vector<unsigned char>& buf, Tables& tb, int which, 
   const double z = std::sqrt(3.0) - 2.0;
   for (int k = 0; k <= kt; ++k)
     reinterpret_cast<T*>(buf.data() + og)[k] = (T)(std::pow(z, k) / (2.0 * std::sqrt(3.0)));
+}
+
+// Tables of the decimated transforms for the transform lengths (log2) of `logs`.
+static double bessel_i0(double x) {
+  double sum = 1.0, term = 1.0;
+  for (int k = 1; k < 200 && term > 1e-18 * sum; ++k) {
+    term *= (x / (2.0 * k)) * (x / (2.0 * k));
+    sum += term;
+  }
+  return sum;
+}
+
+static void fill_dec_tables(std::vector<unsigned char>& buf, Tables& tb, const std::vector<int>& logs) {
+  typedef cx<float> C;
+  auto put = [&](size_t bytes) {
+    size_t off = align256(buf.size());
+    buf.resize(off + bytes);
+    return off;
+  };
+  auto wexp = [](long m, long L) {
+    const double a = 2.0 * M_PI * (double)m / (double)L;
+    C w;
+    w.re = (float)std::cos(a);
+    w.im = (float)(-std::sin(a));
+    return w;
+  };
+  for (int e : logs) {
+    if (tb.off_dhi[e]) continue;
+    const long L = 5L << (e - 3);
+    tb.off_dlo[e] = put(1024 * sizeof(C));
+    for (int m = 0; m < 1024; ++m) reinterpret_cast<C*>(buf.data() + tb.off_dlo[e])[m] = wexp(m, L);
+    const long nh = (L + 1023) / 1024;
+    tb.off_dhi[e] = put(nh * sizeof(C));
+    for (long m = 0; m < nh; ++m) reinterpret_cast<C*>(buf.data() + tb.off_dhi[e])[m] = wexp(1024 * m, L);
+  }
+  tb.off_dstage = put(DEC_TW_ENTRIES * sizeof(C));
+  for (int ns = 5; ns <= 320; ns *= 8)
+    for (int rr = 2; rr <= 8; rr *= 2)
+      for (int k = 0; k < ns; ++k)
+        for (int r = 1; r < rr; ++r)
+          reinterpret_cast<C*>(buf.data() + tb.off_dstage)[dec_tw_offset(ns, rr) + k * (rr - 1) + (r - 1)] =
+              wexp((long)k * r, (long)ns * rr);
+  // Kaiser-windowed sinc, cutoff half the decimated rate, times the 8/5 that makes sums over
+  // decimated samples sums over samples: tap i of output p, at offset 8 p / 5 + 44 - i
+  tb.off_taps = put(DEC_TAPS * DEC_UP * sizeof(double));
+  double* h = reinterpret_cast<double*>(buf.data() + tb.off_taps);
+  const double rate = (double)DEC_UP / DEC_DOWN, i0b = bessel_i0(DEC_BETA);
+  for (int i = 0; i < DEC_TAPS; ++i)
+    for (int p = 0; p < DEC_UP; ++p) {
+      const double t = p / rate + DEC_T - i, u = t / DEC_T;
+      double v = 0.0;
+      if (std::fabs(u) <= 1.0) {
+        const double a = M_PI * rate * t;
+        v = (t == 0.0 ? 1.0 : std::sin(a) / a) * bessel_i0(DEC_BETA * std::sqrt(1.0 - u * u)) / i0b;
+      }
+      h[i * DEC_UP + p] = v;   // rate * (1 / rate)
+    }
 }
 
 constexpr int KT_F32 = 16, KT_F64 = 32;
@@ -502,12 +581,18 @@ struct Dev {
     g = (const T*)((const char*)p->tab.dev + p->tab.off_g[w]);
     twst = (const cx<T>*)((const char*)p->tab.dev + p->tab.off_stage[w]);
   }
+  const cx<T>* dec_lo(int e) const { return (const cx<T>*)((const char*)p->tab.dev + p->tab.off_dlo[e]); }
+  const cx<T>* dec_hi(int e) const { return (const cx<T>*)((const char*)p->tab.dev + p->tab.off_dhi[e]); }
+  const cx<T>* dec_stage() const { return (const cx<T>*)((const char*)p->tab.dev + p->tab.off_dstage); }
+  const double* taps() const { return (const double*)((const char*)p->tab.dev + p->tab.off_taps); }
   int buf = 0;   // which of the two per-sky buffers
   SkyParams* sp() const { return (SkyParams*)((char*)p->ws + p->off_sp[buf]); }
   double* part() const { return (double*)((char*)p->ws + p->off_part); }
   cx<T>* zt() const { return (cx<T>*)((char*)p->ws + p->off_zt[buf]); }
   cx<T>* sky() const { return (cx<T>*)((char*)p->ws + p->off_sky); }
   cx<T>* tmpl() const { return (cx<T>*)((char*)p->ws + p->off_tmpl); }
+  cx<T>* zd() const { return (cx<T>*)((char*)p->ws + p->off_zd[buf]); }
+  int* route() const { return (int*)((char*)p->ws + p->off_route); }
   cx<T>* xs() const { return (cx<T>*)((char*)p->ws + p->off_xs); }
 };
 
@@ -539,7 +624,7 @@ static hipError_t fft_two_pass(const Dev<T>& d, int logL, int P, int Q, const cx
 // Per-sky stage for skies [sky0, sky0 + nb) of segment si; leaves zt and SkyParams.
 template <typename T>
 static fstat_status run_sky_batch(fstat_plan_t p, const Dev<T>& d, const SegInfo& si, const double* alpha,
-                                  const double* delta, int sky0, int nb, hipStream_t st) {
+                                  const double* delta, int sky0, int nb, bool dec, hipStream_t st) {
   const SegConst sc = seg_const(si);
   const int n = sc.n, L = si.nfft, M = si.M;
   const int nblk = (n + NT - 1) / NT;
@@ -568,6 +653,14 @@ static fstat_status run_sky_batch(fstat_plan_t p, const Dev<T>& d, const SegInfo
     FSTAT_LAUNCH((k_spline<T, KT>), dim3(nblk, nb), dim3(NT), 0, st, sc, d.sp(), za, o, (long)M, d.zt(),
                        (long)n, d.g);
     HIP_TRY(p, launch_status(), "spline launch");
+    if constexpr (sizeof(T) == 4) {
+      if (dec) {
+        const int nq = (int)(si.dn / DEC_UP);
+        FSTAT_LAUNCH((k_decimate<T>), dim3((unsigned)((nq + DEC_NT - 1) / DEC_NT), nb), dim3(2 * DEC_NT), 0, st, d.zt(),
+                     (long)n, n, d.zd(), si.dn, nq, d.taps());
+        HIP_TRY(p, launch_status(), "decimation launch");
+      }
+    }
   }
   return FSTAT_OK;
 }
@@ -588,9 +681,90 @@ constexpr int IB_WG_PER_CU_HALF = 3, IB_WG_PER_CU_FULL = 2;
 constexpr int STREAM2_NT = 128;
 constexpr int STREAM2_WG_PER_CU = 3 * 256 / STREAM2_NT;
 
+// First pass of the decimated transforms of nt templates.
+static hipError_t launch_dec_a(const Dev<float>& d, const SegInfo& si, const TmplArgs& ta, int nt, cx<float>* tbuf,
+                               hipStream_t st) {
+  hipError_t err = hipErrorInvalidValue;
+  // first-stage inputs r >= rnz are zero for every column when dn <= rnz dL / 5
+  const int rnz = (int)std::max<long>(2, (5 * si.dn + si.dL - 1) / si.dL);
+  auto go = [&](auto len_c, auto rnz_c) {
+    constexpr int LEN = decltype(len_c)::value, RZ = decltype(rnz_c)::value;
+    FSTAT_LAUNCH((k_tmpl_a_dec<float, LEN, RZ>), dim3((unsigned)(si.tP / dec_tw<LEN>() * nt)), dim3(DEC_A_NT), 0, st,
+                 ta, d.zd(), tbuf, d.dec_stage(), d.dec_lo(si.tlog), d.dec_hi(si.tlog));
+    err = launch_status();
+  };
+  auto len = [&](auto len_c) {
+    switch (rnz) {
+      case 2: go(len_c, std::integral_constant<int, 2>{}); break;
+      case 3: go(len_c, std::integral_constant<int, 3>{}); break;
+      case 4: go(len_c, std::integral_constant<int, 4>{}); break;
+      case 5: go(len_c, std::integral_constant<int, 5>{}); break;
+      default: break;
+    }
+  };
+  switch (si.dQ) {
+    case 40: len(std::integral_constant<int, 40>{}); break;
+    case 80: len(std::integral_constant<int, 80>{}); break;
+    case 160: len(std::integral_constant<int, 160>{}); break;
+    case 320: len(std::integral_constant<int, 320>{}); break;
+    case 640: len(std::integral_constant<int, 640>{}); break;
+    default: break;
+  }
+  return err;
+}
+
+// Streaming second pass of nt templates with rows of PP points (interbinned or not): about
+// one resident round of workgroups walks the launch's row units.  mode 0: candidates,
+// 1: spectrum, 2: candidates and the 2F rows of the patch capture.
+template <int PP, int BAND>
+static hipError_t launch_stream_b(const Dev<float>& d, const SegInfo& si, const TmplArgs& ta, int nt, int mode,
+                                  const OutArgs& oa, const cx<float>* tbuf, hipStream_t st) {
+  const long n_cu = d.p->n_cu;
+  auto go = [&](auto mode_c) {
+    constexpr int MD = decltype(mode_c)::value;
+    if constexpr (PP <= 512) {
+      if (si.ibw != 0.0) {
+        const long units = ta.Q / stream_rpw<PP>();
+        const long max_wgs = n_cu * (BAND == BAND_HALF ? IB_WG_PER_CU_HALF : IB_WG_PER_CU_FULL);
+        const int ch = ib_chunk(nt, (int)units, 4 * max_wgs);
+        const long chunks = (long)nt * (units / ch);
+        const long wgs = std::min((chunks + 3) / 4, max_wgs);
+        FSTAT_LAUNCH((k_tmpl_b_ib<PP, MD, BAND>), dim3((unsigned)wgs), dim3(256), 0, st, ta, nt, ch, d.sp(), tbuf, oa,
+                     d.twst);
+        return;
+      }
+      const long waves = (long)nt * (ta.Q / stream_rpw<PP>());
+      const long wgs = std::min((waves + 3) / 4, n_cu * STREAM_WG_PER_CU);
+      FSTAT_LAUNCH((k_tmpl_b_stream<float, PP, MD, BAND>), dim3((unsigned)wgs), dim3(256), 0, st, ta, nt, d.sp(), tbuf,
+                   oa, d.twst);
+    } else if constexpr (MD != 2) {
+      constexpr int NT2 = STREAM2_NT;
+      const long units = (long)nt * (ta.Q / (NT2 / groups_per_col<PP>()));
+      const long wgs = std::min(units, n_cu * STREAM2_WG_PER_CU);
+      FSTAT_LAUNCH((k_tmpl_b_stream2<MD, BAND, NT2>), dim3((unsigned)wgs), dim3(NT2), 0, st, ta, nt, d.sp(), tbuf, oa,
+                   d.twst);
+    }
+  };
+  if (mode == 0) go(std::integral_constant<int, 0>{});
+  else if (mode == 1) go(std::integral_constant<int, 1>{});
+  else if constexpr (BAND < BAND_DEC) go(std::integral_constant<int, 2>{});
+  return launch_status();
+}
+
+// Whether a call's templates of segment si run as decimated transforms.  They save 3/8 of
+// a template's memory traffic and arithmetic and cost, per call, the filter (0.6 us a sky
+// position) and the launches of the path not taken; small calls, where those weigh more
+// than the templates, keep the full-rate transforms.  The patch capture stores the rows of
+// the full-rate second pass.
+constexpr long DEC_MIN_POINTS = 1L << 24;   // templates times transform points
+static bool use_dec(fstat_plan_t p, const SegInfo& si, const Grid& g, int mode) {
+  return si.dec && p->dn_max && p->variant_b == 1 && !(mode == 0 && p->vet) && g.nfdot >= 2 &&
+         (long)g.nsky * g.nfdot * si.tL >= DEC_MIN_POINTS;
+}
+
 template <typename T>
 static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo& si, int sky0, int nb,
-                                  const Grid& g, int mode, OutArgs oa, hipStream_t st) {
+                                  const Grid& g, int mode, OutArgs oa, bool dec, hipStream_t st) {
   const int nfdot = g.nfdot;
   TmplArgs ta;
   ta.n = (int)si.s.n;
@@ -610,6 +784,24 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
   ta.bins_per_rad = (double)si.nfft / (2.0 * M_PI);
   ta.s_lo = g.s_lo;
   ta.nfft = si.nfft;
+  ta.nblk = 0;
+  // with decimated transforms both paths are launched and the flag that the call's k_route
+  // left says which one works; the other's launches hold one resident round of workgroups,
+  // which return at once (about 5 us each against 470 us for the 512 templates of both passes)
+  ta.route = dec ? d.route() : nullptr;
+  ta.route_want = 0;
+  ta.ibpr = 1.f;
+  ta.ibpi = 0.f;
+  TmplArgs td = ta;
+  if (dec) {
+    td.route_want = 1;
+    td.n = (int)si.dn;
+    td.Q = si.dQ;
+    td.L = si.dL;
+    td.ldzt = si.dn;
+    td.ibpr = (float)std::cos(2.0 * M_PI * DEC_M0 / si.dL);
+    td.ibpi = (float)std::sin(2.0 * M_PI * DEC_M0 / si.dL);
+  }
   const int total = nb * nfdot;
   cx<T>* tbuf = d.tmpl();
   // the plan's B templates per launch are sized for its longest transform; when the
@@ -619,14 +811,19 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
   const int Bs = p->scale_B ? (int)std::min<long>((long)p->B * (p->TL_max / si.tL), 4096L) : p->B;
   for (int t0 = 0; t0 < total; t0 += Bs) {
     const int nt = std::min(Bs, total - t0);
-    ta.t0 = t0;
+    ta.t0 = td.t0 = t0;
     hipError_t err = hipSuccess;
     {
       ProfScope ps(p, FSTAT_KERNEL_TEMPLATE_A, st);
-      with_len(si.tQ, [&](auto c) {
+      if constexpr (sizeof(T) == 4) {
+        if (dec) err = launch_dec_a(d, si, td, nt, tbuf, st);
+      }
+      if (err == hipSuccess) with_len(si.tQ, [&](auto c) {
         constexpr int QQ = decltype(c)::value;
         if constexpr (QQ >= 64) {
           const int ntiles = si.tP / tw_a<T, QQ>();
+          ta.nblk = ntiles * nt;
+          const dim3 grid(dec ? std::min(ta.nblk, 2 * p->n_cu) : ta.nblk);
           // first-stage inputs r >= rnz are zero for every column when n <= rnz tL / 8
           int rnz = 8;
           for (int r = 7; r >= 3; --r)
@@ -634,10 +831,10 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
           auto go = [&](auto rnz_c) {
             constexpr int RZ = decltype(rnz_c)::value;
             if (p->variant_a == 1)
-              FSTAT_LAUNCH((k_tmpl_a_pair<T, QQ, RZ>), dim3(ntiles * nt), dim3(tmpl_nt_a<T, QQ>()), 0, st, ta,
+              FSTAT_LAUNCH((k_tmpl_a_pair<T, QQ, RZ>), grid, dim3(tmpl_nt_a<T, QQ>()), 0, st, ta,
                                  d.zt(), tbuf, d.twst, d.lo(si.tlog), d.hi(si.tlog));
             else
-              FSTAT_LAUNCH((k_tmpl_a<T, QQ, RZ>), dim3(ntiles * nt), dim3(tmpl_nt_a<T, QQ>()), 0, st, ta, d.zt(),
+              FSTAT_LAUNCH((k_tmpl_a<T, QQ, RZ>), grid, dim3(tmpl_nt_a<T, QQ>()), 0, st, ta, d.zt(),
                                  tbuf, d.twst, d.lo(si.tlog), d.hi(si.tlog));
           };
           switch (rnz) {
@@ -664,72 +861,18 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
       ProfScope ps(p, FSTAT_KERNEL_TEMPLATE_B, st);
       with_len(si.tP, [&](auto c) {
         constexpr int PP = decltype(c)::value;
-        if constexpr (sizeof(T) == 4 && PP >= 64 && PP <= 512) {
-          if (si.ibw != 0.0) {
-            // interbinning: about one resident round of wavefronts walking chunks of row units
-            const long units = si.tQ / stream_rpw<PP>();
-            const long chunks = (long)nt * (units / std::min<long>(units, IB_CHUNK));
-            const bool half = (oa.k_min == 0 && oa.k_max == si.nfft / 2);
-            const long wgs = std::min((chunks + 3) / 4, (long)p->n_cu * (half ? IB_WG_PER_CU_HALF : IB_WG_PER_CU_FULL));
-            auto go = [&](auto mode_c, auto half_c) {
-              constexpr int MD = decltype(mode_c)::value;
-              constexpr bool HF = decltype(half_c)::value;
-              FSTAT_LAUNCH((k_tmpl_b_ib<PP, MD, HF>), dim3((unsigned)wgs), dim3(256), 0, st, ta, nt, d.sp(),
-                                 (const cx<float>*)tbuf, oa, (const cx<float>*)d.twst);
-            };
-            using BT = std::true_type;
-            using BF = std::false_type;
-            if (capture) half ? go(std::integral_constant<int, 2>{}, BT{}) : go(std::integral_constant<int, 2>{}, BF{});
-            else if (mode == 0) half ? go(std::integral_constant<int, 0>{}, BT{}) : go(std::integral_constant<int, 0>{}, BF{});
-            else half ? go(std::integral_constant<int, 1>{}, BT{}) : go(std::integral_constant<int, 1>{}, BF{});
-            err = launch_status();
-            return;
-          }
-          if (p->variant_b == 1) {
-          // streaming kernel: about one resident round of wavefronts walks the launch's row units
-          const long waves = (long)nt * (si.tQ / stream_rpw<PP>());
-          const long wgs = std::min((waves + 3) / 4, (long)p->n_cu * STREAM_WG_PER_CU);
-          const dim3 grid((unsigned)wgs);
+        if constexpr (sizeof(T) == 4 && PP >= 64) {
           const bool half = (oa.k_min == 0 && oa.k_max == si.nfft / 2);
-          auto go = [&](auto mode_c, auto half_c) {
-            constexpr int MD = decltype(mode_c)::value;
-            constexpr bool HF = decltype(half_c)::value;
-            FSTAT_LAUNCH((k_tmpl_b_stream<T, PP, MD, HF>), grid, dim3(256), 0, st, ta, nt, d.sp(), tbuf, oa,
-                               d.twst);
-          };
-          using I0 = std::integral_constant<int, 0>;
-          using I1 = std::integral_constant<int, 1>;
-          using I2 = std::integral_constant<int, 2>;
-          using BT = std::true_type;
-          using BF = std::false_type;
-          if (capture) half ? go(I2{}, BT{}) : go(I2{}, BF{});
-          else if (mode == 0) half ? go(I0{}, BT{}) : go(I0{}, BF{});
-          else half ? go(I1{}, BT{}) : go(I1{}, BF{});
-          err = launch_status();
-          return;
-          }
-        }
-        if constexpr (sizeof(T) == 4 && PP == 1024) {
-          if (si.ibw == 0.0 && p->variant_b == 1 && !capture) {
-            // rows of 1024 points, two wavefronts each: about one resident round of
-            // workgroups walks the launch's units of two rows
-            constexpr int NT2 = STREAM2_NT;
-            const long units = (long)nt * (si.tQ / (NT2 / groups_per_col<PP>()));
-            const long wgs = std::min(units, (long)p->n_cu * STREAM2_WG_PER_CU);
-            const bool half = (oa.k_min == 0 && oa.k_max == si.nfft / 2);
-            auto go = [&](auto mode_c, auto half_c) {
-              constexpr int MD = decltype(mode_c)::value;
-              constexpr bool HF = decltype(half_c)::value;
-              FSTAT_LAUNCH((k_tmpl_b_stream2<MD, HF, NT2>), dim3((unsigned)wgs), dim3(NT2), 0, st, ta, nt, d.sp(),
-                           tbuf, oa, d.twst);
-            };
-            using I0 = std::integral_constant<int, 0>;
-            using I1 = std::integral_constant<int, 1>;
-            using BT = std::true_type;
-            using BF = std::false_type;
-            if (mode == 0) half ? go(I0{}, BT{}) : go(I0{}, BF{});
-            else half ? go(I1{}, BT{}) : go(I1{}, BF{});
-            err = launch_status();
+          const bool stream = si.ibw != 0.0 ? PP <= 512 : p->variant_b == 1 && (PP <= 512 || !capture);
+          if (stream) {
+            const int md = capture ? 2 : mode;
+            if (dec) {
+              if (half) err = launch_stream_b<PP, BAND_DEC>(d, si, td, nt, md, oa, tbuf, st);
+              else err = launch_stream_b<PP, BAND_DEC_RANGE>(d, si, td, nt, md, oa, tbuf, st);
+              if (err != hipSuccess) return;
+            }
+            if (half) err = launch_stream_b<PP, BAND_HALF>(d, si, ta, nt, md, oa, tbuf, st);
+            else err = launch_stream_b<PP, BAND_ANY>(d, si, ta, nt, md, oa, tbuf, st);
             return;
           }
         }
@@ -822,6 +965,12 @@ static fstat_status search_impl(fstat_plan_t p, int segment, const Grid& g, int 
     // profiling on, the sky stage stays on `st`, so that each timed kernel runs alone.
     const int nbatch = (nsky + p->Sb - 1) / p->Sb;
     hipStream_t sst = (p->profiling || p->single_stream) ? st : p->sstream;
+    const bool dec = use_dec(p, si, g, mode);
+    if (dec) {
+      FSTAT_LAUNCH(k_route, dim3(1), dim3(1024), 0, st, g.fdot, g.nfdot, si.s.dt, g.w_spin, g.nsky, g.s_lo, g.m11,
+                   (int)si.s.n, d.route());
+      HIP_TRY(p, launch_status(), "path flag launch");
+    }
     if (sst != st) {
       HIP_TRY(p, hipEventRecord(p->ev_fork, st), "sky stream fork");
       HIP_TRY(p, hipStreamWaitEvent(sst, p->ev_fork, 0), "sky stream fork");
@@ -831,7 +980,7 @@ static fstat_status search_impl(fstat_plan_t p, int segment, const Grid& g, int 
       db.buf = b & 1;
       if (b >= 2 && sst != st) HIP_TRY(p, hipStreamWaitEvent(sst, p->ev_tmpl[b & 1], 0), "sky stream order");
       const int sky0 = b * p->Sb;
-      fstat_status r = run_sky_batch<T>(p, db, si, g.alpha, g.delta, sky0, std::min(p->Sb, nsky - sky0), sst);
+      fstat_status r = run_sky_batch<T>(p, db, si, g.alpha, g.delta, sky0, std::min(p->Sb, nsky - sky0), dec, sst);
       if (r != FSTAT_OK) return r;
       if (sst != st) HIP_TRY(p, hipEventRecord(p->ev_sky[b & 1], sst), "sky stream order");
       return FSTAT_OK;
@@ -848,7 +997,7 @@ static fstat_status search_impl(fstat_plan_t p, int segment, const Grid& g, int 
       Dev<T> db = d;
       db.buf = b & 1;
       const int sky0 = b * p->Sb;
-      r = run_templates<T>(p, db, si, sky0, std::min(p->Sb, nsky - sky0), g, mode, oa, st);
+      r = run_templates<T>(p, db, si, sky0, std::min(p->Sb, nsky - sky0), g, mode, oa, dec, st);
       if (r != FSTAT_OK) return r;
       if (sst != st) HIP_TRY(p, hipEventRecord(p->ev_tmpl[b & 1], st), "sky stream order");
     }
@@ -1452,6 +1601,13 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
       si.tL = si.tP * si.tQ;
       si.ibw = interbin_weight(s.n, si.tL);
     }
+    // decimated template transforms: mixed precision, bins below nfft/2, and the decimated
+    // series, filter tails included, within the transform
+    si.dQ = 5 * si.tQ / 8;
+    si.dL = 5 * (si.tL / 8);
+    si.dn = dec_samples(s.n);
+    si.dec = !p->fp64 && si.tQ >= 64 && si.kmax <= si.nfft / 2 && si.dn <= si.dL &&
+             !(opt.interbinning && si.tP > 512);
     if (si.kmax > si.nfft) {
       std::snprintf(msg, sizeof msg, "segment %d: k_max=%d beyond nfft=%d", i, si.kmax, si.nfft);
       delete p;
@@ -1462,12 +1618,15 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
     p->L_max = std::max(p->L_max, (long)si.nfft);
     p->TL_max = std::max(p->TL_max, (long)si.tL);
     p->M_max = std::max(p->M_max, (long)si.M);
+    if (si.dec) p->dn_max = std::max(p->dn_max, si.dn);
   }
   p->nblk_max = (int)((p->n_max + NT - 1) / NT);
 
-  // batch sizes: requested or defaults, shrunk to the budget (admission)
-  int Sb = opt.skies_per_batch ? opt.skies_per_batch : (p->fp64 ? 4 : 8);
-  int B = opt.templates_per_launch ? opt.templates_per_launch : (p->fp64 ? 16 : 256);
+  // batch sizes: requested or defaults, shrunk to the budget (admission).  Mixed precision:
+  // 16 sky positions (8 leave the per-sky kernels too few workgroups: 24 against 14 us a
+  // sky position) and 512 templates (256: 3% slower, more launches of the path not taken)
+  int Sb = opt.skies_per_batch ? opt.skies_per_batch : (p->fp64 ? 4 : 16);
+  int B = opt.templates_per_launch ? opt.templates_per_launch : (p->fp64 ? 16 : 512);
   bool tuned = false;
   if (!opt.skies_per_batch && !opt.templates_per_launch && opt.tuning_cache_path) {
     int tb = 0, ts = 0, tv = 0;
@@ -1484,6 +1643,8 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
   (void)tuned;
   const size_t budget = opt.workspace_budget_bytes;
   if (budget) {
+    // a budget that only the full-rate transforms fit is served by them
+    if (layout(p, 1, 1, false) > budget) p->dn_max = 0;
     if (layout(p, 1, 1, false) > budget) {
       char msg[200];
       std::snprintf(msg, sizeof msg, "largest segment needs %zu workspace bytes with one sky and one template; budget %zu",
@@ -1522,6 +1683,12 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
   std::vector<unsigned char> tb;
   fill_tables<float>(tb, p->tab, 0, KT_F32);
   fill_tables<double>(tb, p->tab, 1, KT_F64);
+  {
+    std::vector<int> logs;
+    for (auto& si : p->segs)
+      if (si.dec) logs.push_back(si.tlog);
+    if (!logs.empty()) fill_dec_tables(tb, p->tab, logs);
+  }
   p->tab.bytes = tb.size();
   if ((e = hipMalloc(&p->tab.dev, tb.size())) != hipSuccess ||
       (e = hipMemcpy(p->tab.dev, tb.data(), tb.size(), hipMemcpyHostToDevice)) != hipSuccess ||
@@ -1824,7 +1991,7 @@ template <typename T>
 static fstat_status sky_stages_impl(fstat_plan_t plan, const SegInfo& si, const double* ad, double* abc, void* za,
                                     void* zb, void* ua, void* ub, void* zta, void* ztb, hipStream_t st) {
   Dev<T> d(plan);
-  fstat_status r = run_sky_batch<T>(plan, d, si, ad, ad + 1, 0, 1, st);
+  fstat_status r = run_sky_batch<T>(plan, d, si, ad, ad + 1, 0, 1, false, st);
   if (r != FSTAT_OK) return r;
   const size_t n = si.s.n, M = si.M, L = si.nfft, cb = sizeof(cx<T>);
   cx<T>* zab = d.sky();

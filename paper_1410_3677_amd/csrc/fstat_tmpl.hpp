@@ -372,56 +372,60 @@ __global__ void __launch_bounds__((tmpl_nt_a<T, Q>())) k_tmpl_a(TmplArgs ta, con
   static_assert(PB1 >= 1 && NB1 % G == 0, "first stage must give each thread whole butterflies");
   static_assert(R1 < Q, "at least two stages");
   __shared__ cx<T> lds[TW * ST];
-  int tile, item;
-  xcd_tile_item(ta.P / TW, tile, item);
-  const int c = threadIdx.x % TW, g = threadIdx.x / TW;
-  const int t = ta.t0 + item;
-  const int skyl = t / ta.nfdot, sidx = t % ta.nfdot;
-  double c2, c1;
-  template_chirp(ta, skyl, sidx, c2, c1);
-  const cx<T>* za = zt + (long)(2 * skyl) * ta.ldzt;
-  const cx<T>* zb = za + ta.ldzt;
-  const int j1 = tile * TW + c;
-  cx<T>* col = lds + c * ST;
-  // first stage: y[j1 + P j2] with the spindown chirp, radix-R1 butterflies in registers
-  cx<T> va[PB1][R1], vb[PB1][R1];
-  chirped_first_stage<T, Q, G, R1, NB1, PB1, RNZ>(va, vb, za, zb, j1, g, ta.P, ta.n, c2, c1);
-  // twiddles W^(j1 k2) of the last-stage outputs k2 = j + NSL r: W^(j1 j) times powers of W^(j1 NSL)
-  constexpr int NSL = last_ns<Q, 1>();
-  constexpr int RL = stage_radix<Q, NSL>();
-  constexpr int PBL = (Q / RL) / G;
-  cx<T> tw[PBL][RL];
-  {
-    const cx<T> step = twiddle_L<T, false>(twlo, twhi, j1 * NSL);
+  if (ta.route && *ta.route != ta.route_want) return;
+  for (int blk = blockIdx.x; blk < ta.nblk; blk += gridDim.x) {
+    if (blk != (int)blockIdx.x) __syncthreads();  // the previous tile has been read
+    int tile, item;
+    xcd_tile_item(blk, ta.P / TW, tile, item);
+    const int c = threadIdx.x % TW, g = threadIdx.x / TW;
+    const int t = ta.t0 + item;
+    const int skyl = t / ta.nfdot, sidx = t % ta.nfdot;
+    double c2, c1;
+    template_chirp(ta, skyl, sidx, c2, c1);
+    const cx<T>* za = zt + (long)(2 * skyl) * ta.ldzt;
+    const cx<T>* zb = za + ta.ldzt;
+    const int j1 = tile * TW + c;
+    cx<T>* col = lds + c * ST;
+    // first stage: y[j1 + P j2] with the spindown chirp, radix-R1 butterflies in registers
+    cx<T> va[PB1][R1], vb[PB1][R1];
+    chirped_first_stage<T, Q, G, R1, NB1, PB1, RNZ>(va, vb, za, zb, j1, g, ta.P, ta.n, c2, c1);
+    // twiddles W^(j1 k2) of the last-stage outputs k2 = j + NSL r: W^(j1 j) times powers of W^(j1 NSL)
+    constexpr int NSL = last_ns<Q, 1>();
+    constexpr int RL = stage_radix<Q, NSL>();
+    constexpr int PBL = (Q / RL) / G;
+    cx<T> tw[PBL][RL];
+    {
+      const cx<T> step = twiddle_L<T, false>(twlo, twhi, j1 * NSL);
 #pragma unroll
-    for (int b = 0; b < PBL; ++b) {
-      cx<T> w = twiddle_L<T, false>(twlo, twhi, j1 * (g + G * b));
+      for (int b = 0; b < PBL; ++b) {
+        cx<T> w = twiddle_L<T, false>(twlo, twhi, j1 * (g + G * b));
 #pragma unroll
-      for (int r = 0; r < RL; ++r) {
-        tw[b][r] = w;
-        if (r + 1 < RL) w = cmul(w, step);
+        for (int r = 0; r < RL; ++r) {
+          tw[b][r] = w;
+          if (r + 1 < RL) w = cmul(w, step);
+        }
       }
     }
-  }
-  // series a's outputs wait in registers so that both series leave as (a, b) pairs
-  cx<T> ka[PBL][RL];
+    // series a's outputs wait in registers so that both series leave as (a, b) pairs
+    cx<T> ka[PBL][RL];
 #pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    if (s == 1) __syncthreads();  // series a's last stage has read the tile
-    stage_to_lds_off<T, Q, G, 1, R1, PB1>(s == 0 ? va : vb, col, g);
-    __syncthreads();
-    middle_stages1_off<T, Q, G, R1, false>(col, g, twst);
-    cx<T> v[PBL][RL];
-    stage_from_lds_off<T, Q, G, NSL, RL, PBL, false>(v, col, g, twst);
-    cx<T>* out = tbuf + (long)(2 * item) * ta.L;
+    for (int s = 0; s < 2; ++s) {
+      if (s == 1) __syncthreads();  // series a's last stage has read the tile
+      stage_to_lds_off<T, Q, G, 1, R1, PB1>(s == 0 ? va : vb, col, g);
+      __syncthreads();
+      middle_stages1_off<T, Q, G, R1, false>(col, g, twst);
+      cx<T> v[PBL][RL];
+      stage_from_lds_off<T, Q, G, NSL, RL, PBL, false>(v, col, g, twst);
+      cx<T>* out = tbuf + (long)(2 * item) * ta.L;
 #pragma unroll
-    for (int b = 0; b < PBL; ++b) {
-      const int j = g + G * b;
+      for (int b = 0; b < PBL; ++b) {
+        const int j = g + G * b;
 #pragma unroll
-      for (int r = 0; r < RL; ++r) {
-        const unsigned o = (unsigned)(j + NSL * r) * (unsigned)ta.P + (unsigned)j1;
-        if (s == 0) ka[b][r] = cmul(v[b][r], tw[b][r]);
-        else store_pair(out, o, ka[b][r], cmul(v[b][r], tw[b][r]));
+        for (int r = 0; r < RL; ++r) {
+          const unsigned o = (unsigned)(j + NSL * r) * (unsigned)ta.P + (unsigned)j1;
+          if (s == 0) ka[b][r] = cmul(v[b][r], tw[b][r]);
+          else store_pair(out, o, ka[b][r], cmul(v[b][r], tw[b][r]));
+        }
       }
     }
   }
@@ -444,42 +448,252 @@ __global__ void __launch_bounds__((tmpl_nt_a<T, Q>())) k_tmpl_a_pair(TmplArgs ta
   static_assert(PB1 >= 1 && NB1 % G == 0, "first stage must give each thread whole butterflies");
   static_assert(R1 < Q, "at least two stages");
   __shared__ cx<T> lds[2 * TW * ST];
+  if (ta.route && *ta.route != ta.route_want) return;
+  for (int blk = blockIdx.x; blk < ta.nblk; blk += gridDim.x) {
+    if (blk != (int)blockIdx.x) __syncthreads();  // the previous tile has been read
+    int tile, item;
+    xcd_tile_item(blk, ta.P / TW, tile, item);
+    const int c = threadIdx.x % TW, g = threadIdx.x / TW;
+    const int t = ta.t0 + item;
+    const int skyl = t / ta.nfdot, sidx = t % ta.nfdot;
+    double c2, c1;
+    template_chirp(ta, skyl, sidx, c2, c1);
+    const cx<T>* za = zt + (long)(2 * skyl) * ta.ldzt;
+    const cx<T>* zb = za + ta.ldzt;
+    const int j1 = tile * TW + c;
+    cx<T>* cola = lds + c * ST;
+    cx<T>* colb = lds + (TW + c) * ST;
+    {
+      cx<T> va[PB1][R1], vb[PB1][R1];
+      chirped_first_stage<T, Q, G, R1, NB1, PB1, RNZ>(va, vb, za, zb, j1, g, ta.P, ta.n, c2, c1);
+      stage_to_lds_off<T, Q, G, 1, R1, PB1>(va, cola, g);
+      stage_to_lds_off<T, Q, G, 1, R1, PB1>(vb, colb, g);
+      __syncthreads();
+    }
+    middle_stages_off<T, Q, G, R1, false>(cola, colb, g, twst);
+    constexpr int NSL = last_ns<Q, 1>();
+    constexpr int RL = stage_radix<Q, NSL>();
+    constexpr int PBL = (Q / RL) / G;
+    cx<T> va[PBL][RL], vb[PBL][RL];
+    stage_from_lds_off<T, Q, G, NSL, RL, PBL, false>(va, cola, g, twst);
+    stage_from_lds_off<T, Q, G, NSL, RL, PBL, false>(vb, colb, g, twst);
+    cx<T>* out = tbuf + (long)(2 * item) * ta.L;
+    const cx<T> step = twiddle_L<T, false>(twlo, twhi, j1 * NSL);
+#pragma unroll
+    for (int b = 0; b < PBL; ++b) {
+      const int j = g + G * b;
+      cx<T> w = twiddle_L<T, false>(twlo, twhi, j1 * j);
+#pragma unroll
+      for (int r = 0; r < RL; ++r) {
+        const unsigned o = (unsigned)(j + NSL * r) * (unsigned)ta.P + (unsigned)j1;
+        store_pair(out, o, cmul(va[b][r], w), cmul(vb[b][r], w));
+        if (r + 1 < RL) w = cmul(w, step);
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------- pass A of the decimated transforms
+// L' = 5 L / 8 points (fstat_kernels.hpp, "decimated series"): P columns as in the general
+// first pass, of LEN = 5 Q / 8 points each: radix 5, then 8s, then 4 or 2.  A workgroup
+// takes 2560 / LEN columns (eight of 320 points: one 128-byte (a, b) line per row of the
+// intermediate) of both series; its 320 threads hold one radix-8 butterfly each per stage
+// and 1.6 radix-5 ones in the first, of whose five inputs only the first RNZ can be
+// nonzero (n' <= RNZ L' / 5).  The LDS tile holds the two series of a position side by
+// side, columns fastest ([index][column][a|b]): one 16-byte access serves both series, a
+// wavefront's accesses are contiguous, no padding is needed and four workgroups (40 KB
+// each) fit a compute unit.  Bound by the HBM writes of the intermediate: 0.49 us per
+// template of L = 2^18 (2.62 MB, 5.3 TB/s), against 0.74 us for the general first pass's
+// 4.19 MB; separate, padded series planes (three workgroups per compute unit) took 0.67, a
+// loop over four templates per workgroup (137 registers) 0.69.
+constexpr int DEC_A_NT = 320;
+template <int LEN>
+__host__ __device__ constexpr int dec_tw() { return 2560 / LEN; }
+template <int LEN, int NS>
+__host__ __device__ constexpr int dec_radix() { return NS == 1 ? 5 : (LEN / NS >= 8 ? 8 : LEN / NS); }
+template <typename T>
+struct alignas(4 * sizeof(T)) cx_pair { cx<T> a, b; };
+// Stage twiddles exp(-2 pi i k r / (NS R)), [k][r - 1], NS in {5, 40, 320} and R in {2, 4, 8}.
+__host__ __device__ constexpr int dec_tw_offset(int NS, int R) {
+  int off = 0;
+  for (int ns = 5; ns <= 320; ns *= 8)
+    for (int rr = 2; rr <= 8; rr *= 2) {
+      if (ns == NS && rr == R) return off;
+      off += ns * (rr - 1);
+    }
+  return -1;
+}
+constexpr int DEC_TW_ENTRIES = (5 + 40 + 320) * 11;
+
+// Forward 5-point DFT of v[0 .. NZ-1], the other inputs zero.
+template <typename T, int NZ>
+__device__ __forceinline__ void dft5(cx<T>* v) {
+  const T c1 = (T)0.30901699437494742410, s1 = (T)0.95105651629515357212;
+  const T c2 = (T)-0.80901699437494742410, s2 = (T)0.58778525229247312917;
+  const cx<T> z = mk<T>(0, 0);
+  const cx<T> x0 = v[0], x1 = v[1], x2 = NZ > 2 ? v[2] : z, x3 = NZ > 3 ? v[3] : z, x4 = NZ > 4 ? v[4] : z;
+  const cx<T> p1 = NZ > 4 ? x1 + x4 : x1, m1 = NZ > 4 ? x1 - x4 : x1;
+  const cx<T> p2 = NZ > 3 ? x2 + x3 : x2, m2 = NZ > 3 ? x2 - x3 : x2;
+  cx<T> t1, t2, u1, u2;   // even and odd parts; outputs t -+ i u
+  if constexpr (NZ > 2) {
+    t1 = mk<T>(x0.re + (c1 * p1.re + c2 * p2.re), x0.im + (c1 * p1.im + c2 * p2.im));
+    t2 = mk<T>(x0.re + (c2 * p1.re + c1 * p2.re), x0.im + (c2 * p1.im + c1 * p2.im));
+    u1 = mk<T>(s1 * m1.re + s2 * m2.re, s1 * m1.im + s2 * m2.im);
+    u2 = mk<T>(s2 * m1.re - s1 * m2.re, s2 * m1.im - s1 * m2.im);
+    v[0] = x0 + (p1 + p2);
+  } else {
+    t1 = mk<T>(x0.re + c1 * p1.re, x0.im + c1 * p1.im);
+    t2 = mk<T>(x0.re + c2 * p1.re, x0.im + c2 * p1.im);
+    u1 = mk<T>(s1 * m1.re, s1 * m1.im);
+    u2 = mk<T>(s2 * m1.re, s2 * m1.im);
+    v[0] = x0 + p1;
+  }
+  v[1] = mk<T>(t1.re + u1.im, t1.im - u1.re);
+  v[4] = mk<T>(t1.re - u1.im, t1.im + u1.re);
+  v[2] = mk<T>(t2.re + u2.im, t2.im - u2.re);
+  v[3] = mk<T>(t2.re - u2.im, t2.im + u2.re);
+}
+
+// One butterfly's inputs of the stage at stride NS from the tile, twiddled and transformed:
+// p points at index j of the thread's column, inputs r LEN / R indices apart.
+template <typename T, int LEN, int NS>
+__device__ __forceinline__ void dec_stage(cx<T>* va, cx<T>* vb, const cx_pair<T>* p, int j,
+                                          const cx<T>* __restrict__ tw5) {
+  constexpr int R = dec_radix<LEN, NS>(), TW = dec_tw<LEN>(), NB = LEN / R;
+  const cx<T>* tw = tw5 + dec_tw_offset(NS, R) + (j % NS) * (R - 1);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const cx_pair<T> v = p[r * NB * TW];
+    va[r] = v.a;
+    vb[r] = v.b;
+    if (r > 0) {
+      const cx<T> w = tw[r - 1];
+      va[r] = cmul(va[r], w);
+      vb[r] = cmul(vb[r], w);
+    }
+  }
+  dftr<T, R, false>(va);
+  dftr<T, R, false>(vb);
+}
+
+// The stages after the first up to, not including, the last, for both series.
+template <typename T, int LEN, int NS>
+__device__ __forceinline__ void dec_middle(cx_pair<T>* lds, const cx<T>* __restrict__ tw5) {
+  constexpr int R = dec_radix<LEN, NS>();
+  if constexpr (NS * R < LEN) {
+    constexpr int TW = dec_tw<LEN>(), NB = LEN / R, TB = TW * NB;
+    constexpr int PER = TB / DEC_A_NT;
+    static_assert(TB % DEC_A_NT == 0, "whole butterflies per thread");
+    cx<T> va[PER][R], vb[PER][R];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int b = (int)threadIdx.x + i * DEC_A_NT;   // index j, column c: b = TW j + c
+      dec_stage<T, LEN, NS>(va[i], vb[i], lds + b, b / TW, tw5);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int b = (int)threadIdx.x + i * DEC_A_NT, c = b % TW, j = b / TW;
+      cx_pair<T>* p = lds + ((j / NS) * NS * R + j % NS) * TW + c;
+#pragma unroll
+      for (int r = 0; r < R; ++r) p[r * NS * TW] = cx_pair<T>{va[i][r], vb[i][r]};
+    }
+    __syncthreads();
+    dec_middle<T, LEN, NS * R>(lds, tw5);
+  }
+}
+
+template <int LEN, int NS>
+__host__ __device__ constexpr int dec_last_ns() {
+  if constexpr (NS * dec_radix<LEN, NS>() >= LEN) return NS;
+  else return dec_last_ns<LEN, NS * dec_radix<LEN, NS>()>();
+}
+
+template <typename T, int LEN, int RNZ>
+__global__ void __launch_bounds__(DEC_A_NT) k_tmpl_a_dec(TmplArgs ta, const cx<T>* __restrict__ zd,
+                                                         cx<T>* __restrict__ tbuf, const cx<T>* __restrict__ tw5,
+                                                         const cx<T>* __restrict__ twlo,
+                                                         const cx<T>* __restrict__ twhi) {
+  constexpr int TW = dec_tw<LEN>();
+  typedef cx_pair<T> pair;
+  __shared__ pair lds[LEN * TW];
+  const int go = *ta.route;   // tested once the loads are on their way
   int tile, item;
-  xcd_tile_item(ta.P / TW, tile, item);
-  const int c = threadIdx.x % TW, g = threadIdx.x / TW;
+  xcd_tile_item(blockIdx.x, ta.P / TW, tile, item);
   const int t = ta.t0 + item;
   const int skyl = t / ta.nfdot, sidx = t % ta.nfdot;
-  double c2, c1;
-  template_chirp(ta, skyl, sidx, c2, c1);
-  const cx<T>* za = zt + (long)(2 * skyl) * ta.ldzt;
-  const cx<T>* zb = za + ta.ldzt;
-  const int j1 = tile * TW + c;
-  cx<T>* cola = lds + c * ST;
-  cx<T>* colb = lds + (TW + c) * ST;
   {
-    cx<T> va[PB1][R1], vb[PB1][R1];
-    chirped_first_stage<T, Q, G, R1, NB1, PB1, RNZ>(va, vb, za, zb, j1, g, ta.P, ta.n, c2, c1);
-    stage_to_lds_off<T, Q, G, 1, R1, PB1>(va, cola, g);
-    stage_to_lds_off<T, Q, G, 1, R1, PB1>(vb, colb, g);
-    __syncthreads();
-  }
-  middle_stages_off<T, Q, G, R1, false>(cola, colb, g, twst);
-  constexpr int NSL = last_ns<Q, 1>();
-  constexpr int RL = stage_radix<Q, NSL>();
-  constexpr int PBL = (Q / RL) / G;
-  cx<T> va[PBL][RL], vb[PBL][RL];
-  stage_from_lds_off<T, Q, G, NSL, RL, PBL, false>(va, cola, g, twst);
-  stage_from_lds_off<T, Q, G, NSL, RL, PBL, false>(vb, colb, g, twst);
-  cx<T>* out = tbuf + (long)(2 * item) * ta.L;
-  const cx<T> step = twiddle_L<T, false>(twlo, twhi, j1 * NSL);
+    // first stage: the chirp in units of decimated samples, one radix-5 butterfly
+    constexpr int NB = LEN / 5, TB = TW * NB, PER = (TB + DEC_A_NT - 1) / DEC_A_NT;
+    const pair* z = reinterpret_cast<const pair*>(zd + (long)(2 * skyl) * ta.ldzt);
+    cx<T> va[PER][5], vb[PER][5];
 #pragma unroll
-  for (int b = 0; b < PBL; ++b) {
-    const int j = g + G * b;
+    for (int i = 0; i < PER; ++i) {
+      const int b = (int)threadIdx.x + i * DEC_A_NT;   // column b % TW, index b / TW
+      const unsigned m0 = (unsigned)(tile * TW + b % TW) + (unsigned)ta.P * (unsigned)(b / TW);
+#pragma unroll
+      for (int r = 0; r < RNZ; ++r) {
+        const unsigned m = m0 + (unsigned)(NB * r) * (unsigned)ta.P;
+        va[i][r] = vb[i][r] = mk<T>(0, 0);
+        if ((TB % DEC_A_NT == 0 || b < TB) && m < (unsigned)ta.n) {
+          const pair v = z[m];
+          va[i][r] = v.a;
+          vb[i][r] = v.b;
+        }
+      }
+    }
+    if (go != ta.route_want) return;
+    double c2, c1;
+    template_chirp(ta, skyl, sidx, c2, c1);
+    c2 *= (double)(DEC_DOWN * DEC_DOWN) / (DEC_UP * DEC_UP);
+    c1 *= (double)DEC_DOWN / DEC_UP;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int b = (int)threadIdx.x + i * DEC_A_NT, c = b % TW, j = b / TW;
+      if (TB % DEC_A_NT == 0 || b < TB) {
+        const int m0 = tile * TW + c + ta.P * j - DEC_M0;
+#pragma unroll
+        for (int r = 0; r < RNZ; ++r) {
+          const double x = (double)(m0 + NB * r * ta.P);
+          double cyc = fma(c2, x, c1) * x;
+          cyc = __builtin_amdgcn_fract(cyc);
+          T s, co;
+          if constexpr (sizeof(T) == 8) {
+            sincospi(2.0 * cyc, &s, &co);
+          } else {
+            const float cf = (float)cyc;   // the hardware sine and cosine take cycles
+            s = __builtin_amdgcn_sinf(cf);
+            co = __builtin_amdgcn_cosf(cf);
+          }
+          const cx<T> w = mk<T>(co, -s);
+          va[i][r] = cmul(va[i][r], w);
+          vb[i][r] = cmul(vb[i][r], w);
+        }
+        dft5<T, RNZ>(va[i]);
+        dft5<T, RNZ>(vb[i]);
+        pair* p = lds + 5 * j * TW + c;
+#pragma unroll
+        for (int r = 0; r < 5; ++r) p[r * TW] = pair{va[i][r], vb[i][r]};
+      }
+    }
+  }
+  __syncthreads();
+  dec_middle<T, LEN, 5>(lds, tw5);
+  // last stage, times W^(j1 k2) for its outputs k2 = j + NSL r
+  constexpr int NSL = dec_last_ns<LEN, 1>(), RL = dec_radix<LEN, NSL>(), NB = LEN / RL;
+  constexpr int TB = TW * NB, PER = TB / DEC_A_NT;
+  static_assert(TB % DEC_A_NT == 0, "whole butterflies per thread");
+  cx<T>* out = tbuf + (long)(2 * item) * ta.L;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int b = (int)threadIdx.x + i * DEC_A_NT, j = b / TW, j1 = tile * TW + b % TW;
+    cx<T> va[RL], vb[RL];
+    dec_stage<T, LEN, NSL>(va, vb, lds + b, j, tw5);
+    const cx<T> step = twiddle_L<T, false>(twlo, twhi, j1 * NSL);
     cx<T> w = twiddle_L<T, false>(twlo, twhi, j1 * j);
 #pragma unroll
     for (int r = 0; r < RL; ++r) {
-      const unsigned o = (unsigned)(j + NSL * r) * (unsigned)ta.P + (unsigned)j1;
-      store_pair(out, o, cmul(va[b][r], w), cmul(vb[b][r], w));
+      store_pair(out, (unsigned)(j + NSL * r) * (unsigned)ta.P + (unsigned)j1, cmul(va[r], w), cmul(vb[r], w));
       if (r + 1 < RL) w = cmul(w, step);
     }
   }
@@ -522,7 +736,7 @@ __global__ void __launch_bounds__((tmpl_nt_b<T, P>())) k_tmpl_b(TmplArgs ta, con
   __shared__ cx<T> lds[2 * TW * ST];
   __shared__ unsigned long long sbase;
   int tile, item;
-  xcd_tile_item(ta.Q / TW, tile, item);
+  xcd_tile_item(blockIdx.x, ta.Q / TW, tile, item);
   const int c = threadIdx.x / G, g = threadIdx.x % G;
   const int t = ta.t0 + item;
   const int skyl = t / ta.nfdot, sidx = t % ta.nfdot;
@@ -731,6 +945,31 @@ __global__ void __launch_bounds__(256) k_interbin_2f(TmplArgs ta, const SkyParam
 // and unit that has any.  When the searched bins are exactly [0, nfft/2) (HALF), the
 // last stage computes only the outputs k1 < P/2 and no bin needs a range check.
 
+// The bins a streaming second pass forms: any range (every output formed, each bin checked),
+// exactly [0, nfft/2) (half the outputs, no checks), or, of a decimated transform of
+// L' = 5 L / 8 points, exactly [0, L/2) (outputs k1 < 4 P / 5; only those around the end
+// checked) or a range within it.
+enum Band { BAND_ANY = 0, BAND_HALF = 1, BAND_DEC = 2, BAND_DEC_RANGE = 3 };
+
+// Of a lane's last-stage outputs k1 = k0 .. k0 + G - 1 (k0 a compile-time constant): whether
+// any can be a searched bin, and whether all of them always are.
+template <int P, int BAND>
+__host__ __device__ constexpr bool band_keeps(int k0) {
+  return BAND >= BAND_DEC ? 5 * k0 < 4 * P : BAND == BAND_HALF ? k0 < P / 2 : true;
+}
+template <int P, int G, int BAND>
+__host__ __device__ constexpr bool band_inside(int k0) {
+  return BAND == BAND_HALF || (BAND == BAND_DEC && 5 * (k0 + G) <= 4 * P);
+}
+// Outputs r < band_outputs of the RL of a last-stage butterfly are formed.
+template <int P, int NSL, int RL, int BAND>
+__host__ __device__ constexpr int band_outputs() {
+  int n = 0;
+  for (int r = 0; r < RL; ++r)
+    if (band_keeps<P, BAND>(NSL * r)) n = r + 1;
+  return n;
+}
+
 // Twiddles of the stage at stride NS and of all later stages, for butterflies j = g + G b.
 template <typename T, int LEN, int G, int NS, bool MORE = (NS < LEN)>
 struct StageTw {
@@ -936,7 +1175,7 @@ constexpr int CAP_BLOCK = 8;
 template <int P>
 __host__ __device__ constexpr int stream_rpw() { return 64 / groups_per_col<P>(); }
 
-template <typename T, int P, int MODE, bool HALF>
+template <typename T, int P, int MODE, int BAND>
 __global__ void __launch_bounds__(256) k_tmpl_b_stream(TmplArgs ta, int ntmpl, const SkyParams* __restrict__ sp,
                                                        const cx<T>* __restrict__ tbuf, OutArgs oa,
                                                        const cx<T>* __restrict__ twst) {
@@ -950,9 +1189,11 @@ __global__ void __launch_bounds__(256) k_tmpl_b_stream(TmplArgs ta, int ntmpl, c
   constexpr int NSL = last_ns<P, 1>();
   constexpr int RL = stage_radix<P, NSL>();
   constexpr int PBL = (P / RL) / G;
-  constexpr int ROUT = HALF ? RL / 2 : RL;
+  constexpr bool HALF = BAND == BAND_HALF;
+  constexpr int ROUT = band_outputs<P, NSL, RL, BAND>();
   constexpr int NOUT = PBL * ROUT;
   static_assert(NOUT <= 32, "output mask");
+  if (ta.route && *ta.route != ta.route_want) return;
   __shared__ cx<T> lds[4 * 2 * RPW * ST];
   // per-wavefront candidate staging: (template of the launch, bin, 2F)
   __shared__ int st_item[4][STAGE_CAP];
@@ -1020,8 +1261,9 @@ __global__ void __launch_bounds__(256) k_tmpl_b_stream(TmplArgs ta, int ntmpl, c
       for (int b = 0; b < PBL; ++b)
 #pragma unroll
         for (int r = 0; r < ROUT; ++r) {
+          if (!band_keeps<P, BAND>(G * b + NSL * r)) continue;
           const int k = ta.Q * (g + G * b + NSL * r) + k2;
-          if (HALF || (k >= oa.k_min && k < oa.k_max))
+          if (band_inside<P, G, BAND>(G * b + NSL * r) || (k >= oa.k_min && k < oa.k_max))
             out[k - oa.k_min] = two_f_value(fa[b][r], fb[b][r], cfa, cfb, cfab);
         }
     } else {
@@ -1039,11 +1281,13 @@ __global__ void __launch_bounds__(256) k_tmpl_b_stream(TmplArgs ta, int ntmpl, c
       for (int b = 0; b < PBL; ++b)
 #pragma unroll
         for (int r = 0; r < ROUT; ++r) {
+          val[b * ROUT + r] = (T)0;
+          if (!band_keeps<P, BAND>(G * b + NSL * r)) continue;
           const int k1 = g + G * b + NSL * r;
           const int k = ta.Q * k1 + k2;
           const T v = two_f_value(fa[b][r], fb[b][r], cfa, cfb, cfab);
           val[b * ROUT + r] = v;
-          const bool inr = HALF || (k >= oa.k_min && k < oa.k_max);
+          const bool inr = band_inside<P, G, BAND>(G * b + NSL * r) || (k >= oa.k_min && k < oa.k_max);
           if (MODE == 2) srow[(long)(k1 / CAP_BLOCK) * ta.Q * CAP_BLOCK + k1 % CAP_BLOCK] = (float)v;
           if (inr && v > thr) mask |= 1u << (b * ROUT + r);
         }
@@ -1064,7 +1308,7 @@ __global__ void __launch_bounds__(256) k_tmpl_b_stream(TmplArgs ta, int ntmpl, c
 // registers; workgroup barriers order the stages.  MODE 0: threshold and candidates
 // (staged per wavefront), MODE 1: the 2F spectrum.  With HALF (bins [0, nfft/2)) the
 // radix-2 last stage forms only the outputs k1 < P/2.
-template <int MODE, bool HALF, int NT>
+template <int MODE, int BAND, int NT>
 __global__ void __launch_bounds__(NT) k_tmpl_b_stream2(TmplArgs ta, int ntmpl, const SkyParams* __restrict__ sp,
                                                         const cx<float>* __restrict__ tbuf, OutArgs oa,
                                                         const cx<float>* __restrict__ twst) {
@@ -1080,9 +1324,11 @@ __global__ void __launch_bounds__(NT) k_tmpl_b_stream2(TmplArgs ta, int ntmpl, c
   constexpr int NSL = last_ns<P, 1>();
   constexpr int RL = stage_radix<P, NSL>();
   constexpr int PBL = (P / RL) / G;
-  constexpr int ROUT = HALF ? RL / 2 : RL;
+  constexpr bool HALF = BAND == BAND_HALF;
+  constexpr int ROUT = band_outputs<P, NSL, RL, BAND>();
   constexpr int NOUT = PBL * ROUT;
   static_assert(NOUT <= 32, "output mask");
+  if (ta.route && *ta.route != ta.route_want) return;
   static_assert(MODE == 0 || MODE == 1, "threshold or spectrum");
   __shared__ cx<T> lds[2 * RPB * ST];
   // per-wavefront candidate staging: (template of the launch, bin, 2F)
@@ -1143,8 +1389,9 @@ __global__ void __launch_bounds__(NT) k_tmpl_b_stream2(TmplArgs ta, int ntmpl, c
       for (int b = 0; b < PBL; ++b)
 #pragma unroll
         for (int r = 0; r < ROUT; ++r) {
+          if (!band_keeps<P, BAND>(G * b + NSL * r)) continue;
           const int k = ta.Q * (g + G * b + NSL * r) + k2;
-          if (HALF || (k >= oa.k_min && k < oa.k_max))
+          if (band_inside<P, G, BAND>(G * b + NSL * r) || (k >= oa.k_min && k < oa.k_max))
             out[k - oa.k_min] = two_f_value(fa[b][r], fb[b][r], cfa, cfb, cfab);
         }
     } else {
@@ -1154,10 +1401,13 @@ __global__ void __launch_bounds__(NT) k_tmpl_b_stream2(TmplArgs ta, int ntmpl, c
       for (int b = 0; b < PBL; ++b)
 #pragma unroll
         for (int r = 0; r < ROUT; ++r) {
+          val[b * ROUT + r] = (T)0;
+          if (!band_keeps<P, BAND>(G * b + NSL * r)) continue;
           const int k = ta.Q * (g + G * b + NSL * r) + k2;
           const T v = two_f_value(fa[b][r], fb[b][r], cfa, cfb, cfab);
           val[b * ROUT + r] = v;
-          if ((HALF || (k >= oa.k_min && k < oa.k_max)) && v > thr) mask |= 1u << (b * ROUT + r);
+          const bool inr = band_inside<P, G, BAND>(G * b + NSL * r) || (k >= oa.k_min && k < oa.k_max);
+          if (inr && v > thr) mask |= 1u << (b * ROUT + r);
         }
       stg.add<false>(oa, ta, search, lane, mask, val, item,
                      [&](int q) { return ta.Q * (g + G * (q / ROUT) + NSL * (q % ROUT)) + k2; });
@@ -1170,7 +1420,7 @@ __global__ void __launch_bounds__(NT) k_tmpl_b_stream2(TmplArgs ta, int ntmpl, c
 // The template transforms have L = nfft/2 points.  Bin 2k of the nfft grid is bin k of the
 // transform; bin 2k + 1 is w (X_k - X_{k+1 mod L}) for each series.  Bin k = Q k1 + k2 lies in
 // row k2 of the intermediate and its neighbour k + 1 in row k2 + 1 at the same k1 (for row
-// Q - 1: row 0 at k1 + 1).  A wavefront walks chunks of IB_CHUNK consecutive row units of
+// Q - 1: row 0 at k1 + 1).  A wavefront walks chunks of `ch` consecutive row units of
 // one template (chunks w, w + nw, ... of the launch, so that the rows in flight form one
 // window of HBM, as in k_tmpl_b_stream), and within a chunk the units in order: the
 // neighbour of a lane's output is one row later, at lane + G in the same unit or, for the
@@ -1185,10 +1435,11 @@ __global__ void __launch_bounds__(NT) k_tmpl_b_stream2(TmplArgs ta, int ntmpl, c
 // Flat output index o = b RO + r of a lane's outputs (k1 = g + G b + NSL r, r < RO).  For
 // g = G - 1 the output holding k1 + 1 is in lane 0 at ib_next(o): the same r in the next
 // butterfly, r + 1 in the first, or past the last (k1 + 1 = P/2 with HALF: the extra output
-// NO; k1 + 1 = P otherwise: output 0, since the transform is periodic).
+// NO; k1 + 1 = P otherwise: output 0, since the transform is periodic; of a decimated
+// transform that output is beyond the searched bins).
 template <int PBL, int RO, int RL>
 __host__ __device__ constexpr int ib_next(int o) {
-  return (o / RO + 1 < PBL) ? o + RO : (o % RO + 1 < RO ? o % RO + 1 : (RO < RL ? PBL * RO : 0));
+  return (o / RO + 1 < PBL) ? o + RO : (o % RO + 1 < RO ? o % RO + 1 : (2 * RO == RL ? PBL * RO : 0));
 }
 
 __device__ __forceinline__ cx<float> shfl_cx(cx<float> v, int src) {
@@ -1208,10 +1459,26 @@ __device__ __forceinline__ void dft_first_half_mid(cx<T>* v, cx<T>& mid) {
   dft_first_half<T, R>(v);
 }
 
-constexpr int IB_CHUNK = 16;
+// Row units of a chunk for `ntmpl` templates of `units` row units on `nw` wavefronts: the
+// divisor of units, 8 to 32 where there is one, that makes the busiest wavefront's walk the
+// shortest (its chunks, each with one unit more for the neighbours).  A fixed 16 left half
+// of the wavefronts idle in the second round of 2560 chunks on 2048 of them.
+inline int ib_chunk(int ntmpl, int units, long nw) {
+  int best = units;
+  long best_cost = -1;
+  for (int ch = units < 8 ? units : 8; ch <= units && (ch <= 32 || best_cost < 0); ++ch) {
+    if (units % ch) continue;
+    const long cost = ((long)ntmpl * (units / ch) + nw - 1) / nw * (ch + 1);
+    if (best_cost < 0 || cost < best_cost) {
+      best_cost = cost;
+      best = ch;
+    }
+  }
+  return best;
+}
 
-template <int P, int MODE, bool HALF>
-__global__ void __launch_bounds__(256) k_tmpl_b_ib(TmplArgs ta, int ntmpl, const SkyParams* __restrict__ sp,
+template <int P, int MODE, int BAND>
+__global__ void __launch_bounds__(256) k_tmpl_b_ib(TmplArgs ta, int ntmpl, int ch, const SkyParams* __restrict__ sp,
                                                    const cx<float>* __restrict__ tbuf, OutArgs oa,
                                                    const cx<float>* __restrict__ twst) {
   using T = float;
@@ -1225,7 +1492,9 @@ __global__ void __launch_bounds__(256) k_tmpl_b_ib(TmplArgs ta, int ntmpl, const
   constexpr int NSL = last_ns<P, 1>();
   constexpr int RL = stage_radix<P, NSL>();
   constexpr int PBL = (P / RL) / G;
-  constexpr int RO = HALF ? RL / 2 : RL;       // outputs kept per last-stage butterfly
+  constexpr bool HALF = BAND == BAND_HALF;
+  constexpr bool DEC = BAND >= BAND_DEC;
+  constexpr int RO = band_outputs<P, NSL, RL, BAND>();   // outputs kept per last-stage butterfly
   constexpr int NO = PBL * RO;                 // outputs per lane and series
   constexpr int NX = HALF ? NO + 1 : NO;       // plus output P/2 of the first butterfly
   constexpr int NV = 2 * NO;                   // 2F values per lane and unit: even and odd bins
@@ -1236,10 +1505,10 @@ __global__ void __launch_bounds__(256) k_tmpl_b_ib(TmplArgs ta, int ntmpl, const
   __shared__ float st_val[4][STAGE_CAP];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int units = ta.Q / RPW;                 // row units of one template (a power of two)
-  const int ch = units < IB_CHUNK ? units : IB_CHUNK;
-  const int lg_cpt = __builtin_ctz((unsigned)(units / ch));   // chunks per template, log2
-  const int nchunk = ntmpl << lg_cpt;           // chunks of the launch
+  if (ta.route && *ta.route != ta.route_want) return;
+  const int units = ta.Q / RPW;                 // row units of one template
+  const int cpt = units / ch;                   // chunks per template
+  const int nchunk = ntmpl * cpt;               // chunks of the launch
   const int nw = gridDim.x * 4;                 // wavefronts of the grid
   int c = blockIdx.x * 4 + wave;
   if (c >= nchunk) return;
@@ -1337,7 +1606,14 @@ __global__ void __launch_bounds__(256) k_tmpl_b_ib(TmplArgs ta, int ntmpl, const
           nb = inner ? qb : nb;
         }
       }
+      val[2 * o] = val[2 * o + 1] = (T)0;
+      if (!band_keeps<P, BAND>(G * (o / RO) + NSL * (o % RO))) continue;
       val[2 * o] = two_f(pa[o], pb[o], cross_c);
+      if constexpr (DEC) {
+        // the decimated transform's phase from one bin to the next
+        na = mk<T>(ta.ibpr * na.re - ta.ibpi * na.im, ta.ibpr * na.im + ta.ibpi * na.re);
+        nb = mk<T>(ta.ibpr * nb.re - ta.ibpi * nb.im, ta.ibpr * nb.im + ta.ibpi * nb.re);
+      }
       const cx<T> da = pa[o] - na, db = pb[o] - nb;
       val[2 * o + 1] = two_f(mk<T>(wib * da.re, wib * da.im), mk<T>(wib * db.re, wib * db.im), cross_c);
     }
@@ -1352,16 +1628,20 @@ __global__ void __launch_bounds__(256) k_tmpl_b_ib(TmplArgs ta, int ntmpl, const
       T* out = (T*)oa.spectrum + ((long)(ta.sky0 + skyl) * ta.nfdot + sidx) * (long)(oa.k_max - oa.k_min);
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
+        const int k0 = G * (v / 2 / RO) + NSL * (v / 2 % RO);
+        if (!band_keeps<P, BAND>(k0)) continue;
         const int k = bin_of(v);
-        if (HALF || (k >= oa.k_min && k < oa.k_max)) out[k - oa.k_min] = val[v];
+        if (band_inside<P, G, BAND>(k0) || (k >= oa.k_min && k < oa.k_max)) out[k - oa.k_min] = val[v];
       }
     } else {
       float* srow = (float*)oa.spectrum + (long)item * (long)(oa.k_max - oa.k_min);
       uint32_t mask = 0;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
+        const int k0 = G * (v / 2 / RO) + NSL * (v / 2 % RO);
+        if (!band_keeps<P, BAND>(k0)) continue;
         const int k = bin_of(v);
-        const bool inr = HALF || (k >= oa.k_min && k < oa.k_max);
+        const bool inr = band_inside<P, G, BAND>(k0) || (k >= oa.k_min && k < oa.k_max);
         if (MODE == 2 && inr) srow[k - oa.k_min] = (float)val[v];
         if (inr && val[v] > thr) mask |= 1u << v;
       }
@@ -1373,7 +1653,7 @@ __global__ void __launch_bounds__(256) k_tmpl_b_ib(TmplArgs ta, int ntmpl, const
   // the unit after the chunk, unit 0 at the template's end) and forms the bins of unit
   // u0 + j - 1.
   auto unit_of = [&](int u0, int j) { return j < ch ? u0 + j : (u0 + ch == units ? 0 : u0 + ch); };
-  int item = c >> lg_cpt, u0 = (c - (item << lg_cpt)) * ch, j = 0;
+  int item = c / cpt, u0 = (c - item * cpt) * ch, j = 0;
   cx<T> xa[PB1][R1], xb[PB1][R1];
   load_unit(xa, xb, item, u0);
   while (true) {
@@ -1389,8 +1669,8 @@ __global__ void __launch_bounds__(256) k_tmpl_b_ib(TmplArgs ta, int ntmpl, const
     int n_c = c, n_item = item, n_u0 = u0, n_j = j + 1;
     if (j == ch) {
       n_c = c + nw;
-      n_item = n_c >> lg_cpt;
-      n_u0 = (n_c - (n_item << lg_cpt)) * ch;
+      n_item = n_c / cpt;
+      n_u0 = (n_c - n_item * cpt) * ch;
       n_j = 0;
     }
     const bool more = n_c < nchunk;
