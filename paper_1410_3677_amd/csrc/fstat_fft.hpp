@@ -1,12 +1,9 @@
-// Device building blocks: complex arithmetic and an LDS-resident Stockham FFT
-// for gfx950 (64-wide wavefronts).
-//
-// A workgroup transforms NC independent columns of LEN points that sit in LDS
-// with a column stride STRIDE.  Each stage of radix R (8 while at least 8
-// points remain, then 4 or 2) loads R points per butterfly into registers,
-// applies the inter-stage twiddles, does an R-point DFT in registers, and
-// writes the outputs back in Stockham (self-sorting) order, so the result is
-// in natural order without a bit-reversal pass.
+// Device building blocks for gfx950: complex arithmetic, in-register DFTs of 2, 4 and 8
+// points, and twiddles from split tables.  The transforms themselves are Stockham
+// (self-sorting) stages of radix 8 while at least 8 points remain, then 4 or 2: each loads
+// R points per butterfly, applies the inter-stage twiddles, does an R-point DFT in
+// registers and writes the outputs in Stockham order, so that the result is in natural
+// order without a bit-reversal pass.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -16,6 +13,12 @@ namespace fstat {
 template <typename T>
 struct alignas(2 * sizeof(T)) cx {
   T re, im;
+};
+
+// The two amplitude series at one position.
+template <typename T>
+struct alignas(4 * sizeof(T)) cx_pair {
+  cx<T> a, b;
 };
 
 template <typename T>
@@ -88,70 +91,6 @@ __device__ __forceinline__ void dftr(cx<T>* v) {
   if constexpr (R == 8) dft8<T, INV>(v);
   else if constexpr (R == 4) dft4<T, INV>(v);
   else dft2<T, INV>(v);
-}
-
-// One Stockham stage over NC columns of LEN points (column stride STRIDE),
-// radix R, NS = product of the previous radices.  tw1024[m] = exp(-2 pi i m/1024).
-template <typename T, int LEN, int NC, int NT, int STRIDE, int R, int NS, bool INV>
-__device__ __forceinline__ void stockham_stage(cx<T>* lds, const cx<T>* __restrict__ tw1024) {
-  constexpr int NB = LEN / R;           // butterflies per column
-  constexpr int TOT = NC * NB;
-  constexpr int PER = (TOT + NT - 1) / NT;
-  constexpr int TWSTEP = 1024 / (NS * R);
-  const int tid = threadIdx.x;
-  cx<T> v[PER][R];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int b = tid + i * NT;
-    if ((TOT % NT == 0) || b < TOT) {
-      const int c = b / NB, j = b % NB;
-      const cx<T>* col = lds + c * STRIDE;
-      const int k = j % NS;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        cx<T> x = col[j + r * NB];
-        if (NS > 1 && r > 0) {
-          cx<T> w = tw1024[k * r * TWSTEP];
-          if (INV) w.im = -w.im;
-          x = cmul(x, w);
-        }
-        v[i][r] = x;
-      }
-      dftr<T, R, INV>(v[i]);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int b = tid + i * NT;
-    if ((TOT % NT == 0) || b < TOT) {
-      const int c = b / NB, j = b % NB;
-      cx<T>* col = lds + c * STRIDE;
-      const int k = j % NS;
-      const int base = (j / NS) * NS * R + k;
-#pragma unroll
-      for (int r = 0; r < R; ++r) col[base + r * NS] = v[i][r];
-    }
-  }
-  __syncthreads();
-}
-
-template <typename T, int LEN, int NC, int NT, int STRIDE, bool INV, int NS>
-__device__ __forceinline__ void lds_fft_from(cx<T>* lds, const cx<T>* __restrict__ tw1024) {
-  if constexpr (NS < LEN) {
-    constexpr int REM = LEN / NS;
-    constexpr int R = REM >= 8 ? 8 : REM;
-    stockham_stage<T, LEN, NC, NT, STRIDE, R, NS, INV>(lds, tw1024);
-    lds_fft_from<T, LEN, NC, NT, STRIDE, INV, NS * R>(lds, tw1024);
-  }
-}
-
-// In-place DFT (unnormalised; forward sign -i, INV sign +i) of NC LDS columns.
-// Callers must __syncthreads() after filling LDS; the routine ends with a barrier.
-template <typename T, int LEN, int NC, int NT, int STRIDE, bool INV>
-__device__ __forceinline__ void lds_fft(cx<T>* lds, const cx<T>* __restrict__ tw1024) {
-  static_assert(LEN >= 2 && LEN <= 1024 && (LEN & (LEN - 1)) == 0, "LEN must be a power of two <= 1024");
-  lds_fft_from<T, LEN, NC, NT, STRIDE, INV, 1>(lds, tw1024);
 }
 
 // exp(-+ 2 pi i m / L) for 0 <= m < L from a split table: lo[m % 1024] * hi[m / 1024],

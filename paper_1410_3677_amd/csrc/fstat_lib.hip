@@ -18,6 +18,8 @@
 #include "fstat_launch.hpp"
 #include "fstat_drain.hpp"
 #include "fstat_tmpl.hpp"
+#include "fstat_sky.hpp"
+#include "fstat_sky_fullrate.hpp"
 #include "fstat_vet.hpp"
 
 using namespace fstat;
@@ -26,7 +28,7 @@ namespace {
 
 thread_local std::string g_last_error;
 
-constexpr int LOG_MIN = 10, LOG_MAX = 20;  // supported FFT lengths 2^10 .. 2^20
+constexpr int LOG_MAX = 20;  // the longest FFT is 2^20 points
 
 struct SegInfo {
   fstat_segment s;
@@ -89,13 +91,12 @@ struct GraphEntry {
 
 struct Tables {
   void* dev = nullptr;         // one allocation for both precisions
-  size_t off_tw1024[2] = {0, 0};
   size_t off_lo[2][LOG_MAX + 1] = {};
   size_t off_hi[2][LOG_MAX + 1] = {};
-  size_t off_g[2] = {0, 0};
   size_t off_stage[2] = {0, 0};
   // decimated transforms (single precision): twiddles of 5 2^(e-3) points, stage twiddles,
   // filter taps (double)
+  size_t off_tw1024 = 0, off_g = 0;   // full-rate calls' per-sky stage (single precision)
   size_t off_dlo[LOG_MAX + 1] = {}, off_dhi[LOG_MAX + 1] = {}, off_dstage = 0, off_taps = 0;
   size_t bytes = 0;
 };
@@ -133,10 +134,9 @@ struct fstat_plan_s {
   bool ws_owned = false;
   // per-sky parameters and resampled series twice (the sky batch being prepared and the
   // one being searched), per-sky scratch, template intermediate
-  size_t off_sp[2] = {0, 0}, off_part = 0, off_zt[2] = {0, 0}, off_sky = 0, off_tmpl = 0;
+  size_t off_sp[2] = {0, 0}, off_zt[2] = {0, 0}, off_sky = 0, off_tmpl = 0;
   size_t off_zd[2] = {0, 0}, off_route = 0;   // decimated series, path flag of the running call
   size_t off_xs = 0;   // FP64 with interbinning: the second pass's transforms [B][tL][2]
-  int nblk_max = 0;
   long n_max = 0, L_max = 0, M_max = 0;
   long TL_max = 0;             // longest template FFT
   long dn_max = 0;             // longest decimated series (0: no segment has one)
@@ -314,13 +314,6 @@ static void with_len(int len, F&& f) {
   }
 }
 
-template <typename T>
-static int tw_of(int len) {
-  int tw = 0;
-  with_len(len, [&](auto c) { tw = tile_width<T, decltype(c)::value>(); });
-  return tw;
-}
-
 // Interbinning whose second pass is the tiled kernel plus a separate 2F pass: FP64, and
 // mixed precision for template transforms with P > 512 rows' length (nfft = 2^20).
 static bool tiled_interbinning(fstat_plan_t p) {
@@ -340,13 +333,12 @@ static size_t layout(fstat_plan_t p, int Sb, int B, bool commit) {
     o_sp[k] = off;
     off = align256(off + (size_t)Sb * sizeof(SkyParams));
   }
-  const size_t o_part = off;
-  off = align256(off + (size_t)Sb * p->nblk_max * 3 * sizeof(double));
   for (int k = 0; k < 2; ++k) {
     o_zt[k] = off;
     off = align256(off + (size_t)Sb * 2 * p->n_max * cx);
   }
-  // per-sky scratch: za [2][M], Z [2][M], tmp [2][L], u [2][L] per sky
+  // per-sky scratch: the demodulated series and three more arrays of [M] pairs (full-rate
+  // calls use them all)
   const size_t o_sky = off;
   off = align256(off + (size_t)Sb * (4 * p->M_max + 4 * p->L_max) * cx);
   // template intermediate [B][tL][2]
@@ -373,7 +365,6 @@ static size_t layout(fstat_plan_t p, int Sb, int B, bool commit) {
       p->off_zd[k] = o_zd[k];
     }
     p->off_route = o_route;
-    p->off_part = o_part;
     p->off_sky = o_sky;
     p->off_tmpl = o_tmpl;
     p->off_xs = o_xs;
@@ -382,7 +373,7 @@ static size_t layout(fstat_plan_t p, int Sb, int B, bool commit) {
 }
 
 template <typename T>
-static void fill_tables(std::vector<unsigned char>& buf, Tables& tb, int which, int kt) {
+static void fill_tables(std::vector<unsigned char>& buf, Tables& tb, int which, const std::vector<int>& logs) {
   auto put = [&](size_t count) {
     size_t off = align256(buf.size());
     buf.resize(off + count * sizeof(cx<T>));
@@ -396,10 +387,8 @@ static void fill_tables(std::vector<unsigned char>& buf, Tables& tb, int which, 
     w.im = (T)(-std::sin(a));
     return w;
   };
-  size_t o = put(1024);
-  tb.off_tw1024[which] = o;
-  for (int m = 0; m < 1024; ++m) reinterpret_cast<cx<T>*>(buf.data() + o)[m] = wexp(m, 1024);
-  for (int e = LOG_MIN; e <= LOG_MAX; ++e) {
+  for (int e : logs) {
+    if (tb.off_hi[which][e]) continue;
     const long L = 1L << e;
     size_t lo = put(1024);
     tb.off_lo[which][e] = lo;
@@ -418,12 +407,26 @@ static void fill_tables(std::vector<unsigned char>& buf, Tables& tb, int which, 
         for (int r = 1; r < rr; ++r)
           reinterpret_cast<cx<T>*>(buf.data() + os)[stage_tw_offset(ns, rr) + k * (rr - 1) + (r - 1)] =
               wexp((long)k * r, (long)ns * rr);
-  size_t og = align256(buf.size());
-  buf.resize(og + (kt + 1) * sizeof(T));
-  tb.off_g[which] = og;
+}
+
+// Tables of the full-rate calls' per-sky stage: twiddles of 1024 points, the Green's
+// function's taps.
+constexpr int KT_FULL = 16;
+static void fill_full_tables(std::vector<unsigned char>& buf, Tables& tb) {
+  tb.off_tw1024 = align256(buf.size());
+  buf.resize(tb.off_tw1024 + 1024 * sizeof(cx<float>));
+  for (int m = 0; m < 1024; ++m) {
+    const double a = 2.0 * M_PI * (double)m / 1024.0;
+    cx<float> w;
+    w.re = (float)std::cos(a);
+    w.im = (float)(-std::sin(a));
+    reinterpret_cast<cx<float>*>(buf.data() + tb.off_tw1024)[m] = w;
+  }
+  tb.off_g = align256(buf.size());
+  buf.resize(tb.off_g + (KT_FULL + 1) * sizeof(float));
   const double z = std::sqrt(3.0) - 2.0;
-  for (int k = 0; k <= kt; ++k)
-    reinterpret_cast<T*>(buf.data() + og)[k] = (T)(std::pow(z, k) / (2.0 * std::sqrt(3.0)));
+  for (int k = 0; k <= KT_FULL; ++k)
+    reinterpret_cast<float*>(buf.data() + tb.off_g)[k] = (float)(std::pow(z, k) / (2.0 * std::sqrt(3.0)));
 }
 
 // Tables of the decimated transforms for the transform lengths (log2) of `logs`.
@@ -483,8 +486,6 @@ static void fill_dec_tables(std::vector<unsigned char>& buf, Tables& tb, const s
     }
 }
 
-constexpr int KT_F32 = 16, KT_F64 = 32;
-
 static SegConst seg_const(const SegInfo& si) {
   SegConst sc;
   sc.n = (int)si.s.n;
@@ -492,9 +493,23 @@ static SegConst seg_const(const SegInfo& si) {
   sc.dt = si.s.dt;
   sc.f_off = si.s.f_off;
   sc.sigma2 = si.s.sigma2;
-  sc.lat = si.s.lat;
-  sc.gamma = si.s.gamma;
   sc.phi_r = si.s.phi_r;
+  sc.s2g = std::sin(2.0 * si.s.gamma);
+  sc.c2g = std::cos(2.0 * si.s.gamma);
+  sc.sl = std::sin(si.s.lat);
+  sc.cl = std::cos(si.s.lat);
+  sc.s2l = std::sin(2.0 * si.s.lat);
+  sc.c2l = std::cos(2.0 * si.s.lat);
+  // mean of exp(-i m rate dt j) over j < n: exp(-i m mid) sin(n h) / (n sin h), h = m rate dt / 2,
+  // taken to within pi/2 of zero so that intervals of whole half-turns stay exact
+  const double step = sidereal_rate() * sc.dt, n = (double)sc.n;
+  sc.mid = 0.5 * (n - 1.0) * step;
+  for (int m = 1; m <= 4; ++m) {
+    const double h = 0.5 * m * step, turns = std::nearbyint(h / M_PI), r = std::remainder(h, M_PI);
+    const double ratio = std::sin(r) == 0.0 ? 1.0 : std::sin(n * r) / (n * std::sin(r));
+    // each half-turn of h flips sin(n h) / sin(h) when n is even
+    sc.dir[m - 1] = sc.n % 2 == 0 && std::fmod(turns, 2.0) != 0.0 ? -ratio : ratio;
+  }
   sc.x = si.s.x;
   sc.r = si.s.r_ssb;
   return sc;
@@ -566,9 +581,7 @@ struct ProfScope {
 template <typename T>
 struct Dev {
   fstat_plan_t p;
-  const cx<T>* tw1024;
   const cx<T>* twst;
-  const T* g;
   const cx<T>* lo(int e) const {
     return (const cx<T>*)((const char*)p->tab.dev + p->tab.off_lo[sizeof(T) == 8][e]);
   }
@@ -577,81 +590,117 @@ struct Dev {
   }
   explicit Dev(fstat_plan_t p_) : p(p_) {
     const int w = sizeof(T) == 8;
-    tw1024 = (const cx<T>*)((const char*)p->tab.dev + p->tab.off_tw1024[w]);
-    g = (const T*)((const char*)p->tab.dev + p->tab.off_g[w]);
     twst = (const cx<T>*)((const char*)p->tab.dev + p->tab.off_stage[w]);
   }
   const cx<T>* dec_lo(int e) const { return (const cx<T>*)((const char*)p->tab.dev + p->tab.off_dlo[e]); }
   const cx<T>* dec_hi(int e) const { return (const cx<T>*)((const char*)p->tab.dev + p->tab.off_dhi[e]); }
   const cx<T>* dec_stage() const { return (const cx<T>*)((const char*)p->tab.dev + p->tab.off_dstage); }
+  const cx<T>* tw1024() const { return (const cx<T>*)((const char*)p->tab.dev + p->tab.off_tw1024); }
+  const T* spline_taps() const { return (const T*)((const char*)p->tab.dev + p->tab.off_g); }
   const double* taps() const { return (const double*)((const char*)p->tab.dev + p->tab.off_taps); }
   int buf = 0;   // which of the two per-sky buffers
   SkyParams* sp() const { return (SkyParams*)((char*)p->ws + p->off_sp[buf]); }
-  double* part() const { return (double*)((char*)p->ws + p->off_part); }
-  cx<T>* zt() const { return (cx<T>*)((char*)p->ws + p->off_zt[buf]); }
-  cx<T>* sky() const { return (cx<T>*)((char*)p->ws + p->off_sky); }
+  cx_pair<T>* zt() const { return (cx_pair<T>*)((char*)p->ws + p->off_zt[buf]); }
+  cx_pair<T>* sky() const { return (cx_pair<T>*)((char*)p->ws + p->off_sky); }
   cx<T>* tmpl() const { return (cx<T>*)((char*)p->ws + p->off_tmpl); }
   cx<T>* zd() const { return (cx<T>*)((char*)p->ws + p->off_zd[buf]); }
   int* route() const { return (int*)((char*)p->ws + p->off_route); }
   cx<T>* xs() const { return (cx<T>*)((char*)p->ws + p->off_xs); }
 };
 
-// forward or inverse L-point FFT of `items` pairs of series, two passes
-template <typename T, bool INV, int SRC>
-static hipError_t fft_two_pass(const Dev<T>& d, int logL, int P, int Q, const cx<T>* in, long ld_in,
-                               int nvalid, cx<T>* tmp, cx<T>* out, long ld_out, int items, T scale,
-                               hipStream_t st, const cx<T>* shlo = nullptr, const cx<T>* shhi = nullptr) {
+// Two passes of a transform of nb pairs of series in full-rate mixed-precision calls.
+template <bool INV, int SRC>
+static hipError_t fft_two_pass_full(const Dev<float>& d, int logL, int P, int Q, const cx<float>* in, long ld_in,
+                                    int nvalid, cx<float>* tmp, cx<float>* out, long ld_out, int items, float scale,
+                                    hipStream_t st, const cx<float>* shlo = nullptr, const cx<float>* shhi = nullptr) {
   const int L = 1 << logL;
   hipError_t err = hipSuccess;
   with_len(Q, [&](auto c) {
     constexpr int QQ = decltype(c)::value;
-    const int ntiles = P / tile_width<T, QQ>();
-    FSTAT_LAUNCH((k_fft_pass_a<T, QQ, INV, SRC>), dim3(ntiles * items), dim3(NT), 0, st, in, ld_in,
-                       nvalid, tmp, P, L, d.tw1024, d.lo(logL), d.hi(logL), shlo, shhi);
+    FSTAT_LAUNCH((full::k_fft_pass_a<float, QQ, INV, SRC>), dim3(P / full::tile_width<float, QQ>() * items), dim3(NT), 0,
+                 st, in, ld_in, nvalid, tmp, P, L, d.tw1024(), d.lo(logL), d.hi(logL), shlo, shhi);
     err = launch_status();
   });
   if (err != hipSuccess) return err;
   with_len(P, [&](auto c) {
     constexpr int PP = decltype(c)::value;
-    const int ntiles = Q / tile_width<T, PP>();
-    FSTAT_LAUNCH((k_fft_pass_b<T, PP, INV>), dim3(ntiles * items), dim3(NT), 0, st, tmp, out, ld_out, Q,
-                       L, scale, d.tw1024);
+    FSTAT_LAUNCH((full::k_fft_pass_b<float, PP, INV>), dim3(Q / full::tile_width<float, PP>() * items), dim3(NT), 0, st,
+                 tmp, out, ld_out, Q, L, scale, d.tw1024());
     err = launch_status();
   });
   return err;
 }
 
-// Per-sky stage for skies [sky0, sky0 + nb) of segment si; leaves zt and SkyParams.
+// Per-sky stage for skies [sky0, sky0 + nb) of segment si; leaves zt and SkyParams, and the
+// demodulated and odd series of its batch at the start of d.sky() ([nb][M] pairs each).
+// keep_all: every odd sample, not only those the spline reads.  full_rate: the templates of
+// this mixed-precision call are not decimated (fstat_sky_fullrate.hpp).
 template <typename T>
 static fstat_status run_sky_batch(fstat_plan_t p, const Dev<T>& d, const SegInfo& si, const double* alpha,
-                                  const double* delta, int sky0, int nb, bool dec, hipStream_t st) {
+                                  const double* delta, int sky0, int nb, bool dec, bool full_rate, hipStream_t st,
+                                  bool keep_all = false) {
   const SegConst sc = seg_const(si);
-  const int n = sc.n, L = si.nfft, M = si.M;
-  const int nblk = (n + NT - 1) / NT;
-  cx<T>* za = d.sky();                             // [nb][2][M]
-  cx<T>* Z = za + (size_t)nb * 2 * M;              // [nb][2][M]
-  cx<T>* tmp = Z + (size_t)nb * 2 * M;             // [nb][2][L] (M used)
-  cx<T>* o = tmp + (size_t)nb * 2 * L;             // [nb][2][M]: odd samples of the 2x upsampling
+  const int n = sc.n, M = si.M, P = si.PM, Q = si.QM, logM = si.logL - 1;
+  cx_pair<T>* z = d.sky();                    // [nb][M]: the demodulated series
+  cx_pair<T>* o = z + (size_t)nb * M;         // [nb][M]: odd samples of the 2x upsampling
+  cx_pair<T>* t = o + (size_t)nb * M;         // [nb][Q][P]: between the passes
   {
     ProfScope ps(p, FSTAT_KERNEL_SKY_PREP, st);
-    FSTAT_LAUNCH(k_sky_setup, dim3((nb + 63) / 64), dim3(64), 0, st, alpha, delta, sky0, nb, sc, d.sp());
-    FSTAT_LAUNCH((k_sky_demod<T>), dim3(nblk, nb), dim3(NT), 0, st, sc, d.sp(), za, (long)M, d.part());
-    FSTAT_LAUNCH(k_sky_finalize, dim3(nb), dim3(NT), 0, st, sc, d.sp(), d.part(), nblk,
-                       p->opt.form == FSTAT_FORM_FULL ? 1 : 0);
+    FSTAT_LAUNCH(k_sky_setup, dim3((nb + 63) / 64), dim3(64), 0, st, alpha, delta, sky0, nb, sc,
+                 p->opt.form == FSTAT_FORM_FULL ? 1 : 0, d.sp());
+    FSTAT_LAUNCH((k_sky_demod<T>), dim3((n + NT - 1) / NT, (nb + DEMOD_SKIES - 1) / DEMOD_SKIES), dim3(NT), 0, st, sc,
+                 d.sp(), nb, z, (long)M);
     HIP_TRY(p, launch_status(), "sky stage launch");
   }
   {
     ProfScope ps(p, FSTAT_KERNEL_RESAMPLE, st);
-    HIP_TRY(p, (fft_two_pass<T, false, SRC_PLAIN>(d, si.logL - 1, si.PM, si.QM, za, M, n, tmp, Z, M, nb, (T)1, st)),
-            "upsampling forward FFT");
-    // 2x band-limited upsampling: the even samples are za itself, the odd ones the inverse
-    // M-point transform of the spectrum shifted by half a sample
-    HIP_TRY(p, (fft_two_pass<T, true, SRC_HALFSHIFT>(d, si.logL - 1, si.PM, si.QM, Z, M, 0, tmp, o, M, nb,
-                                                      (T)(1.0 / M), st, d.lo(si.logL), d.hi(si.logL))),
-            "upsampling inverse FFT");
-    constexpr int KT = sizeof(T) == 8 ? KT_F64 : KT_F32;
-    FSTAT_LAUNCH((k_spline<T, KT>), dim3(nblk, nb), dim3(NT), 0, st, sc, d.sp(), za, o, (long)M, d.zt(),
-                       (long)n, d.g);
+    if constexpr (sizeof(T) == 4) {
+      if (full_rate) {
+        cx<T>* planes = (cx<T>*)(z + (size_t)nb * M);
+        cx<T>* Z = planes;                           // [nb][2][M]
+        cx<T>* tmp = Z + (size_t)nb * 2 * M;         // [nb][2][M]
+        cx<T>* oo = tmp + (size_t)nb * 2 * M;        // [nb][2][M]
+        HIP_TRY(p, (fft_two_pass_full<false, full::SRC_PLAIN>(d, logM, P, Q, (const cx<T>*)z, M, n, tmp, Z, M, nb, (T)1,
+                                                              st)), "upsampling forward FFT");
+        HIP_TRY(p, (fft_two_pass_full<true, full::SRC_HALFSHIFT>(d, logM, P, Q, Z, M, 0, tmp, oo, M, nb, (T)(1.0 / M),
+                                                                 st, d.lo(si.logL), d.hi(si.logL))),
+                "upsampling inverse FFT");
+        FSTAT_LAUNCH((full::k_spline<T, KT_FULL>), dim3((n + NT - 1) / NT, nb), dim3(NT), 0, st, sc, d.sp(),
+                     (const cx<T>*)z, oo, (long)M, d.zt(), (long)n, d.spline_taps());
+        HIP_TRY(p, launch_status(), "spline launch");
+        return FSTAT_OK;
+      }
+    }
+    hipError_t err = hipErrorInvalidValue;
+    auto cols = [&](auto inv, const cx_pair<T>* in, int nvalid, cx_pair<T>* out, int nkeep, T scale) {
+      with_len(Q, [&](auto c) {
+        constexpr int QQ = decltype(c)::value;
+        if constexpr (QQ <= 512) {
+          FSTAT_LAUNCH((k_sky_cols<T, QQ, decltype(inv)::value>), dim3((unsigned)(P / sky_tw<T, QQ>() * nb)),
+                       dim3(sky_nt<T, QQ>()), 0, st, in, (long)M, nvalid, out, (long)M, nkeep, P, scale, d.twst,
+                       d.lo(logM), d.hi(logM));
+          err = launch_status();
+        }
+      });
+    };
+    cols(std::false_type{}, z, n, t, M, (T)1);
+    HIP_TRY(p, err, "upsampling first pass");
+    err = hipErrorInvalidValue;
+    with_len(P, [&](auto c) {
+      constexpr int PP = decltype(c)::value;
+      if constexpr (PP >= 64) {
+        const int nwg = nb * Q / (NT / groups_per_col<PP>());
+        FSTAT_LAUNCH((k_sky_rows<T, PP>), dim3((unsigned)nwg), dim3(NT), 0, st, t, Q, d.twst, d.lo(logM), d.hi(logM),
+                     d.lo(si.logL), d.hi(si.logL));
+        err = launch_status();
+      }
+    });
+    HIP_TRY(p, err, "upsampling second pass");
+    err = hipErrorInvalidValue;
+    cols(std::true_type{}, t, M, o, keep_all ? M : spline_keep<T>(n, M), (T)(1.0 / M));
+    HIP_TRY(p, err, "upsampling third pass");
+    FSTAT_LAUNCH((k_spline<T>), dim3((unsigned)((n + spl_out<T>() - 1) / spl_out<T>()), nb), dim3(SPL_NT), 0, st, sc,
+                 d.sp(), z, (long)M, o, (long)M, d.zt(), (long)n);
     HIP_TRY(p, launch_status(), "spline launch");
     if constexpr (sizeof(T) == 4) {
       if (dec) {
@@ -752,13 +801,14 @@ static hipError_t launch_stream_b(const Dev<float>& d, const SegInfo& si, const 
 }
 
 // Whether a call's templates of segment si run as decimated transforms.  They save 3/8 of
-// a template's memory traffic and arithmetic and cost, per call, the filter (0.6 us a sky
-// position) and the launches of the path not taken; small calls, where those weigh more
-// than the templates, keep the full-rate transforms.  The patch capture stores the rows of
-// the full-rate second pass.
+// a template's memory traffic and arithmetic (0.93 against 1.47 us at 2^18 points) and cost
+// the filter, once a sky position (2.2 us), and the launches of the path not taken (10 us a
+// launch pair); where those weigh more, with few spindowns or in small calls, the full-rate
+// transforms stay.  The patch capture stores the rows of the full-rate second pass.
 constexpr long DEC_MIN_POINTS = 1L << 24;   // templates times transform points
+constexpr int DEC_MIN_FDOT = 5;             // spindowns per sky position
 static bool use_dec(fstat_plan_t p, const SegInfo& si, const Grid& g, int mode) {
-  return si.dec && p->dn_max && p->variant_b == 1 && !(mode == 0 && p->vet) && g.nfdot >= 2 &&
+  return si.dec && p->dn_max && p->variant_b == 1 && !(mode == 0 && p->vet) && g.nfdot >= DEC_MIN_FDOT &&
          (long)g.nsky * g.nfdot * si.tL >= DEC_MIN_POINTS;
 }
 
@@ -980,7 +1030,7 @@ static fstat_status search_impl(fstat_plan_t p, int segment, const Grid& g, int 
       db.buf = b & 1;
       if (b >= 2 && sst != st) HIP_TRY(p, hipStreamWaitEvent(sst, p->ev_tmpl[b & 1], 0), "sky stream order");
       const int sky0 = b * p->Sb;
-      fstat_status r = run_sky_batch<T>(p, db, si, g.alpha, g.delta, sky0, std::min(p->Sb, nsky - sky0), dec, sst);
+      fstat_status r = run_sky_batch<T>(p, db, si, g.alpha, g.delta, sky0, std::min(p->Sb, nsky - sky0), dec, !dec, sst);
       if (r != FSTAT_OK) return r;
       if (sst != st) HIP_TRY(p, hipEventRecord(p->ev_sky[b & 1], sst), "sky stream order");
       return FSTAT_OK;
@@ -1620,7 +1670,6 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
     p->M_max = std::max(p->M_max, (long)si.M);
     if (si.dec) p->dn_max = std::max(p->dn_max, si.dn);
   }
-  p->nblk_max = (int)((p->n_max + NT - 1) / NT);
 
   // batch sizes: requested or defaults, shrunk to the budget (admission).  Mixed precision:
   // 16 sky positions (8 leave the per-sky kernels too few workgroups: 24 against 14 us a
@@ -1681,13 +1730,21 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
     if (es != hipSuccess) p->static_err = std::string("static scratch address: ") + hipGetErrorString(es);
   }
   std::vector<unsigned char> tb;
-  fill_tables<float>(tb, p->tab, 0, KT_F32);
-  fill_tables<double>(tb, p->tab, 1, KT_F64);
   {
-    std::vector<int> logs;
-    for (auto& si : p->segs)
-      if (si.dec) logs.push_back(si.tlog);
-    if (!logs.empty()) fill_dec_tables(tb, p->tab, logs);
+    // of the plan's precision and lengths only: the interpolated transform, the upsampling's
+    // and the templates'
+    std::vector<int> logs, dec;
+    for (auto& si : p->segs) {
+      logs.insert(logs.end(), {si.logL, si.logL - 1, si.tlog});
+      if (si.dec) dec.push_back(si.tlog);
+    }
+    if (p->fp64) {
+      fill_tables<double>(tb, p->tab, 1, logs);
+    } else {
+      fill_tables<float>(tb, p->tab, 0, logs);
+      fill_full_tables(tb, p->tab);
+      if (!dec.empty()) fill_dec_tables(tb, p->tab, dec);
+    }
   }
   p->tab.bytes = tb.size();
   if ((e = hipMalloc(&p->tab.dev, tb.size())) != hipSuccess ||
@@ -1991,25 +2048,16 @@ template <typename T>
 static fstat_status sky_stages_impl(fstat_plan_t plan, const SegInfo& si, const double* ad, double* abc, void* za,
                                     void* zb, void* ua, void* ub, void* zta, void* ztb, hipStream_t st) {
   Dev<T> d(plan);
-  fstat_status r = run_sky_batch<T>(plan, d, si, ad, ad + 1, 0, 1, false, st);
+  fstat_status r = run_sky_batch<T>(plan, d, si, ad, ad + 1, 0, 1, false, false, st, true);
   if (r != FSTAT_OK) return r;
-  const size_t n = si.s.n, M = si.M, L = si.nfft, cb = sizeof(cx<T>);
-  cx<T>* zab = d.sky();
-  cx<T>* o = zab + 4 * M + 2 * L;
-  auto cp = [&](void* dst, const void* src, size_t bytes) {
-    return dst ? hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, st) : hipSuccess;
-  };
-  HIP_TRY(plan, cp(za, zab, n * cb), "stage copy");
-  HIP_TRY(plan, cp(zb, zab + M, n * cb), "stage copy");
-  // the 2x upsampled series, assembled from the series and its half-sample shift
-  cx<T>* u = zab + 2 * M;   // the spectrum's space, no longer needed
-  FSTAT_LAUNCH((k_upsampled<T>), dim3((unsigned)((L + NT - 1) / NT), 2), dim3(NT), 0, st, zab, o, (long)M,
-                     (int)n, (int)L, u);
-  HIP_TRY(plan, launch_status(), "upsampled series launch");
-  HIP_TRY(plan, cp(ua, u, L * cb), "stage copy");
-  HIP_TRY(plan, cp(ub, u + L, L * cb), "stage copy");
-  HIP_TRY(plan, cp(zta, d.zt(), n * cb), "stage copy");
-  HIP_TRY(plan, cp(ztb, d.zt() + n, n * cb), "stage copy");
+  const int n = (int)si.s.n, L = si.nfft;
+  const cx_pair<T>* z = d.sky();
+  const cx_pair<T>* o = z + si.M;
+  const dim3 gn((unsigned)((n + NT - 1) / NT)), gl((unsigned)((L + NT - 1) / NT));
+  FSTAT_LAUNCH((k_unpair<T>), gn, dim3(NT), 0, st, z, n, (cx<T>*)za, (cx<T>*)zb);
+  FSTAT_LAUNCH((k_upsampled<T>), gl, dim3(NT), 0, st, z, o, n, L, (cx<T>*)ua, (cx<T>*)ub);
+  FSTAT_LAUNCH((k_unpair<T>), gn, dim3(NT), 0, st, (const cx_pair<T>*)d.zt(), n, (cx<T>*)zta, (cx<T>*)ztb);
+  HIP_TRY(plan, launch_status(), "stage copy");
   if (abc) {
     SkyParams* sp = d.sp();
     HIP_TRY(plan, hipMemcpyAsync(abc, &sp->A, 3 * sizeof(double), hipMemcpyDeviceToDevice, st), "stage copy");

@@ -307,8 +307,7 @@ __device__ __forceinline__ void dft8_pruned(cx<T>* v) {
 // length), so they are neither loaded nor transformed.
 template <typename T, int Q, int G, int R1, int NB1, int PB1, int RNZ = R1>
 __device__ __forceinline__ void chirped_first_stage(cx<T> (&va)[PB1][R1], cx<T> (&vb)[PB1][R1],
-                                                    const cx<T>* __restrict__ za, const cx<T>* __restrict__ zb,
-                                                    int j1, int g, int P, int n, double c2, double c1) {
+                                                    const cx_pair<T>* __restrict__ z, int j1, int g, int P, int n, double c2, double c1) {
 #pragma unroll
   for (int b = 0; b < PB1; ++b) {
     const unsigned j = (unsigned)(g + G * b);
@@ -318,8 +317,9 @@ __device__ __forceinline__ void chirped_first_stage(cx<T> (&va)[PB1][R1], cx<T> 
       va[b][r] = mk<T>(0, 0);
       vb[b][r] = mk<T>(0, 0);
       if (jj < (unsigned)n) {
-        va[b][r] = at32(za, jj);
-        vb[b][r] = at32(zb, jj);
+        const cx_pair<T> v = z[jj];
+        va[b][r] = v.a;
+        vb[b][r] = v.b;
       }
     }
 #pragma unroll
@@ -359,7 +359,7 @@ __device__ __forceinline__ void chirped_first_stage(cx<T> (&va)[PB1][R1], cx<T> 
 // The two series share the chirp; they pass through one LDS tile one after the
 // other, the second series' first-stage outputs waiting in registers.
 template <typename T, int Q, int RNZ = stage_radix<Q, 1>()>
-__global__ void __launch_bounds__((tmpl_nt_a<T, Q>())) k_tmpl_a(TmplArgs ta, const cx<T>* __restrict__ zt,
+__global__ void __launch_bounds__((tmpl_nt_a<T, Q>())) k_tmpl_a(TmplArgs ta, const cx_pair<T>* __restrict__ zt,
                                                            cx<T>* __restrict__ tbuf,
                                                            const cx<T>* __restrict__ twst,
                                                            const cx<T>* __restrict__ twlo,
@@ -382,13 +382,12 @@ __global__ void __launch_bounds__((tmpl_nt_a<T, Q>())) k_tmpl_a(TmplArgs ta, con
     const int skyl = t / ta.nfdot, sidx = t % ta.nfdot;
     double c2, c1;
     template_chirp(ta, skyl, sidx, c2, c1);
-    const cx<T>* za = zt + (long)(2 * skyl) * ta.ldzt;
-    const cx<T>* zb = za + ta.ldzt;
+    const cx_pair<T>* z = zt + (long)skyl * ta.ldzt;
     const int j1 = tile * TW + c;
     cx<T>* col = lds + c * ST;
     // first stage: y[j1 + P j2] with the spindown chirp, radix-R1 butterflies in registers
     cx<T> va[PB1][R1], vb[PB1][R1];
-    chirped_first_stage<T, Q, G, R1, NB1, PB1, RNZ>(va, vb, za, zb, j1, g, ta.P, ta.n, c2, c1);
+    chirped_first_stage<T, Q, G, R1, NB1, PB1, RNZ>(va, vb, z, j1, g, ta.P, ta.n, c2, c1);
     // twiddles W^(j1 k2) of the last-stage outputs k2 = j + NSL r: W^(j1 j) times powers of W^(j1 NSL)
     constexpr int NSL = last_ns<Q, 1>();
     constexpr int RL = stage_radix<Q, NSL>();
@@ -435,7 +434,7 @@ __global__ void __launch_bounds__((tmpl_nt_a<T, Q>())) k_tmpl_a(TmplArgs ta, con
 // barriers).  The same operations as k_tmpl_a (the compiler may contract
 // multiply-adds differently, so results can differ in the last bit).
 template <typename T, int Q, int RNZ = stage_radix<Q, 1>()>
-__global__ void __launch_bounds__((tmpl_nt_a<T, Q>())) k_tmpl_a_pair(TmplArgs ta, const cx<T>* __restrict__ zt,
+__global__ void __launch_bounds__((tmpl_nt_a<T, Q>())) k_tmpl_a_pair(TmplArgs ta, const cx_pair<T>* __restrict__ zt,
                                                                 cx<T>* __restrict__ tbuf,
                                                                 const cx<T>* __restrict__ twst,
                                                                 const cx<T>* __restrict__ twlo,
@@ -458,14 +457,13 @@ __global__ void __launch_bounds__((tmpl_nt_a<T, Q>())) k_tmpl_a_pair(TmplArgs ta
     const int skyl = t / ta.nfdot, sidx = t % ta.nfdot;
     double c2, c1;
     template_chirp(ta, skyl, sidx, c2, c1);
-    const cx<T>* za = zt + (long)(2 * skyl) * ta.ldzt;
-    const cx<T>* zb = za + ta.ldzt;
+    const cx_pair<T>* z = zt + (long)skyl * ta.ldzt;
     const int j1 = tile * TW + c;
     cx<T>* cola = lds + c * ST;
     cx<T>* colb = lds + (TW + c) * ST;
     {
       cx<T> va[PB1][R1], vb[PB1][R1];
-      chirped_first_stage<T, Q, G, R1, NB1, PB1, RNZ>(va, vb, za, zb, j1, g, ta.P, ta.n, c2, c1);
+      chirped_first_stage<T, Q, G, R1, NB1, PB1, RNZ>(va, vb, z, j1, g, ta.P, ta.n, c2, c1);
       stage_to_lds_off<T, Q, G, 1, R1, PB1>(va, cola, g);
       stage_to_lds_off<T, Q, G, 1, R1, PB1>(vb, colb, g);
       __syncthreads();
@@ -511,8 +509,6 @@ template <int LEN>
 __host__ __device__ constexpr int dec_tw() { return 2560 / LEN; }
 template <int LEN, int NS>
 __host__ __device__ constexpr int dec_radix() { return NS == 1 ? 5 : (LEN / NS >= 8 ? 8 : LEN / NS); }
-template <typename T>
-struct alignas(4 * sizeof(T)) cx_pair { cx<T> a, b; };
 // Stage twiddles exp(-2 pi i k r / (NS R)), [k][r - 1], NS in {5, 40, 320} and R in {2, 4, 8}.
 __host__ __device__ constexpr int dec_tw_offset(int NS, int R) {
   int off = 0;
@@ -656,7 +652,7 @@ __global__ void __launch_bounds__(DEC_A_NT) k_tmpl_a_dec(TmplArgs ta, const cx<T
         for (int r = 0; r < RNZ; ++r) {
           const double x = (double)(m0 + NB * r * ta.P);
           double cyc = fma(c2, x, c1) * x;
-          cyc = __builtin_amdgcn_fract(cyc);
+          cyc -= rint(cyc);   // to half a cycle either side: half of [0, 1)'s rounding below
           T s, co;
           if constexpr (sizeof(T) == 8) {
             sincospi(2.0 * cyc, &s, &co);
