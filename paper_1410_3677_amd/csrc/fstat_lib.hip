@@ -769,6 +769,15 @@ template <int PP, int BAND>
 static hipError_t launch_stream_b(const Dev<float>& d, const SegInfo& si, const TmplArgs& ta, int nt, int mode,
                                   const OutArgs& oa, const cx<float>* tbuf, hipStream_t st) {
   const long n_cu = d.p->n_cu;
+  // a spectrum's rows are taken four in turn from 4096 resident wavefronts' worth of points
+  // on (512 points each); below, fewer wavefronts would be left than the chip holds (one
+  // template of 2^14 points: 108 against 103 us for the whole call)
+  auto walk = [&](auto mode_c, auto launch) {
+    if (decltype(mode_c)::value == 1 && (long)nt * ta.Q * PP >= 4096L * 512 * SPEC_ROWS)
+      launch(std::integral_constant<int, decltype(mode_c)::value == 1 ? SPEC_ROWS : 1>{});
+    else
+      launch(std::integral_constant<int, 1>{});
+  };
   auto go = [&](auto mode_c) {
     constexpr int MD = decltype(mode_c)::value;
     if constexpr (PP <= 512) {
@@ -782,16 +791,21 @@ static hipError_t launch_stream_b(const Dev<float>& d, const SegInfo& si, const 
                      d.twst);
         return;
       }
-      const long waves = (long)nt * (ta.Q / stream_rpw<PP>());
-      const long wgs = std::min((waves + 3) / 4, n_cu * STREAM_WG_PER_CU);
-      FSTAT_LAUNCH((k_tmpl_b_stream<float, PP, MD, BAND>), dim3((unsigned)wgs), dim3(256), 0, st, ta, nt, d.sp(), tbuf,
-                   oa, d.twst);
+      walk(mode_c, [&](auto rb_c) {
+        constexpr int RB = decltype(rb_c)::value, rows = stream_rpw<PP>() * RB;
+        const long waves = (long)nt * ((ta.Q + rows - 1) / rows);
+        const long wgs = std::min((waves + 3) / 4, n_cu * STREAM_WG_PER_CU);
+        FSTAT_LAUNCH((k_tmpl_b_stream<float, PP, MD, BAND, RB>), dim3((unsigned)wgs), dim3(256), 0, st, ta, nt, d.sp(),
+                     tbuf, oa, d.twst);
+      });
     } else if constexpr (MD != 2) {
-      constexpr int NT2 = STREAM2_NT;
-      const long units = (long)nt * (ta.Q / (NT2 / groups_per_col<PP>()));
-      const long wgs = std::min(units, n_cu * STREAM2_WG_PER_CU);
-      FSTAT_LAUNCH((k_tmpl_b_stream2<MD, BAND, NT2>), dim3((unsigned)wgs), dim3(NT2), 0, st, ta, nt, d.sp(), tbuf, oa,
-                   d.twst);
+      walk(mode_c, [&](auto rb_c) {
+        constexpr int NT2 = STREAM2_NT, RB = decltype(rb_c)::value;
+        const long units = (long)nt * (ta.Q / (NT2 / groups_per_col<PP>() * RB));
+        const long wgs = std::min(units, n_cu * STREAM2_WG_PER_CU);
+        FSTAT_LAUNCH((k_tmpl_b_stream2<MD, BAND, NT2, RB>), dim3((unsigned)wgs), dim3(NT2), 0, st, ta, nt, d.sp(), tbuf,
+                     oa, d.twst);
+      });
     }
   };
   if (mode == 0) go(std::integral_constant<int, 0>{});

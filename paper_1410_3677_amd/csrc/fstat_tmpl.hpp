@@ -1171,7 +1171,30 @@ constexpr int CAP_BLOCK = 8;
 template <int P>
 __host__ __device__ constexpr int stream_rpw() { return 64 / groups_per_col<P>(); }
 
-template <typename T, int P, int MODE, int BAND>
+// The spectrum (MODE 1) is bin-major, k = Q k1 + k2, and a lane forms the bins of one row k2,
+// Q apart: a lane therefore takes SPEC_ROWS consecutive rows in turn and stores each k1's
+// bins together, 16 bytes, which the workgroup's other wavefronts, four rows further each,
+// fill to 64 (stored one by one as they were formed, 4 bytes per line and row: 233 us for
+// 128 templates of 2^18 points, against 67 of the transforms themselves).  The rows are
+// walked by a loop that is not unrolled, the finished ones moving down a register queue:
+// unrolled, the loads of all four rows moved to the top and took 330 registers.
+constexpr int SPEC_ROWS = 4;
+typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));
+// The first `rows` of bins k .. k + RB - 1 at out[k - k_min], those in [k_min, k_max) (inside: all).
+template <int RB>
+__device__ __forceinline__ void store_bins(float* out, const OutArgs& oa, int k, int rows, bool inside,
+                                           const float (&v)[RB]) {
+  if (RB == SPEC_ROWS && rows >= SPEC_ROWS && (inside || (k >= oa.k_min && k + SPEC_ROWS <= oa.k_max))) {
+    *reinterpret_cast<f4u_t*>(out + (k - oa.k_min)) = f4u_t{v[0], v[1 % RB], v[2 % RB], v[3 % RB]};
+  } else {
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+      if (i < rows && (inside || (k + i >= oa.k_min && k + i < oa.k_max))) out[k + i - oa.k_min] = v[i];
+  }
+}
+
+// RB: rows a lane takes in turn, SPEC_ROWS in spectrum launches that still fill the chip so.
+template <typename T, int P, int MODE, int BAND, int RB>
 __global__ void __launch_bounds__(256) k_tmpl_b_stream(TmplArgs ta, int ntmpl, const SkyParams* __restrict__ sp,
                                                        const cx<T>* __restrict__ tbuf, OutArgs oa,
                                                        const cx<T>* __restrict__ twst) {
@@ -1197,7 +1220,7 @@ __global__ void __launch_bounds__(256) k_tmpl_b_stream(TmplArgs ta, int ntmpl, c
   __shared__ float st_val[4][STAGE_CAP];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int units = ta.Q / RPW;        // row units of one template
+  const int units = (ta.Q + RPW * RB - 1) / (RPW * RB);        // row units of one template
   const int total = ntmpl * units;     // row units of the launch
   const int nw = gridDim.x * 4;        // wavefronts of the grid
   const int sub = lane / G, g = lane % G;
@@ -1208,16 +1231,18 @@ __global__ void __launch_bounds__(256) k_tmpl_b_stream(TmplArgs ta, int ntmpl, c
   StageTw<T, P, G, R1> tw;
   tw.load(twst, g);
   const auto& twl = last_stage_tw<T, P, G, R1>(tw);
-  const int lofs = sub * P + g;
 
-  // unit U of the launch: template U / units, rows (U % units) RPW + sub
-  auto load_unit = [&](cx<T> (&ca)[PB1][R1], cx<T> (&cb)[PB1][R1], int U) {
+  // row i of unit U of the launch: template U / units, row ((U % units) RPW + sub) RB + i (the
+  // last unit may reach past the Q rows: its extra rows read the last one and store nothing)
+  auto load_row = [&](cx<T> (&ca)[PB1][R1], cx<T> (&cb)[PB1][R1], int U, int i) {
     const int item = U / units, u = U - item * units;
-    const cx<T>* p = tbuf + (long)(2 * item) * ta.L + 2 * (long)u * (RPW * P);
+    int row = (u * RPW + sub) * RB + i;
+    if (RB > 1) row = min(row, ta.Q - 1);
+    const cx<T>* p = tbuf + (long)(2 * item) * ta.L + 2 * ((long)row * P + g);
 #pragma unroll
     for (int b = 0; b < PB1; ++b)
 #pragma unroll
-      for (int r = 0; r < R1; ++r) load_stream(p + 2 * (lofs + G * b + NB1 * r), ca[b][r], cb[b][r]);
+      for (int r = 0; r < R1; ++r) load_stream(p + 2 * (G * b + NB1 * r), ca[b][r], cb[b][r]);
   };
 
   WaveStage stg{st_item[wave], st_bin[wave], st_val[wave]};
@@ -1227,7 +1252,7 @@ __global__ void __launch_bounds__(256) k_tmpl_b_stream(TmplArgs ta, int ntmpl, c
   int U = blockIdx.x * 4 + wave;
   if (U >= total) return;
   cx<T> xa[PB1][R1], xb[PB1][R1];
-  load_unit(xa, xb, U);
+  load_row(xa, xb, U, 0);
   for (; U < total; U += nw) {
     const int item = U / units;
     const int u = U - item * units;
@@ -1235,22 +1260,66 @@ __global__ void __launch_bounds__(256) k_tmpl_b_stream(TmplArgs ta, int ntmpl, c
     const int skyl = t / ta.nfdot, sidx = t - skyl * ta.nfdot;
     const SkyParams& pr = sp[skyl];
     const T cfa = (T)pr.cfa, cfb = (T)pr.cfb, cfab = (T)pr.cfab;
+    const int k2 = (u * RPW + sub) * RB;
+    T spec[MODE == 1 ? NOUT : 1][RB] = {};
+#pragma unroll 1
+    for (int i = 0; i < RB; ++i) {
 #pragma unroll
-    for (int b = 0; b < PB1; ++b) {
-      dftr<T, R1, false>(xa[b]);
-      dftr<T, R1, false>(xb[b]);
+      for (int b = 0; b < PB1; ++b) {
+        dftr<T, R1, false>(xa[b]);
+        dftr<T, R1, false>(xb[b]);
+      }
+      stage_sync<true>();  // the previous row's last stage has read the slab
+      stage_to_lds_off<T, P, G, 1, R1, PB1>(xa, cola, g);
+      stage_to_lds_off<T, P, G, 1, R1, PB1>(xb, colb, g);
+      stage_sync<true>();
+      // the next row's loads go into the registers just freed and overlap the rest
+      if (i + 1 < RB) load_row(xa, xb, U, i + 1);
+      else if (U + nw < total) load_row(xa, xb, U + nw, 0);
+      middle_stages_reg<T, P, G, R1>(cola, colb, g, tw);
+      cx<T> fa[PBL][RL], fb[PBL][RL];
+      stage_from_lds_reg<T, P, G, NSL, RL, PBL, HALF>(fa, cola, g, twl.w);
+      stage_from_lds_reg<T, P, G, NSL, RL, PBL, HALF>(fb, colb, g, twl.w);
+      if constexpr (MODE == 1) {
+#pragma unroll
+        for (int b = 0; b < PBL; ++b)
+#pragma unroll
+          for (int r = 0; r < ROUT; ++r)
+            if (band_keeps<P, BAND>(G * b + NSL * r)) {
+              T (&q)[RB] = spec[b * ROUT + r];
+#pragma unroll
+              for (int k = 0; k + 1 < RB; ++k) q[k] = q[k + 1];
+              q[RB - 1] = two_f_value(fa[b][r], fb[b][r], cfa, cfb, cfab);
+            }
+      } else {
+        // MODE 2 (patch capture) stores the launch's 2F values in blocks of eight columns,
+        // [template][k1 / 8][k2][k1 % 8] (RLEN columns: the outputs a row forms): eight lanes
+        // store 32 contiguous bytes, the lines filled by the neighbouring rows that other
+        // wavefronts form at the same time, and a window's 256 consecutive bins (consecutive
+        // k2, one or two k1) lie four to a 128-byte line
+        constexpr int RLEN = HALF ? P / 2 : P;
+        static_assert(RLEN % CAP_BLOCK == 0, "whole column blocks");
+        float* srow = (float*)oa.spectrum + (long)item * ta.Q * RLEN + (long)k2 * CAP_BLOCK;
+        uint32_t mask = 0;
+        T val[NOUT];
+#pragma unroll
+        for (int b = 0; b < PBL; ++b)
+#pragma unroll
+          for (int r = 0; r < ROUT; ++r) {
+            val[b * ROUT + r] = (T)0;
+            if (!band_keeps<P, BAND>(G * b + NSL * r)) continue;
+            const int k1 = g + G * b + NSL * r;
+            const int k = ta.Q * k1 + k2;
+            const T v = two_f_value(fa[b][r], fb[b][r], cfa, cfb, cfab);
+            val[b * ROUT + r] = v;
+            const bool inr = band_inside<P, G, BAND>(G * b + NSL * r) || (k >= oa.k_min && k < oa.k_max);
+            if (MODE == 2) srow[(long)(k1 / CAP_BLOCK) * ta.Q * CAP_BLOCK + k1 % CAP_BLOCK] = (float)v;
+            if (inr && v > thr) mask |= 1u << (b * ROUT + r);
+          }
+        stg.add<false>(oa, ta, search, lane, mask, val, item,
+                       [&](int q) { return ta.Q * (g + G * (q / ROUT) + NSL * (q % ROUT)) + k2; });
+      }
     }
-    stage_sync<true>();  // the previous unit's last stage has read the slab
-    stage_to_lds_off<T, P, G, 1, R1, PB1>(xa, cola, g);
-    stage_to_lds_off<T, P, G, 1, R1, PB1>(xb, colb, g);
-    stage_sync<true>();
-    // the next unit's loads go into the registers just freed and overlap the rest
-    if (U + nw < total) load_unit(xa, xb, U + nw);
-    middle_stages_reg<T, P, G, R1>(cola, colb, g, tw);
-    cx<T> fa[PBL][RL], fb[PBL][RL];
-    stage_from_lds_reg<T, P, G, NSL, RL, PBL, HALF>(fa, cola, g, twl.w);
-    stage_from_lds_reg<T, P, G, NSL, RL, PBL, HALF>(fb, colb, g, twl.w);
-    const int k2 = u * RPW + sub;
     if constexpr (MODE == 1) {
       T* out = (T*)oa.spectrum + ((long)(ta.sky0 + skyl) * ta.nfdot + sidx) * (long)(oa.k_max - oa.k_min);
 #pragma unroll
@@ -1258,37 +1327,9 @@ __global__ void __launch_bounds__(256) k_tmpl_b_stream(TmplArgs ta, int ntmpl, c
 #pragma unroll
         for (int r = 0; r < ROUT; ++r) {
           if (!band_keeps<P, BAND>(G * b + NSL * r)) continue;
-          const int k = ta.Q * (g + G * b + NSL * r) + k2;
-          if (band_inside<P, G, BAND>(G * b + NSL * r) || (k >= oa.k_min && k < oa.k_max))
-            out[k - oa.k_min] = two_f_value(fa[b][r], fb[b][r], cfa, cfb, cfab);
+          store_bins<RB>(out, oa, ta.Q * (g + G * b + NSL * r) + k2, ta.Q - k2,
+                     band_inside<P, G, BAND>(G * b + NSL * r), spec[b * ROUT + r]);
         }
-    } else {
-      // MODE 2 (patch capture) stores the launch's 2F values in blocks of eight columns,
-      // [template][k1 / 8][k2][k1 % 8] (RLEN columns: the outputs a row forms): eight lanes
-      // store 32 contiguous bytes, the lines filled by the neighbouring rows that other
-      // wavefronts form at the same time, and a window's 256 consecutive bins (consecutive
-      // k2, one or two k1) lie four to a 128-byte line
-      constexpr int RLEN = HALF ? P / 2 : P;
-      static_assert(RLEN % CAP_BLOCK == 0, "whole column blocks");
-      float* srow = (float*)oa.spectrum + (long)item * ta.Q * RLEN + (long)k2 * CAP_BLOCK;
-      uint32_t mask = 0;
-      T val[NOUT];
-#pragma unroll
-      for (int b = 0; b < PBL; ++b)
-#pragma unroll
-        for (int r = 0; r < ROUT; ++r) {
-          val[b * ROUT + r] = (T)0;
-          if (!band_keeps<P, BAND>(G * b + NSL * r)) continue;
-          const int k1 = g + G * b + NSL * r;
-          const int k = ta.Q * k1 + k2;
-          const T v = two_f_value(fa[b][r], fb[b][r], cfa, cfb, cfab);
-          val[b * ROUT + r] = v;
-          const bool inr = band_inside<P, G, BAND>(G * b + NSL * r) || (k >= oa.k_min && k < oa.k_max);
-          if (MODE == 2) srow[(long)(k1 / CAP_BLOCK) * ta.Q * CAP_BLOCK + k1 % CAP_BLOCK] = (float)v;
-          if (inr && v > thr) mask |= 1u << (b * ROUT + r);
-        }
-      stg.add<false>(oa, ta, search, lane, mask, val, item,
-                     [&](int q) { return ta.Q * (g + G * (q / ROUT) + NSL * (q % ROUT)) + k2; });
     }
   }
   if constexpr (MODE != 1) stg.flush(oa, ta, search, lane);
@@ -1304,7 +1345,7 @@ __global__ void __launch_bounds__(256) k_tmpl_b_stream(TmplArgs ta, int ntmpl, c
 // registers; workgroup barriers order the stages.  MODE 0: threshold and candidates
 // (staged per wavefront), MODE 1: the 2F spectrum.  With HALF (bins [0, nfft/2)) the
 // radix-2 last stage forms only the outputs k1 < P/2.
-template <int MODE, int BAND, int NT>
+template <int MODE, int BAND, int NT, int RB>
 __global__ void __launch_bounds__(NT) k_tmpl_b_stream2(TmplArgs ta, int ntmpl, const SkyParams* __restrict__ sp,
                                                         const cx<float>* __restrict__ tbuf, OutArgs oa,
                                                         const cx<float>* __restrict__ twst) {
@@ -1334,7 +1375,7 @@ __global__ void __launch_bounds__(NT) k_tmpl_b_stream2(TmplArgs ta, int ntmpl, c
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int sub = threadIdx.x / G, g = threadIdx.x % G;
-  const int units = ta.Q / RPB;        // row units of one template
+  const int units = ta.Q / (RPB * RB);  // row units of one template
   const int total = ntmpl * units;     // row units of the launch
   const int nwg = gridDim.x;
   cx<T>* cola = lds + (2 * sub) * ST;
@@ -1345,10 +1386,10 @@ __global__ void __launch_bounds__(NT) k_tmpl_b_stream2(TmplArgs ta, int ntmpl, c
   tw.load(twst, g);
   const auto& twl = last_stage_tw<T, P, G, R1>(tw);
 
-  // unit U of the launch: template U / units, rows (U % units) RPB + sub
-  auto load_unit = [&](cx<T> (&ca)[PB1][R1], cx<T> (&cb)[PB1][R1], int U) {
+  // row i of unit U of the launch: template U / units, row ((U % units) RPB + sub) RB + i
+  auto load_row = [&](cx<T> (&ca)[PB1][R1], cx<T> (&cb)[PB1][R1], int U, int i) {
     const int item = U / units, u = U - item * units;
-    const cx<T>* p = tbuf + (long)(2 * item) * ta.L + 2 * (long)(u * RPB + sub) * P;
+    const cx<T>* p = tbuf + (long)(2 * item) * ta.L + 2 * (long)((u * RPB + sub) * RB + i) * P;
 #pragma unroll
     for (int r = 0; r < R1; ++r) load_stream(p + 2 * (g + NB1 * r), ca[0][r], cb[0][r]);
   };
@@ -1358,7 +1399,7 @@ __global__ void __launch_bounds__(NT) k_tmpl_b_stream2(TmplArgs ta, int ntmpl, c
   int U = blockIdx.x;
   if (U >= total) return;   // the same for the whole workgroup
   cx<T> xa[PB1][R1], xb[PB1][R1];
-  load_unit(xa, xb, U);
+  load_row(xa, xb, U, 0);
   for (; U < total; U += nwg) {
     const int item = U / units;
     const int u = U - item * units;
@@ -1366,19 +1407,53 @@ __global__ void __launch_bounds__(NT) k_tmpl_b_stream2(TmplArgs ta, int ntmpl, c
     const int skyl = t / ta.nfdot, sidx = t - skyl * ta.nfdot;
     const SkyParams& pr = sp[skyl];
     const T cfa = (T)pr.cfa, cfb = (T)pr.cfb, cfab = (T)pr.cfab;
-    dftr<T, R1, false>(xa[0]);
-    dftr<T, R1, false>(xb[0]);
-    __syncthreads();  // the previous unit's last stage has read the tile
-    stage_to_lds_off<T, P, G, 1, R1, PB1>(xa, cola, g);
-    stage_to_lds_off<T, P, G, 1, R1, PB1>(xb, colb, g);
-    __syncthreads();
-    // the next unit's loads go into the registers just freed and overlap the rest
-    if (U + nwg < total) load_unit(xa, xb, U + nwg);
-    middle_stages_reg<T, P, G, R1, false>(cola, colb, g, tw);
-    cx<T> fa[PBL][RL], fb[PBL][RL];
-    stage_from_lds_reg<T, P, G, NSL, RL, PBL, HALF>(fa, cola, g, twl.w);
-    stage_from_lds_reg<T, P, G, NSL, RL, PBL, HALF>(fb, colb, g, twl.w);
-    const int k2 = u * RPB + sub;
+    const int k2 = (u * RPB + sub) * RB;
+    T spec[MODE == 1 ? NOUT : 1][RB] = {};
+#pragma unroll 1
+    for (int i = 0; i < RB; ++i) {
+      dftr<T, R1, false>(xa[0]);
+      dftr<T, R1, false>(xb[0]);
+      __syncthreads();  // the previous row's last stage has read the tile
+      stage_to_lds_off<T, P, G, 1, R1, PB1>(xa, cola, g);
+      stage_to_lds_off<T, P, G, 1, R1, PB1>(xb, colb, g);
+      __syncthreads();
+      // the next row's loads go into the registers just freed and overlap the rest
+      if (i + 1 < RB) load_row(xa, xb, U, i + 1);
+      else if (U + nwg < total) load_row(xa, xb, U + nwg, 0);
+      middle_stages_reg<T, P, G, R1, false>(cola, colb, g, tw);
+      cx<T> fa[PBL][RL], fb[PBL][RL];
+      stage_from_lds_reg<T, P, G, NSL, RL, PBL, HALF>(fa, cola, g, twl.w);
+      stage_from_lds_reg<T, P, G, NSL, RL, PBL, HALF>(fb, colb, g, twl.w);
+      if constexpr (MODE == 1) {
+#pragma unroll
+        for (int b = 0; b < PBL; ++b)
+#pragma unroll
+          for (int r = 0; r < ROUT; ++r)
+            if (band_keeps<P, BAND>(G * b + NSL * r)) {
+              T (&q)[RB] = spec[b * ROUT + r];
+#pragma unroll
+              for (int k = 0; k + 1 < RB; ++k) q[k] = q[k + 1];
+              q[RB - 1] = two_f_value(fa[b][r], fb[b][r], cfa, cfb, cfab);
+            }
+      } else {
+        uint32_t mask = 0;
+        T val[NOUT];
+#pragma unroll
+        for (int b = 0; b < PBL; ++b)
+#pragma unroll
+          for (int r = 0; r < ROUT; ++r) {
+            val[b * ROUT + r] = (T)0;
+            if (!band_keeps<P, BAND>(G * b + NSL * r)) continue;
+            const int k = ta.Q * (g + G * b + NSL * r) + k2;
+            const T v = two_f_value(fa[b][r], fb[b][r], cfa, cfb, cfab);
+            val[b * ROUT + r] = v;
+            const bool inr = band_inside<P, G, BAND>(G * b + NSL * r) || (k >= oa.k_min && k < oa.k_max);
+            if (inr && v > thr) mask |= 1u << (b * ROUT + r);
+          }
+        stg.add<false>(oa, ta, search, lane, mask, val, item,
+                       [&](int q) { return ta.Q * (g + G * (q / ROUT) + NSL * (q % ROUT)) + k2; });
+      }
+    }
     if constexpr (MODE == 1) {
       T* out = (T*)oa.spectrum + ((long)(ta.sky0 + skyl) * ta.nfdot + sidx) * (long)(oa.k_max - oa.k_min);
 #pragma unroll
@@ -1386,27 +1461,9 @@ __global__ void __launch_bounds__(NT) k_tmpl_b_stream2(TmplArgs ta, int ntmpl, c
 #pragma unroll
         for (int r = 0; r < ROUT; ++r) {
           if (!band_keeps<P, BAND>(G * b + NSL * r)) continue;
-          const int k = ta.Q * (g + G * b + NSL * r) + k2;
-          if (band_inside<P, G, BAND>(G * b + NSL * r) || (k >= oa.k_min && k < oa.k_max))
-            out[k - oa.k_min] = two_f_value(fa[b][r], fb[b][r], cfa, cfb, cfab);
+          store_bins<RB>(out, oa, ta.Q * (g + G * b + NSL * r) + k2, RB,
+                     band_inside<P, G, BAND>(G * b + NSL * r), spec[b * ROUT + r]);
         }
-    } else {
-      uint32_t mask = 0;
-      T val[NOUT];
-#pragma unroll
-      for (int b = 0; b < PBL; ++b)
-#pragma unroll
-        for (int r = 0; r < ROUT; ++r) {
-          val[b * ROUT + r] = (T)0;
-          if (!band_keeps<P, BAND>(G * b + NSL * r)) continue;
-          const int k = ta.Q * (g + G * b + NSL * r) + k2;
-          const T v = two_f_value(fa[b][r], fb[b][r], cfa, cfb, cfab);
-          val[b * ROUT + r] = v;
-          const bool inr = band_inside<P, G, BAND>(G * b + NSL * r) || (k >= oa.k_min && k < oa.k_max);
-          if (inr && v > thr) mask |= 1u << (b * ROUT + r);
-        }
-      stg.add<false>(oa, ta, search, lane, mask, val, item,
-                     [&](int q) { return ta.Q * (g + G * (q / ROUT) + NSL * (q % ROUT)) + k2; });
     }
   }
   if constexpr (MODE == 0) stg.flush(oa, ta, search, lane);

@@ -174,3 +174,20 @@ def test_budget_that_only_full_rate_fits(torch):
     got = _spectra(torch, plan, al, de, fd, nfft // 2)
     ref = _spectra(torch, make_plan([seg]), al, de, fd, nfft // 2)
     assert float(((got - ref).abs() / ref.clamp(min=4.0)).max()) < TOL
+
+
+@pytest.mark.parametrize("n,k_min,k_max", [(2048, 0, 0), (4097, 3, 8000), (30011, 5, 40006), (150001, 1, 262143)])
+def test_spectrum_rows_taken_in_turn(torch, n, k_min, k_max):
+    """Full-rate spectra large enough that each lane stores four rows' bins together: the
+    same 2F as the same templates one launch each, which store theirs one by one."""
+    seg = _segment(n)
+    nfft = synth.nfft_for(n)
+    nbins = (k_max or nfft // 2) - k_min
+    al, de, fd = _grid(n, nfft)
+    fd = np.append(fd, HUGE)
+    many = _spectra(torch, make_plan([seg], k_min=k_min, k_max=k_max), al, de, fd, nbins)
+    one = _spectra(torch, make_plan([seg], k_min=k_min, k_max=k_max, templates_per_launch=1), al, de, fd, nbins)
+    far = float(((many - one).abs() / one.clamp(min=4.0)).max())
+    note(f"n={n} bins [{k_min}, {k_max or nfft // 2}): {far:.2e}")
+    # instantiations may contract differently in the last place of about twenty stages
+    assert bool(torch.isfinite(many).all()) and far < TOL
