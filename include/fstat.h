@@ -166,7 +166,9 @@ fstat_status fstat_search_batch(fstat_plan_t plan, int32_t segment,
  * written.  With out and keys both NULL the call only reports the count and
  * drains the buffer (FSTAT_E_OVERFLOW only if the device buffer overflowed).
  * When the device buffer overflowed, which crossings were kept is
- * unspecified.  The ordering and the records are formed on the device in memory the
+ * unspecified.  Up to 4096 crossings of up to four searches are ordered and copied out by
+ * one launch through 256 KiB of page-locked memory of the plan.  Otherwise the ordering and
+ * the records are formed on the device in memory the
  * plan allocates at its first full drain and keeps until fstat_destroy (about 36 bytes
  * per stored crossing and 12 per template of the drained searches, plus 64 per
  * crossing copied out); FSTAT_E_NOMEM if it cannot, with the candidates kept for a

@@ -150,8 +150,9 @@ __global__ void k_drain_scatter(const CandEntry* __restrict__ cand, long long n,
 // k_drain_order_long.
 __global__ void __launch_bounds__(DRAIN_NT) k_drain_order(const CandEntry* __restrict__ grouped,
                                                           const unsigned long long* __restrict__ off, long long ntpl,
-                                                          CandEntry* __restrict__ out) {
+                                                          CandEntry* __restrict__ out, const unsigned* bad) {
   __shared__ int sbin[DRAIN_SEG_MAX];
+  if (*bad) return;   // a key outside its search: the entries stay as they are
   for (long long t = blockIdx.x; t < ntpl; t += gridDim.x) {
     const unsigned long long a = off[t], c = off[t + 1] - a;
     if (c == 0 || c > (unsigned long long)DRAIN_SEG_MAX) continue;
@@ -172,7 +173,8 @@ __global__ void __launch_bounds__(DRAIN_NT) k_drain_order(const CandEntry* __res
 // template's bins cross): a bitmap of the template's bins in LDS (up to 2^20 bins, the
 // longest transform), popcounts of 32-word blocks scanned across the workgroup, and each
 // entry's place = the set bits below its bin.  Bins of one template are distinct: a
-// repeated one, or a range wider than the bitmap, sets *bad.
+// repeated one, or a range wider than the bitmap, sets *bad (bad[-1]: a key outside its
+// search, as above).
 constexpr int DRAIN_LONG_NT = 1024;
 constexpr int DRAIN_BITMAP_WORDS = (1 << 20) / 32;
 __global__ void __launch_bounds__(DRAIN_LONG_NT) k_drain_order_long(const CandEntry* __restrict__ grouped,
@@ -184,6 +186,7 @@ __global__ void __launch_bounds__(DRAIN_LONG_NT) k_drain_order_long(const CandEn
   __shared__ int rmin[DRAIN_LONG_NT / 64], rmax[DRAIN_LONG_NT / 64];
   __shared__ unsigned wsum[DRAIN_LONG_NT / 64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  if (bad[-1]) return;
   for (long long t = blockIdx.x; t < ntpl; t += gridDim.x) {
     const unsigned long long a = off[t], c = off[t + 1] - a;
     if (c <= (unsigned long long)DRAIN_SEG_MAX) continue;
@@ -266,41 +269,143 @@ struct DrainSeg {
   int nfft;
 };
 
+// A search call's lists, kept on the device for the records of its candidates:
+// alpha[nsky], delta[nsky], then c[nc] and d[nd] to dst.
+__global__ void __launch_bounds__(DRAIN_NT) k_record_lists(const double* __restrict__ alpha,
+                                                           const double* __restrict__ delta, int nsky,
+                                                           const double* __restrict__ c, int nc,
+                                                           const double* __restrict__ d, int nd,
+                                                           double* __restrict__ dst) {
+  const long long n = 2LL * nsky + nc + nd;
+  for (long long i = (long long)blockIdx.x * DRAIN_NT + threadIdx.x; i < n; i += (long long)gridDim.x * DRAIN_NT) {
+    long long k = i;
+    double v;
+    if (k < nsky) v = alpha[k];
+    else if ((k -= nsky) < nsky) v = delta[k];
+    else if ((k -= nsky) < nc) v = c[k];
+    else v = d[k - nc];
+    dst[i] = v;
+  }
+}
+
+__device__ __forceinline__ fstat_candidate_key drain_key(const CandEntry& c, int scored) {
+  fstat_candidate_key k;
+  k.search = c.search;
+  k.segment = c.segment;
+  k.sky = c.sky;
+  k.fdot_idx = c.fdot_idx;
+  k.bin = c.bin;
+  k.vet_score = scored ? __int_as_float(c.pad) : __builtin_nanf("");
+  return k;
+}
+
+__device__ __forceinline__ fstat_candidate drain_record(const CandEntry& c, const DrainList& L, const DrainSeg& sg) {
+#pragma clang fp contract(off)
+  fstat_candidate r;
+  if (L.lattice) {
+    // the template's frequency shift and spindown, as the search kernels formed them
+    const int s = L.s_lo + c.fdot_idx;
+    const double u = lattice_shift_bins(lattice_w(s, L.m10, L.v[2 * L.nsky + c.sky]), (double)sg.nfft / (2.0 * M_PI));
+    r.f_hz = sg.f_off + ((double)c.bin + u) / ((double)sg.nfft * sg.dt);
+    r.fdot = lattice_w(s, L.m11, L.v[3 * L.nsky + c.sky]) / (M_PI * sg.dt * sg.dt);
+  } else {
+    r.f_hz = sg.f_off + (double)c.bin / ((double)sg.nfft * sg.dt);
+    r.fdot = L.v[2 * L.nsky + c.fdot_idx];
+  }
+  r.alpha = L.v[c.sky];
+  r.delta = L.v[L.nsky + c.sky];
+  r.twoF = c.twoF;
+  return r;
+}
+
 __global__ void k_drain_records(const CandEntry* __restrict__ ent, long long n, const DrainList* __restrict__ lists,
                                 int search0, const DrainSeg* __restrict__ segs, int scored,
                                 fstat_candidate* __restrict__ out, fstat_candidate_key* __restrict__ keys) {
-#pragma clang fp contract(off)
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
     const CandEntry c = ent[i];
-    if (keys) {
-      fstat_candidate_key k;
-      k.search = c.search;
-      k.segment = c.segment;
-      k.sky = c.sky;
-      k.fdot_idx = c.fdot_idx;
-      k.bin = c.bin;
-      k.vet_score = scored ? __int_as_float(c.pad) : __builtin_nanf("");
-      keys[i] = k;
-    }
-    if (out) {
-      const DrainList& L = lists[c.search - search0];
-      const DrainSeg sg = segs[c.segment];
-      fstat_candidate r;
-      if (L.lattice) {
-        // the template's frequency shift and spindown, as the search kernels formed them
-        const int s = L.s_lo + c.fdot_idx;
-        const double u = lattice_shift_bins(lattice_w(s, L.m10, L.v[2 * L.nsky + c.sky]), (double)sg.nfft / (2.0 * M_PI));
-        r.f_hz = sg.f_off + ((double)c.bin + u) / ((double)sg.nfft * sg.dt);
-        r.fdot = lattice_w(s, L.m11, L.v[3 * L.nsky + c.sky]) / (M_PI * sg.dt * sg.dt);
-      } else {
-        r.f_hz = sg.f_off + (double)c.bin / ((double)sg.nfft * sg.dt);
-        r.fdot = L.v[2 * L.nsky + c.fdot_idx];
+    if (keys) keys[i] = drain_key(c, scored);
+    if (out) out[i] = drain_record(c, lists[c.search - search0], segs[c.segment]);
+  }
+}
+
+// ---- small drains: one launch
+// Up to SMALL_CAP crossings of up to SMALL_SEARCHES searches: one workgroup reads the count,
+// sorts the entries' keys in LDS (template number, bin and entry packed into 63 bits) and
+// writes head, records and keys straight to page-locked host memory.  The general drain's
+// ten launches, three synchronous copies each way and per-search page-locked lists took
+// 250 us of a search that itself takes 150.
+constexpr int SMALL_CAP = 4096, SMALL_SEARCHES = 4, SMALL_NT = 1024;
+struct SmallDrain {
+  int nsearch, search0, nseg, scored, want;   // want: 0 count only, else records and keys
+  long long capacity, buffer;                 // entries asked for; entries of the device buffer
+  DrainSearch s[SMALL_SEARCHES];
+  DrainList l[SMALL_SEARCHES];
+};
+struct SmallHead {
+  unsigned long long count;
+  unsigned bad, done;                          // done: drained here (the count is reset)
+  unsigned flags[2], pad[2];                   // the general drain's flags
+};
+
+// The count of a general drain, unless its flags say that it failed.
+__global__ void k_drain_reset(unsigned long long* __restrict__ count, const unsigned* __restrict__ bad) {
+  if (!bad[0] && !bad[1]) *count = 0ull;
+}
+
+__global__ void __launch_bounds__(SMALL_NT) k_drain_small(SmallDrain a, const CandEntry* __restrict__ cand,
+                                                          unsigned long long* __restrict__ count,
+                                                          const DrainSeg* __restrict__ segs, SmallHead* head,
+                                                          fstat_candidate* out, fstat_candidate_key* keys) {
+  __shared__ unsigned long long key[SMALL_CAP];
+  __shared__ unsigned bad;
+  const int tid = threadIdx.x;
+  const unsigned long long found = *count;
+  if (tid == 0) bad = 0u;
+  __syncthreads();   // every thread has the count before it is reset
+  const bool small = a.want && found <= (unsigned long long)SMALL_CAP && (long long)found <= a.buffer;
+  if (small && found > 0) {
+    const int n = (int)found;
+    int n2 = 2;
+    while (n2 < n) n2 <<= 1;
+    for (int i = tid; i < n2; i += SMALL_NT) {
+      unsigned long long k = ~0ull;
+      if (i < n) {
+        const CandEntry c = cand[i];
+        const long long t = drain_template(c, a.s, a.nsearch, a.search0, a.nseg, &bad);
+        if (t >= 0) k = ((((unsigned long long)t << 20) | (unsigned)c.bin) << 12) | (unsigned)i;
       }
-      r.alpha = L.v[c.sky];
-      r.delta = L.v[L.nsky + c.sky];
-      r.twoF = c.twoF;
-      out[i] = r;
+      key[i] = k;
     }
+    __syncthreads();
+    for (int size = 2; size <= n2; size <<= 1)
+      for (int step = size >> 1; step > 0; step >>= 1) {
+        for (int p = tid; p < n2 / 2; p += SMALL_NT) {
+          const int lo = 2 * p - (p & (step - 1)), hi = lo + step;
+          const unsigned long long x = key[lo], y = key[hi];
+          if ((x > y) == ((lo & size) == 0)) {
+            key[lo] = y;
+            key[hi] = x;
+          }
+        }
+        __syncthreads();
+      }
+    if (!bad) {
+      const int nout = (int)min((long long)n, a.capacity);
+      for (int r = tid; r < nout; r += SMALL_NT) {
+        const CandEntry c = cand[key[r] & (SMALL_CAP - 1)];
+        keys[r] = drain_key(c, a.scored);
+        out[r] = drain_record(c, a.l[c.search - a.search0], segs[c.segment]);
+      }
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    const unsigned done = !a.want || (small && !bad);
+    head->count = found;
+    head->bad = bad;
+    head->done = done;
+    if (done) *count = 0ull;
+    __threadfence_system();
   }
 }
 

@@ -63,9 +63,9 @@ struct Grid {
 
 struct SearchRecord {
   int nsky = 0, nfdot = 0;
-  // pinned: alpha[nsky], delta[nsky], then fdot[nfdot] (explicit list) or
+  // device copy: alpha[nsky], delta[nsky], then fdot[nfdot] (explicit list) or
   // w_freq[nsky], w_spin[nsky] (lattice grid)
-  double* host = nullptr;
+  const double* lists = nullptr;
   bool lattice = false;
   int s_lo = 0;
   double m10 = 0.0, m11 = 0.0;
@@ -163,6 +163,12 @@ struct fstat_plan_s {
   unsigned long long* d_first = nullptr;
   bool scored = false;
   std::vector<SearchRecord> searches;
+  // device memory for the searches' lists since the last drain: chunks filled in turn and
+  // kept until destroy
+  struct ListChunk { double* dev; size_t cap, used; };
+  std::vector<ListChunk> list_chunks;
+  DrainSeg* d_segs = nullptr;    // what candidate records need of the segments
+  SmallHead* small = nullptr;    // page-locked: head, records and keys of a small drain
   // device memory of the key-ordering drain (grown on demand, kept until destroy)
   void* drain_ws = nullptr;
   size_t drain_bytes = 0;
@@ -1761,7 +1767,11 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
     }
   }
   p->tab.bytes = tb.size();
-  if ((e = hipMalloc(&p->tab.dev, tb.size())) != hipSuccess ||
+  std::vector<DrainSeg> dsegs;
+  for (auto& si : p->segs) dsegs.push_back(DrainSeg{si.s.f_off, si.s.dt, si.nfft});
+  if ((e = hipMalloc((void**)&p->d_segs, dsegs.size() * sizeof(DrainSeg))) != hipSuccess ||
+      (e = hipMemcpy(p->d_segs, dsegs.data(), dsegs.size() * sizeof(DrainSeg), hipMemcpyHostToDevice)) != hipSuccess ||
+      (e = hipMalloc(&p->tab.dev, tb.size())) != hipSuccess ||
       (e = hipMemcpy(p->tab.dev, tb.data(), tb.size(), hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMalloc((void**)&p->d_cand, (size_t)opt.candidate_capacity * sizeof(CandEntry))) != hipSuccess ||
       (e = hipMalloc((void**)&p->d_count, sizeof(unsigned long long))) != hipSuccess ||
@@ -1809,7 +1819,7 @@ static fstat_status check_lists(fstat_plan_t plan, int32_t segment, const double
   return FSTAT_OK;
 }
 
-// Pinned host copies of a search call's lists, for the candidate records.
+// Device copies of a search call's lists, for the candidate records.
 static fstat_status record_search(fstat_plan_t plan, const Grid& g, hipStream_t st) {
   SearchRecord rec;
   rec.nsky = g.nsky;
@@ -1819,19 +1829,37 @@ static fstat_status record_search(fstat_plan_t plan, const Grid& g, hipStream_t 
   rec.m10 = g.m10;
   rec.m11 = g.m11;
   const size_t nd = rec.lattice ? 4 * (size_t)g.nsky : 2 * (size_t)g.nsky + g.nfdot;
-  HIP_TRY(plan, hipHostMalloc((void**)&rec.host, nd * sizeof(double), hipHostMallocDefault), "pinned list copy");
-  plan->searches.push_back(rec);
-  const size_t ns = (size_t)g.nsky * sizeof(double);
-  HIP_TRY(plan, hipMemcpyAsync(rec.host, g.alpha, ns, hipMemcpyDeviceToHost, st), "list copy");
-  HIP_TRY(plan, hipMemcpyAsync(rec.host + g.nsky, g.delta, ns, hipMemcpyDeviceToHost, st), "list copy");
-  if (rec.lattice) {
-    HIP_TRY(plan, hipMemcpyAsync(rec.host + 2 * g.nsky, g.w_freq, ns, hipMemcpyDeviceToHost, st), "list copy");
-    HIP_TRY(plan, hipMemcpyAsync(rec.host + 3 * g.nsky, g.w_spin, ns, hipMemcpyDeviceToHost, st), "list copy");
-  } else {
-    HIP_TRY(plan, hipMemcpyAsync(rec.host + 2 * g.nsky, g.fdot, g.nfdot * sizeof(double), hipMemcpyDeviceToHost, st),
-            "list copy");
+  fstat_plan_s::ListChunk* c = nullptr;
+  for (auto& k : plan->list_chunks)
+    if (k.cap - k.used >= nd) {
+      c = &k;
+      break;
+    }
+  if (!c) {
+    fstat_plan_s::ListChunk k{nullptr, std::max<size_t>(nd, 1u << 16), 0};
+    HIP_TRY(plan, hipMalloc((void**)&k.dev, k.cap * sizeof(double)), "list copy memory");
+    plan->list_chunks.push_back(k);
+    c = &plan->list_chunks.back();
   }
+  double* dst = c->dev + c->used;
+  const unsigned blocks = (unsigned)std::min<size_t>((nd + DRAIN_NT - 1) / DRAIN_NT, 1024);
+  if (rec.lattice)
+    FSTAT_LAUNCH(k_record_lists, dim3(blocks), dim3(DRAIN_NT), 0, st, g.alpha, g.delta, g.nsky, g.w_freq, g.nsky,
+                 g.w_spin, g.nsky, dst);
+  else
+    FSTAT_LAUNCH(k_record_lists, dim3(blocks), dim3(DRAIN_NT), 0, st, g.alpha, g.delta, g.nsky, g.fdot, g.nfdot,
+                 (const double*)nullptr, 0, dst);
+  HIP_TRY(plan, launch_status(), "list copy");
+  c->used += nd;
+  rec.lists = dst;
+  plan->searches.push_back(rec);
   return FSTAT_OK;
+}
+
+// The searches since the last drain are done with.
+static void forget_searches(fstat_plan_t plan) {
+  plan->searches.clear();
+  for (auto& c : plan->list_chunks) c.used = 0;
 }
 
 static Grid explicit_grid(const double* alpha, const double* delta, int nsky, const double* fdot, int nfdot) {
@@ -2100,9 +2128,20 @@ fstat_status fstat_sky_stages(fstat_plan_t plan, int32_t segment, double alpha, 
   return r;
 }
 
+static DrainList drain_list(const SearchRecord& sr) {
+  DrainList l;
+  l.v = sr.lists;
+  l.nsky = sr.nsky;
+  l.lattice = sr.lattice ? 1 : 0;
+  l.s_lo = sr.s_lo;
+  l.m10 = sr.m10;
+  l.m11 = sr.m11;
+  return l;
+}
+
 // Key order on the device (fstat_drain.hpp: count -> offsets -> write, then each
 // template's range by bin), leaving d_cand[0, stored) ordered.
-static fstat_status order_on_device(fstat_plan_t p, long long stored) {
+static fstat_status order_on_device(fstat_plan_t p, long long stored, const DrainList** lists, unsigned** bad) {
   const int nsearch = (int)p->searches.size();
   const int search0 = p->search_count - nsearch;
   const int nseg = (int)p->segs.size();
@@ -2122,7 +2161,7 @@ static fstat_status order_on_device(fstat_plan_t p, long long stored) {
   auto put = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return at; };
   const size_t o_grp = put((size_t)stored * sizeof(CandEntry)), o_rank = put((size_t)stored * 4),
                o_cnt = put((size_t)ntpl * 4), o_off = put((size_t)(ntpl + 1) * 8), o_sums = put((size_t)ntiles * 8),
-               o_srch = put((size_t)nsearch * sizeof(DrainSearch)), o_flag = put(2 * 4);
+               o_tab = put((size_t)nsearch * (sizeof(DrainSearch) + sizeof(DrainList))), o_flag = put(2 * 4);
   if (o > p->drain_bytes) {
     if (p->drain_ws) (void)hipFree(p->drain_ws);
     p->drain_ws = nullptr;
@@ -2136,9 +2175,18 @@ static fstat_status order_on_device(fstat_plan_t p, long long stored) {
   unsigned* counts = (unsigned*)(w + o_cnt);
   unsigned long long* off = (unsigned long long*)(w + o_off);
   unsigned long long* sums = (unsigned long long*)(w + o_sums);
-  DrainSearch* ds = (DrainSearch*)(w + o_srch);
+  DrainSearch* ds = (DrainSearch*)(w + o_tab);
   unsigned* flags = (unsigned*)(w + o_flag);   // [0] key outside its search, [1] repeated bin of a template
-  HIP_TRY(p, hipMemcpy(ds, hs.data(), hs.size() * sizeof(DrainSearch), hipMemcpyHostToDevice), "drain tables");
+  // the searches, then their lists, in one copy
+  std::vector<unsigned char> tab(hs.size() * (sizeof(DrainSearch) + sizeof(DrainList)));
+  std::memcpy(tab.data(), hs.data(), hs.size() * sizeof(DrainSearch));
+  for (int i = 0; i < nsearch; ++i) {
+    const DrainList l = drain_list(p->searches[(size_t)i]);
+    std::memcpy(tab.data() + hs.size() * sizeof(DrainSearch) + (size_t)i * sizeof l, &l, sizeof l);
+  }
+  HIP_TRY(p, hipMemcpy(ds, tab.data(), tab.size(), hipMemcpyHostToDevice), "drain tables");
+  *lists = (const DrainList*)(ds + nsearch);
+  *bad = flags;
   const hipStream_t st = nullptr;
   const unsigned gblk = (unsigned)std::min<long long>((stored + DRAIN_NT - 1) / DRAIN_NT, 1LL << 20);
   FSTAT_LAUNCH(k_drain_zero, dim3((unsigned)std::min<long long>((ntpl + DRAIN_NT - 1) / DRAIN_NT, 1LL << 20)),
@@ -2147,41 +2195,28 @@ static fstat_status order_on_device(fstat_plan_t p, long long stored) {
   FSTAT_LAUNCH(k_drain_count, dim3(gblk), dim3(DRAIN_NT), 0, st, p->d_cand, stored, ds, nsearch, search0, nseg, counts,
                rank, flags);
   HIP_TRY(p, launch_status(), "drain count launch");
-  unsigned hf[2] = {0, 0};
-  HIP_TRY(p, hipMemcpy(hf, flags, sizeof hf, hipMemcpyDeviceToHost), "drain flags");
-  if (hf[0]) return fail(p, FSTAT_E_STATE, "a stored candidate's key lies outside its search");
   FSTAT_LAUNCH(k_scan_tile_sums, dim3((unsigned)ntiles), dim3(DRAIN_NT), 0, st, counts, ntpl, sums);
   FSTAT_LAUNCH(k_scan_sums, dim3(1), dim3(DRAIN_NT), 0, st, sums, ntiles);
   FSTAT_LAUNCH(k_scan_apply, dim3((unsigned)ntiles), dim3(DRAIN_NT), 0, st, counts, ntpl, sums, off);
   FSTAT_LAUNCH(k_drain_scatter, dim3(gblk), dim3(DRAIN_NT), 0, st, p->d_cand, stored, ds, nsearch, search0, nseg, off,
                rank, grouped, flags);
   FSTAT_LAUNCH(k_drain_order, dim3((unsigned)std::min<long long>(ntpl, 1LL << 18)), dim3(DRAIN_NT), 0, st, grouped, off,
-               ntpl, p->d_cand);
+               ntpl, p->d_cand, flags);
   FSTAT_LAUNCH(k_drain_order_long, dim3((unsigned)std::min<long long>(ntpl, 2LL * p->n_cu)), dim3(DRAIN_LONG_NT), 0,
                st, grouped, off, ntpl, p->d_cand, flags + 1);
   HIP_TRY(p, launch_status(), "drain ordering launch");
-  HIP_TRY(p, hipMemcpy(hf, flags, sizeof hf, hipMemcpyDeviceToHost), "drain flags");
-  if (hf[0] || hf[1]) return fail(p, FSTAT_E_STATE, "a template's candidates repeat a bin");
   return FSTAT_OK;
 }
 
 // Records and keys of the first `nout` entries of d_cand (in key order) formed on the device
 // and copied straight into the caller's arrays (either may be NULL).
-static fstat_status form_on_device(fstat_plan_t p, long long nout, fstat_candidate* out, fstat_candidate_key* keys) {
-  const int nsearch = (int)p->searches.size();
-  const int search0 = p->search_count - nsearch;
-  std::vector<size_t> nd((size_t)nsearch);
-  size_t ndouble = 0;
-  for (int i = 0; i < nsearch; ++i) {
-    const SearchRecord& sr = p->searches[(size_t)i];
-    nd[(size_t)i] = sr.lattice ? 4 * (size_t)sr.nsky : 2 * (size_t)sr.nsky + sr.nfdot;
-    ndouble += nd[(size_t)i];
-  }
+static fstat_status form_on_device(fstat_plan_t p, long long nout, const DrainList* dl, const unsigned* bad,
+                                   fstat_candidate* out, fstat_candidate_key* keys) {
+  const int search0 = p->search_count - (int)p->searches.size();
   size_t o = 0;
   auto put = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return at; };
   const size_t o_rec = put(out ? (size_t)nout * sizeof(fstat_candidate) : 0),
-               o_key = put(keys ? (size_t)nout * sizeof(fstat_candidate_key) : 0), o_val = put(ndouble * 8),
-               o_list = put((size_t)nsearch * sizeof(DrainList)), o_seg = put(p->segs.size() * sizeof(DrainSeg));
+               o_key = put(keys ? (size_t)nout * sizeof(fstat_candidate_key) : 0);
   if (o > p->drain_out_bytes) {
     if (p->drain_out) (void)hipFree(p->drain_out);
     p->drain_out = nullptr;
@@ -2190,40 +2225,28 @@ static fstat_status form_on_device(fstat_plan_t p, long long nout, fstat_candida
     p->drain_out_bytes = o;
   }
   char* w = (char*)p->drain_out;
-  double* vals = (double*)(w + o_val);
-  std::vector<DrainList> hl((size_t)nsearch);
-  size_t at = 0;
-  for (int i = 0; i < nsearch; ++i) {
-    const SearchRecord& sr = p->searches[(size_t)i];
-    HIP_TRY(p, hipMemcpy(vals + at, sr.host, nd[(size_t)i] * 8, hipMemcpyHostToDevice), "drain lists");
-    DrainList& L = hl[(size_t)i];
-    L.v = vals + at;
-    L.nsky = sr.nsky;
-    L.lattice = sr.lattice ? 1 : 0;
-    L.s_lo = sr.s_lo;
-    L.m10 = sr.m10;
-    L.m11 = sr.m11;
-    at += nd[(size_t)i];
-  }
-  std::vector<DrainSeg> hg(p->segs.size());
-  for (size_t i = 0; i < p->segs.size(); ++i) {
-    hg[i].f_off = p->segs[i].s.f_off;
-    hg[i].dt = p->segs[i].s.dt;
-    hg[i].nfft = p->segs[i].nfft;
-  }
-  DrainList* dl = (DrainList*)(w + o_list);
-  DrainSeg* dg = (DrainSeg*)(w + o_seg);
-  HIP_TRY(p, hipMemcpy(dl, hl.data(), hl.size() * sizeof(DrainList), hipMemcpyHostToDevice), "drain lists");
-  HIP_TRY(p, hipMemcpy(dg, hg.data(), hg.size() * sizeof(DrainSeg), hipMemcpyHostToDevice), "drain segments");
   fstat_candidate* drec = out ? (fstat_candidate*)(w + o_rec) : nullptr;
   fstat_candidate_key* dkey = keys ? (fstat_candidate_key*)(w + o_key) : nullptr;
   const unsigned blk = (unsigned)std::min<long long>((nout + DRAIN_NT - 1) / DRAIN_NT, 1LL << 20);
-  FSTAT_LAUNCH(k_drain_records, dim3(blk), dim3(DRAIN_NT), 0, (hipStream_t)nullptr, p->d_cand, nout, dl, search0, dg,
+  FSTAT_LAUNCH(k_drain_records, dim3(blk), dim3(DRAIN_NT), 0, (hipStream_t)nullptr, p->d_cand, nout, dl, search0, p->d_segs,
                p->scored ? 1 : 0, drec, dkey);
   HIP_TRY(p, launch_status(), "drain records launch");
-  if (out) HIP_TRY(p, hipMemcpy(out, drec, (size_t)nout * sizeof(fstat_candidate), hipMemcpyDeviceToHost), "record copy");
+  // copies, the ordering's flags and the count's reset (none where the flags are set), waited
+  // for once
+  const hipStream_t st = nullptr;
+  unsigned* hf = p->small->flags;
+  if (out)
+    HIP_TRY(p, hipMemcpyAsync(out, drec, (size_t)nout * sizeof(fstat_candidate), hipMemcpyDeviceToHost, st),
+            "record copy");
   if (keys)
-    HIP_TRY(p, hipMemcpy(keys, dkey, (size_t)nout * sizeof(fstat_candidate_key), hipMemcpyDeviceToHost), "key copy");
+    HIP_TRY(p, hipMemcpyAsync(keys, dkey, (size_t)nout * sizeof(fstat_candidate_key), hipMemcpyDeviceToHost, st),
+            "key copy");
+  HIP_TRY(p, hipMemcpyAsync(hf, bad, 2 * sizeof(unsigned), hipMemcpyDeviceToHost, st), "drain flags");
+  FSTAT_LAUNCH(k_drain_reset, dim3(1), dim3(1), 0, st, p->d_count, bad);
+  HIP_TRY(p, launch_status(), "count reset");
+  HIP_TRY(p, hipStreamSynchronize(st), "drain");
+  if (hf[0]) return fail(p, FSTAT_E_STATE, "a stored candidate's key lies outside its search");
+  if (hf[1]) return fail(p, FSTAT_E_STATE, "a template's candidates repeat a bin");
   return FSTAT_OK;
 }
 
@@ -2234,30 +2257,66 @@ fstat_status fstat_candidates(fstat_plan_t plan, fstat_candidate* out, fstat_can
   *n_found = 0;
   if (plan->used_stream) HIP_TRY(plan, hipStreamSynchronize(plan->last_stream), "stream synchronize");
   HIP_TRY(plan, hipDeviceSynchronize(), "device synchronize");
-  unsigned long long count = 0;
-  HIP_TRY(plan, hipMemcpy(&count, plan->d_count, sizeof count, hipMemcpyDeviceToHost), "count copy");
+  // one launch counts, and drains a small number of crossings whole
+  const int nsearch = (int)plan->searches.size();
+  const bool want = (out || keys) && capacity > 0;
+  SmallDrain sd{};
+  long long ntpl = 0;
+  if (want && nsearch <= SMALL_SEARCHES) {
+    for (int i = 0; i < nsearch; ++i) {
+      const SearchRecord& sr = plan->searches[(size_t)i];
+      sd.s[i] = DrainSearch{ntpl, sr.nsky, sr.nfdot};
+      sd.l[i] = drain_list(sr);
+      ntpl += (long long)plan->segs.size() * sr.nsky * sr.nfdot;
+    }
+    sd.nsearch = nsearch;
+  }
+  sd.search0 = plan->search_count - nsearch;
+  sd.nseg = (int)plan->segs.size();
+  sd.scored = plan->scored ? 1 : 0;
+  // without any output the launch only counts and resets; otherwise it also drains, where
+  // it can, or leaves the crossings as they are
+  sd.want = out || keys ? 1 : 0;
+  sd.capacity = want && nsearch >= 1 && nsearch <= SMALL_SEARCHES && ntpl <= (1LL << 31) ? capacity : 0;
+  sd.buffer = sd.capacity ? (long long)plan->opt.candidate_capacity : -1;   // -1: nothing is small enough
+  if (!plan->small)
+    HIP_TRY(plan, hipHostMalloc((void**)&plan->small, sizeof(SmallHead) + SMALL_CAP * (sizeof(fstat_candidate) +
+                                sizeof(fstat_candidate_key)), hipHostMallocDefault), "drain memory");
+  SmallHead* head = plan->small;
+  fstat_candidate* srec = reinterpret_cast<fstat_candidate*>(head + 1);
+  fstat_candidate_key* skey = reinterpret_cast<fstat_candidate_key*>(srec + SMALL_CAP);
+  FSTAT_LAUNCH(k_drain_small, dim3(1), dim3(SMALL_NT), 0, (hipStream_t)nullptr, sd, plan->d_cand, plan->d_count,
+               plan->d_segs, head, srec, skey);
+  HIP_TRY(plan, launch_status(), "drain launch");
+  HIP_TRY(plan, hipStreamSynchronize(nullptr), "drain");
+  const unsigned long long count = head->count;
   const long long stored = std::min<long long>((long long)count, plan->opt.candidate_capacity);
   if (!out && !keys) {
-    // count-only drain: nothing is copied or sorted
     plan->scored = false;
-    HIP_TRY(plan, hipMemset(plan->d_count, 0, sizeof(unsigned long long)), "count reset");
-    for (auto& sr : plan->searches) (void)hipHostFree(sr.host);
-    plan->searches.clear();
+    forget_searches(plan);
     *n_found = (int64_t)count;
     if ((long long)count > plan->opt.candidate_capacity)
       return fail(plan, FSTAT_E_OVERFLOW, "more candidates than the device buffer holds");
     return FSTAT_OK;
   }
-  // key order, records and keys on the device; the first min(stored, capacity) copied out
+  if (head->bad) return fail(plan, FSTAT_E_STATE, "a stored candidate's key lies outside its search");
   const long long nout = std::min<long long>(stored, capacity);
-  if (stored > 0 && nout > 0) {
-    fstat_status r = order_on_device(plan, stored);
-    if (r == FSTAT_OK) r = form_on_device(plan, nout, out, keys);
-    if (r != FSTAT_OK) return r;
+  if (head->done) {
+    if (out) std::memcpy(out, srec, (size_t)nout * sizeof(fstat_candidate));
+    if (keys) std::memcpy(keys, skey, (size_t)nout * sizeof(fstat_candidate_key));
+  } else {
+    // key order, records and keys on the device; the first min(stored, capacity) copied out
+    if (stored > 0 && nout > 0) {
+      const DrainList* lists = nullptr;
+      unsigned* bad = nullptr;
+      fstat_status r = order_on_device(plan, stored, &lists, &bad);
+      if (r == FSTAT_OK) r = form_on_device(plan, nout, lists, bad, out, keys);
+      if (r != FSTAT_OK) return r;
+    } else {
+      HIP_TRY(plan, hipMemset(plan->d_count, 0, sizeof(unsigned long long)), "count reset");
+    }
   }
-  HIP_TRY(plan, hipMemset(plan->d_count, 0, sizeof(unsigned long long)), "count reset");
-  for (auto& sr : plan->searches) (void)hipHostFree(sr.host);
-  plan->searches.clear();
+  forget_searches(plan);
   plan->scored = false;
   *n_found = (int64_t)count;
   if ((long long)count > plan->opt.candidate_capacity || (long long)count > capacity)
@@ -2408,8 +2467,7 @@ fstat_status fstat_autotune(fstat_plan_t plan, int32_t segment, double budget_ms
   (void)hipMemset(plan->d_count, 0, sizeof(unsigned long long));
   (void)hipMemset(plan->d_search_next, 0, sizeof(int));
   plan->search_count = 0;
-  for (auto& sr : plan->searches) (void)hipHostFree(sr.host);
-  plan->searches.clear();
+  forget_searches(plan);
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   (void)hipFree(dl);
@@ -2445,7 +2503,9 @@ fstat_status fstat_destroy(fstat_plan_t plan) {
     (void)hipEventDestroy(pr.b);
   }
   for (auto e : plan->ev_pool) (void)hipEventDestroy(e);
-  for (auto& sr : plan->searches) (void)hipHostFree(sr.host);
+  for (auto& c : plan->list_chunks) (void)hipFree(c.dev);
+  if (plan->d_segs) (void)hipFree(plan->d_segs);
+  if (plan->small) (void)hipHostFree(plan->small);
   if (plan->ws_owned && plan->ws) (void)hipFree(plan->ws);
   if (plan->tab.dev) (void)hipFree(plan->tab.dev);
   if (plan->d_cand) (void)hipFree(plan->d_cand);
