@@ -21,6 +21,7 @@
 #include "fstat_sky.hpp"
 #include "fstat_sky_fullrate.hpp"
 #include "fstat_vet.hpp"
+#include "fstat_vet_train.hpp"
 
 using namespace fstat;
 
@@ -109,11 +110,14 @@ struct fstat_vet_s {
   int steps = 0;                 // Adam steps taken
   void* mem = nullptr;           // one allocation for everything below
   float *theta = nullptr, *grad = nullptr, *m1 = nullptr, *m2 = nullptr;
-  uint16_t *wf2, *wt2, *wf3, *wt3, *w4b, *w5b;
-  uint16_t *wq2, *wq3;           // convolution weights in matrix-core fragment order (inference)
-  float *u, *z1, *z2, *z3, *z4, *z5, *a5, *logit, *dlogit, *lterm, *dz5, *dh4, *dx, *da, *dwm, *loss;
-  float* scratch = nullptr;      // split-K partial tiles and reduction partials
-  uint16_t *a1b, *a2b, *a3b, *a4b, *colA, *colB, *colC, *dz5b, *dz4b, *dzb;
+  vet::WeightCopies wc;          // BF16 copies of the weights
+  // training activations and gradients of a batch: input u, BF16 activations of the three
+  // convolutions and of the first dense layer, BF16 dz5, dz4, dz3, dz2; FP32 values and parts
+  // of the sums over patches; logits
+  float *u, *logit, *loss, *dz2, *sums3, *bsum, *part1, *convp;
+  vet::HeadOut head;
+  uint16_t *a1b, *a2b, *a3b, *a4b, *dz5b, *dz4b, *dz3b, *dz2b;
+  float* scratch = nullptr;      // split-K partial tiles, convolution gradient partials
   std::string last_error;
 };
 
@@ -1225,44 +1229,11 @@ fstat_status vet_fail(fstat_vet_t v, fstat_status st, const std::string& msg) {
                       std::string(what) + ": " + hip_error_text(e_));                 \
   } while (0)
 
-// C[m][n] = sum_k A(m, k) B(k, n) on the matrix cores.  Products with a long K and a small
-// output split K over workgroups into partial tiles (in `scratch`) summed in a fixed order.
 constexpr long VET_SCRATCH = 8L << 20;  // floats of split-K and reduction scratch
-void gemm(hipStream_t st, int M, int N, int K, const uint16_t* A, long sam, long sak, const uint16_t* B, long sbk,
-          long sbn, float* Cm, long ldc, float* scratch = nullptr) {
-  const int tiles = ((N + 63) / 64) * ((M + 63) / 64);
-  int splits = 1;
-  if (scratch && tiles < 256 && K >= 4096) {
-    splits = std::min(K / 1024, 1024 / tiles);
-    while (splits > 1 && (long)splits * M * N > VET_SCRATCH) --splits;
-    splits = std::max(splits, 1);
-  }
-  const int kchunk = ((K + splits - 1) / splits + 15) / 16 * 16;
-  dim3 grid((N + 63) / 64, (M + 63) / 64, splits);
-  if (splits == 1) {
-    FSTAT_LAUNCH(vet::k_gemm_bf16, grid, dim3(256), 0, st, M, N, K, A, sam, sak, B, sbk, sbn, Cm, ldc, 0L,
-                       kchunk);
-  } else {
-    const long count = (long)M * N;
-    FSTAT_LAUNCH(vet::k_gemm_bf16, grid, dim3(256), 0, st, M, N, K, A, sam, sak, B, sbk, sbn, scratch, (long)N,
-                       count, kchunk);
-    FSTAT_LAUNCH(vet::k_vet_sum_splits, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, scratch, splits,
-                       count, N, ldc, Cm);
-  }
-}
-
-// out[j] = sum_r m[r][j] (rows x cols, FP32), two fixed-order stages
-void colsum(hipStream_t st, const float* m, long rows, int cols, float* out, float* scratch) {
-  const long per = 4096;
-  const int chunks = (int)((rows + per - 1) / per);
-  FSTAT_LAUNCH(vet::k_vet_colsum_part, dim3(cols, chunks), dim3(256), 0, st, m, rows, cols, per, scratch);
-  FSTAT_LAUNCH(vet::k_vet_colsum_final, dim3((cols + 255) / 256), dim3(256), 0, st, scratch, chunks, cols, out);
-}
-
+// the BF16 copies of the master weights
 void vet_prepare(fstat_vet_t v, hipStream_t st) {
-  FSTAT_LAUNCH(vet::k_vet_prepare, blocks_for((long)vet::H * vet::X), dim3(256), 0, st, v->theta, v->wf2,
-                     v->wt2, v->wf3, v->wt3, v->w4b, v->w5b);
-  FSTAT_LAUNCH(vet::k_vet_prepare_frag, blocks_for(vet::WQ_ELEMS), dim3(256), 0, st, v->theta, v->wq2, v->wq3);
+  FSTAT_LAUNCH(vet::k_vet_update<false>, blocks_for(vet::N_PARAMS), dim3(256), 0, st, v->theta, v->grad, v->m1, v->m2,
+               v->wc, 0.f, 0.f, 0.f, 0.f);
 }
 
 // Scoring of n <= max_batch patches in two parts: the three convolutions into x (one
@@ -1276,18 +1247,18 @@ void vet_conv_stage(fstat_vet_t v, const float* patches, int n, uint16_t* x, hip
   using namespace vet;
   const long items = (long)n * CV_ITEMS;
   const unsigned grid = (unsigned)std::max(1L, std::min<long>(v->n_cu, (items + CV_WAVES - 1) / CV_WAVES));
-  FSTAT_LAUNCH(k_vet_conv_infer, dim3(grid), dim3(CV_NT), 0, st, patches, n, v->theta, v->wq2, v->wq3, x);
+  FSTAT_LAUNCH(k_vet_conv_infer, dim3(grid), dim3(CV_NT), 0, st, patches, n, v->theta, v->wc.wq2, v->wc.wq3, x);
 }
 
 void vet_dense_stage(fstat_vet_t v, const uint16_t* x, int n, float* out, hipStream_t st, CandEntry* cand) {
   using namespace vet;
   const int nbp = (n + GW_M - 1) / GW_M * GW_M;
-  FSTAT_LAUNCH(k_gemm_nt_wide, dim3(1, nbp / GW_M, INFER_SPLITS), dim3(GW_NT), 0, st, nbp, X, x, v->w4b, v->scratch,
+  FSTAT_LAUNCH(k_gemm_nt_wide, dim3(1, nbp / GW_M, INFER_SPLITS), dim3(GW_NT), 0, st, nbp, X, x, v->wc.w4b, v->scratch,
                X / INFER_SPLITS);
   const long count = (long)nbp * H;
   // the split-K sum, the two small layers and the score in one launch
   FSTAT_LAUNCH(k_vet_head_infer<INFER_SPLITS>, dim3((unsigned)((n + HD_NP - 1) / HD_NP)), dim3(256), 0, st,
-               v->scratch, count, n, v->theta, v->w5b, out, cand);
+               v->scratch, count, n, v->theta, v->wc.w5b, out, cand);
 }
 
 // All n patches in batches of max_batch on the caller's stream: each batch's convolutions,
@@ -1307,78 +1278,41 @@ static fstat_status vet_score_all(fstat_vet_t v, const float* patches, long long
   return FSTAT_OK;
 }
 
-// forward of n <= max_batch patches; logits to `out`
-void vet_forward_batch(fstat_vet_t v, const float* patches, int n, float* out, hipStream_t st) {
+// Gradient of the mean loss of n <= max_batch patches into v->grad, loss into v->loss
+// (fstat_vet_train.hpp).
+constexpr int TRAIN_CONV_PARTS = 256;   // parts at most of the convolutions' weight gradients
+void vet_gradient(fstat_vet_t v, const float* patches, const float* labels, int n, hipStream_t st) {
   using namespace vet;
+  FSTAT_LAUNCH(k_train_conv_fwd, dim3(n), dim3(256), 0, st, patches, v->theta, v->wc.f2, v->wc.f3, v->u, v->a1b, v->a2b,
+               v->a3b);
+  // the 8192 -> 128 layer: LDS-tiled product, K split so that the grid fills the chip
+  const int nbp = (n + GT - 1) / GT * GT;
+  const int tiles = (H / GT) * (nbp / GT);
+  int splits = 1;
+  while (splits < 32 && tiles * splits < 256) splits <<= 1;
+  FSTAT_LAUNCH(k_gemm_nt_lds, dim3(H / GT, nbp / GT, splits), dim3(256), 0, st, nbp, H, X, v->a3b, v->wc.w4b, v->scratch,
+               X / splits);
+  FSTAT_LAUNCH(k_train_head, dim3((n + HP - 1) / HP), dim3(256), 0, st, v->scratch, splits, (long)nbp * H, n, v->theta,
+               v->wc.w5b, labels, v->a4b, v->dz5b, v->dz4b, v->head);
+  // sums over many rows are split into parts of 1024 rows or more: dW5 from 4096 patches on
+  // (into the scratch, whose partial tiles the head has read), the convolutions' from 16
+  auto parts = [](long rows, int most) { return rows < 4096 ? 1 : (int)std::min<long>(rows / 1024, most); };
+  auto rows_per = [](long rows, int p) { return (int)((rows + p - 1) / p + 15) / 16 * 16; };
   const long NL = (long)n * L;
-  FSTAT_LAUNCH(k_vet_input, blocks_for(NL), dim3(256), 0, st, patches, NL, v->u);
-  FSTAT_LAUNCH(k_vet_conv1, blocks_for(NL * C), dim3(256), 0, st, v->u, n, v->theta, v->z1, v->a1b);
-  FSTAT_LAUNCH(k_vet_im2col, blocks_for(NL * KC), dim3(256), 0, st, v->a1b, n, 1, v->colA);
-  gemm(st, (int)NL, C, KC, v->colA, KC, 1, v->wf2, C, 1, v->z2, C);
-  FSTAT_LAUNCH(k_vet_bias_relu, blocks_for(NL * C), dim3(256), 0, st, v->z2, NL, C, v->theta + O_B2, v->a2b,
-                     (float*)nullptr);
-  FSTAT_LAUNCH(k_vet_im2col, blocks_for(NL * KC), dim3(256), 0, st, v->a2b, n, 1, v->colB);
-  gemm(st, (int)NL, C, KC, v->colB, KC, 1, v->wf3, C, 1, v->z3, C);
-  FSTAT_LAUNCH(k_vet_bias_relu, blocks_for(NL * C), dim3(256), 0, st, v->z3, NL, C, v->theta + O_B3, v->a3b,
-                     (float*)nullptr);
-  {
-    // the 8192 -> 128 layer: LDS-tiled product, K split so that the grid fills the chip
-    const int nbp = (n + GT - 1) / GT * GT;
-    const int tiles = (H / GT) * (nbp / GT);
-    int splits = 1;
-    while (splits < 32 && tiles * splits < 256) splits <<= 1;
-    FSTAT_LAUNCH(k_gemm_nt_lds, dim3(H / GT, nbp / GT, splits), dim3(256), 0, st, nbp, H, X, v->a3b, v->w4b,
-                       v->scratch, X / splits);
-    const long count = (long)nbp * H;
-    FSTAT_LAUNCH(k_vet_sum_splits, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, v->scratch, splits,
-                       count, H, (long)H, v->z4);
-  }
-  FSTAT_LAUNCH(k_vet_bias_relu, blocks_for((long)n * H), dim3(256), 0, st, v->z4, (long)n, H, v->theta + O_B4,
-                     v->a4b, (float*)nullptr);
-  gemm(st, n, H, H, v->a4b, H, 1, v->w5b, 1, H, v->z5, H);
-  FSTAT_LAUNCH(k_vet_bias_relu, blocks_for((long)n * H), dim3(256), 0, st, v->z5, (long)n, H, v->theta + O_B5,
-                     (uint16_t*)nullptr, v->a5);
-  FSTAT_LAUNCH(k_vet_fc3, blocks_for(n), dim3(256), 0, st, v->a5, n, v->theta, out);
+  const int split5 = parts(n, TRAIN_CONV_PARTS), conv = parts(NL, TRAIN_CONV_PARTS);
+  FSTAT_LAUNCH(k_train_dw_dense, dim3(DW_TILES + H / 64 * split5), dim3(256), 0, st, v->dz4b, v->a3b, v->dz5b, v->a4b, n,
+               split5, rows_per(n, split5), v->grad, v->scratch);
+  FSTAT_LAUNCH(k_train_dx, dim3(DW_TILES, (n + 63) / 64), dim3(256), 0, st, v->dz4b, v->wc.w4b, v->a3b, n, v->dz3b,
+               v->sums3);
+  FSTAT_LAUNCH(k_train_conv_bwd, dim3(n), dim3(256), 0, st, v->u, v->a1b, v->a2b, v->dz3b, v->wc.g3, v->wc.g2, v->dz2b,
+               v->dz2, v->part1);
+  FSTAT_LAUNCH(k_train_dw_conv, dim3(4 * conv + 4 * ((n + 15) / 16)), dim3(256), 0, st, v->a1b, v->a2b, v->dz2b, v->dz3b,
+               v->dz2, v->sums3, n, conv, rows_per(NL, conv), v->convp, v->bsum);
+  ReduceArgs ra{v->convp, v->part1, v->bsum, v->scratch, v->head, n, conv, split5};
+  FSTAT_LAUNCH(k_train_reduce, dim3(RD_DB + RD_W6 + RD_BIAS + RD_P1 + RD_CONV + (split5 > 1 ? RD_W5 : 0)), dim3(256), 0,
+               st, ra, v->grad, v->loss);
 }
-
-void vet_backward(fstat_vet_t v, const float* labels, int n, hipStream_t st) {
-  using namespace vet;
-  const long NL = (long)n * L;
-  float* g = v->grad;
-  float* sc = v->scratch;
-  FSTAT_LAUNCH(k_vet_head_backward, blocks_for((long)n * H), dim3(256), 0, st, v->logit, labels, n, v->theta,
-                     v->z5, v->dz5, v->dz5b, v->dlogit, v->lterm);
-  FSTAT_LAUNCH(k_vet_head_reduce, dim3(1), dim3(1024), 0, st, v->dlogit, v->a5, v->lterm, n, g, v->loss);
-  gemm(st, H, H, n, v->dz5b, 1, H, v->a4b, H, 1, g + O_W5, H, sc);             // dW5 = dz5^T a4
-  colsum(st, v->dz5, (long)n, H, g + O_B5, sc);
-  gemm(st, n, H, H, v->dz5b, H, 1, v->w5b, H, 1, v->dh4, H);                   // dh4 = dz5 W5
-  FSTAT_LAUNCH(k_vet_relu_mask, blocks_for((long)n * H), dim3(256), 0, st, v->dh4, v->z4, (long)n * H, v->dz4b);
-  gemm(st, H, X, n, v->dz4b, 1, H, v->a3b, X, 1, g + O_W4, X, sc);             // dW4 = dz4^T x
-  colsum(st, v->dh4, (long)n, H, g + O_B4, sc);
-  gemm(st, n, X, H, v->dz4b, H, 1, v->w4b, X, 1, v->dx, X);                    // dx = dz4 W4
-  FSTAT_LAUNCH(k_vet_relu_mask, blocks_for(NL * C), dim3(256), 0, st, v->dx, v->z3, NL * C, v->dzb);
-  gemm(st, KC, C, (int)NL, v->colB, 1, KC, v->dzb, C, 1, v->dwm, C, sc);        // dW3 (im2col layout)
-  FSTAT_LAUNCH(k_vet_scatter_conv_grad, blocks_for(C * C * KW), dim3(256), 0, st, v->dwm, g + O_W3);
-  colsum(st, v->dx, NL, C, g + O_B3, sc);
-  FSTAT_LAUNCH(k_vet_im2col, blocks_for(NL * KC), dim3(256), 0, st, v->dzb, n, -1, v->colC);
-  gemm(st, (int)NL, C, KC, v->colC, KC, 1, v->wt3, C, 1, v->da, C);             // da2
-  FSTAT_LAUNCH(k_vet_relu_mask, blocks_for(NL * C), dim3(256), 0, st, v->da, v->z2, NL * C, v->dzb);
-  gemm(st, KC, C, (int)NL, v->colA, 1, KC, v->dzb, C, 1, v->dwm, C, sc);        // dW2
-  FSTAT_LAUNCH(k_vet_scatter_conv_grad, blocks_for(C * C * KW), dim3(256), 0, st, v->dwm, g + O_W2);
-  colsum(st, v->da, NL, C, g + O_B2, sc);
-  FSTAT_LAUNCH(k_vet_im2col, blocks_for(NL * KC), dim3(256), 0, st, v->dzb, n, -1, v->colC);
-  gemm(st, (int)NL, C, KC, v->colC, KC, 1, v->wt2, C, 1, v->da, C);             // da1
-  FSTAT_LAUNCH(k_vet_relu_mask, blocks_for(NL * C), dim3(256), 0, st, v->da, v->z1, NL * C, v->dzb);
-  {
-    const long per = 256;
-    const int chunks = (int)((NL + per - 1) / per);
-    const int ncols = C * (KW + 1);
-    FSTAT_LAUNCH(k_vet_conv1_backward_part, dim3(chunks), dim3(256), 0, st, v->da, v->u, NL, per, sc);
-    FSTAT_LAUNCH(k_vet_colsum_final, dim3((ncols + 255) / 256), dim3(256), 0, st, sc, chunks, ncols,
-                       sc + (long)chunks * ncols);
-    FSTAT_LAUNCH(k_vet_conv1_scatter, dim3(1), dim3(256), 0, st, sc + (long)chunks * ncols, g);
-  }
-}
+static_assert((long)TRAIN_CONV_PARTS * vet::H * vet::H <= VET_SCRATCH, "parts of dW5 fit the scratch");
 }  // namespace
 
 int64_t fstat_vet_param_count(void) { return vet::N_PARAMS; }
@@ -1405,19 +1339,18 @@ fstat_status fstat_vet_create(int32_t max_batch, fstat_vet_t* out) {
   struct Part { void** p; size_t bytes; };
   std::vector<Part> parts = {
       {(void**)&v->theta, N_PARAMS * 4}, {(void**)&v->grad, N_PARAMS * 4}, {(void**)&v->m1, N_PARAMS * 4},
-      {(void**)&v->m2, N_PARAMS * 4}, {(void**)&v->wf2, KC * C * 2}, {(void**)&v->wt2, KC * C * 2},
-      {(void**)&v->wf3, KC * C * 2}, {(void**)&v->wt3, KC * C * 2}, {(void**)&v->w4b, (size_t)H * X * 2},
-      {(void**)&v->w5b, H * H * 2}, {(void**)&v->wq2, WQ_ELEMS * 2}, {(void**)&v->wq3, WQ_ELEMS * 2}, {(void**)&v->u, NL * 4}, {(void**)&v->z1, NL * C * 4},
-      {(void**)&v->z2, NL * C * 4}, {(void**)&v->z3, NL * C * 4}, {(void**)&v->z4, nbp * H * 4},
-      {(void**)&v->z5, nb * H * 4}, {(void**)&v->a5, nb * H * 4}, {(void**)&v->logit, nb * 4},
-      {(void**)&v->dlogit, nb * 4}, {(void**)&v->lterm, nb * 4}, {(void**)&v->dz5, nb * H * 4},
-      {(void**)&v->dh4, nb * H * 4}, {(void**)&v->dx, NL * C * 4}, {(void**)&v->da, NL * C * 4},
-      {(void**)&v->dwm, KC * C * 4}, {(void**)&v->loss, 4}, {(void**)&v->scratch, (size_t)VET_SCRATCH * 4},
-      {(void**)&v->a1b, NL * C * 2},
-      {(void**)&v->a2b, NL * C * 2}, {(void**)&v->a3b, nbp * X * 2},
-      {(void**)&v->a4b, nb * H * 2},
-      {(void**)&v->colA, NL * KC * 2}, {(void**)&v->colB, NL * KC * 2}, {(void**)&v->colC, NL * KC * 2},
-      {(void**)&v->dz5b, nb * H * 2}, {(void**)&v->dz4b, nb * H * 2}, {(void**)&v->dzb, NL * C * 2}};
+      {(void**)&v->m2, N_PARAMS * 4}, {(void**)&v->wc.w4b, (size_t)H * X * 2}, {(void**)&v->wc.w5b, H * H * 2},
+      {(void**)&v->wc.wq2, WQ_ELEMS * 2}, {(void**)&v->wc.wq3, WQ_ELEMS * 2}, {(void**)&v->wc.f2, TF_ELEMS * 2},
+      {(void**)&v->wc.f3, TF_ELEMS * 2}, {(void**)&v->wc.g2, TF_ELEMS * 2}, {(void**)&v->wc.g3, TF_ELEMS * 2},
+      {(void**)&v->u, NL * 4}, {(void**)&v->logit, nb * 4}, {(void**)&v->loss, 4},
+      {(void**)&v->dz2, NL * C * 4}, {(void**)&v->sums3, (nb + 15) / 16 * X * 4},
+      {(void**)&v->bsum, (nb + 15) / 16 * 2 * C * 4}, {(void**)&v->part1, nb * P1 * 4},
+      {(void**)&v->convp, (size_t)2 * TRAIN_CONV_PARTS * CP_W * 4}, {(void**)&v->head.a5, nb * H * 4},
+      {(void**)&v->head.dz5, nb * H * 4}, {(void**)&v->head.dz4, nb * H * 4}, {(void**)&v->head.dlogit, nb * 4},
+      {(void**)&v->head.term, nb * 4}, {(void**)&v->scratch, (size_t)VET_SCRATCH * 4},
+      {(void**)&v->a1b, NL * C * 2}, {(void**)&v->a2b, NL * C * 2}, {(void**)&v->a3b, nbp * X * 2},
+      {(void**)&v->a4b, nb * H * 2}, {(void**)&v->dz5b, nb * H * 2}, {(void**)&v->dz4b, nb * H * 2},
+      {(void**)&v->dz3b, NL * C * 2}, {(void**)&v->dz2b, NL * C * 2}};
   size_t total = 0;
   for (auto& pt : parts) total = align256(total + pt.bytes);
   hipError_t e = hipMalloc(&v->mem, total);
@@ -1468,8 +1401,7 @@ fstat_status fstat_vet_gradient(fstat_vet_t v, const float* patches, const float
                                 float* grad, void* stream) {
   if (!v || !patches || !labels || n < 1 || n > v->max_batch) return vet_fail(v, FSTAT_E_INVAL, "bad arguments");
   hipStream_t st = (hipStream_t)stream;
-  vet_forward_batch(v, patches, (int)n, v->logit, st);
-  vet_backward(v, labels, (int)n, st);
+  vet_gradient(v, patches, labels, (int)n, st);
   VET_TRY(v, launch_status(), "gradient launch");
   if (loss) VET_TRY(v, hipMemcpyAsync(loss, v->loss, 4, hipMemcpyDeviceToDevice, st), "loss copy");
   if (grad) VET_TRY(v, hipMemcpyAsync(grad, v->grad, vet::N_PARAMS * 4, hipMemcpyDeviceToDevice, st), "grad copy");
@@ -1482,9 +1414,8 @@ fstat_status fstat_vet_adam_step(fstat_vet_t v, float lr, float beta1, float bet
   hipStream_t st = (hipStream_t)stream;
   v->steps += 1;
   const double step = lr * std::sqrt(1.0 - std::pow((double)beta2, v->steps)) / (1.0 - std::pow((double)beta1, v->steps));
-  FSTAT_LAUNCH(vet::k_vet_adam, blocks_for(vet::N_PARAMS), dim3(256), 0, st, v->theta, v->grad, v->m1, v->m2,
-                     (long)vet::N_PARAMS, (float)step, beta1, beta2, eps);
-  vet_prepare(v, st);
+  FSTAT_LAUNCH(vet::k_vet_update<true>, blocks_for(vet::N_PARAMS), dim3(256), 0, st, v->theta, v->grad, v->m1, v->m2,
+               v->wc, (float)step, beta1, beta2, eps);
   VET_TRY(v, launch_status(), "optimiser launch");
   return FSTAT_OK;
 }

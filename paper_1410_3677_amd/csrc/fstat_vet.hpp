@@ -49,316 +49,9 @@ __device__ __forceinline__ v8s lds8(const uint16_t* p) {
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
-// C[m][n] = sum_k A(m, k) B(k, n) over k in this workgroup's K range
-// A(m, k) = A[m*sam + k*sak], B(k, n) = B[k*sbk + n*sbn] (BF16), C row-major with ldc (FP32).
-// Workgroup: 4 wavefronts, a 64 x 64 tile of C; each wavefront a 32 x 32 block made of
-// 2 x 2 matrix-core tiles of 16 x 16, stepping K by 16.  Out-of-range elements are zero.
-// Matrix-core operand layout (16x16x16): lane l holds A[l%16][4(l/16)+i], B[4(l/16)+i][l%16]
-// and receives D[4(l/16)+i][l%16], i = 0..3.  With gridDim.z > 1 the K range is split and
-// each split writes its partial tile to C + z * split_stride (summed by k_vet_sum_splits).
-// Operands contiguous along K (stride 1) are read four elements per 8-byte load.
-__device__ __forceinline__ v4s load4(const uint16_t* __restrict__ p, long base, long stride, int k, int K, bool vec) {
-  v4s r;
-  if (vec && k + 3 < K && (reinterpret_cast<uintptr_t>(p + base + k) & 7) == 0) {
-    const ushort4 q = *reinterpret_cast<const ushort4*>(p + base + k);
-    r[0] = (short)q.x;
-    r[1] = (short)q.y;
-    r[2] = (short)q.z;
-    r[3] = (short)q.w;
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r[i] = (k + i < K) ? (short)p[base + (long)(k + i) * stride] : (short)0;
-  }
-  return r;
-}
-
-__global__ void __launch_bounds__(256) k_gemm_bf16(int M, int N, int K, const uint16_t* __restrict__ A, long sam,
-                                                   long sak, const uint16_t* __restrict__ B, long sbk, long sbn,
-                                                   float* __restrict__ Cm, long ldc, long split_stride, int kchunk) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int m0 = blockIdx.y * 64 + (w >> 1) * 32;
-  const int n0 = blockIdx.x * 64 + (w & 1) * 32;
-  const int r16 = lane & 15, kq = (lane >> 4) * 4;
-  const int kbeg = blockIdx.z * kchunk;
-  const int kend = min(K, kbeg + kchunk);
-  const bool va = (sak == 1), vb = (sbk == 1);
-  v4f acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = kbeg; k0 < kend; k0 += 16) {
-    v4s fa[2], fb[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int m = m0 + t * 16 + r16;
-      const int n = n0 + t * 16 + r16;
-      fa[t] = m < M ? load4(A, (long)m * sam, sak, k0 + kq, kend, va) : v4s{0, 0, 0, 0};
-      fb[t] = n < N ? load4(B, (long)n * sbn, sbk, k0 + kq, kend, vb) : v4s{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(fa[a], fb[b], acc[a][b], 0, 0, 0);
-  }
-  float* Cz = Cm + (long)blockIdx.z * split_stride;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int m = m0 + a * 16 + kq + i;
-        const int n = n0 + b * 16 + r16;
-        if (m < M && n < N) Cz[(long)m * ldc + n] = acc[a][b][i];
-      }
-}
-
-// out[m][n] = sum over splits z (in order) of part[z][m][n]
-__global__ void k_vet_sum_splits(const float* __restrict__ part, int splits, long count, int N, long ldc,
-                                 float* __restrict__ out) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= count) return;
-  const long m = idx / N, n = idx % N;
-  float acc = 0.f;
-  for (int z = 0; z < splits; ++z) acc += part[(long)z * count + idx];
-  out[m * ldc + n] = acc;
-}
-
-// Column sums in two fixed-order stages: block (j, chunk) sums its rows of column j.
-__global__ void __launch_bounds__(256) k_vet_colsum_part(const float* __restrict__ m, long rows, int cols,
-                                                         long rows_per_chunk, float* __restrict__ part) {
-  const int j = blockIdx.x, chunk = blockIdx.y;
-  const long r0 = (long)chunk * rows_per_chunk;
-  const long r1 = min(rows, r0 + rows_per_chunk);
-  float acc = 0.f;
-  for (long r = r0 + threadIdx.x; r < r1; r += 256) acc += m[r * cols + j];
-  __shared__ float red[256];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[(long)chunk * cols + j] = red[0];
-}
-
-// u = log(1 + 2F) - log 5 per patch bin (n * L threads)
 // Network input u = log(1 + 2F) - log 5, with the hardware logarithm (absolute error
 // about 1e-7, far below the BF16 rounding of the layers that follow).
 __device__ __forceinline__ float vet_u(float v) { return __logf(1.f + v) - 1.6094379124341003f; }
-
-__global__ void k_vet_input(const float* __restrict__ patches, long count, float* __restrict__ u) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < count) u[idx] = vet_u(patches[idx]);
-}
-
-// conv1 (one input channel): z1[n][p][c] = b1[c] + sum_t w1[c][t] u[n][p+t-3]; a1 = relu(z1)
-// as BF16 (n * L * C threads).
-__global__ void k_vet_conv1(const float* __restrict__ u, int n, const float* __restrict__ theta,
-                            float* __restrict__ z1, uint16_t* __restrict__ a1b) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;  // over n * L * C
-  if (idx >= (long)n * L * C) return;
-  const int c = idx % C;
-  const int p = (idx / C) % L;
-  const long s = idx / (C * L);
-  const float* us = u + s * L;
-  float z = theta[O_B1 + c];
-#pragma unroll
-  for (int t = 0; t < KW; ++t) {
-    const int q = p + t - 3;
-    if (q >= 0 && q < L) z += theta[O_W1 + c * KW + t] * us[q];
-  }
-  z1[idx] = z;
-  a1b[idx] = f2bf(z > 0.f ? z : 0.f);
-}
-
-// im2col of a position-major BF16 activation [n][L][C]:
-//   col[(s*L + p)][t*C + c] = act[s][p + dir*(t-3)][c]   (zero outside [0, L))
-// dir = +1 for a convolution, -1 for the transposed convolution of its input gradient.
-__global__ void k_vet_im2col(const uint16_t* __restrict__ act, int n, int dir, uint16_t* __restrict__ col) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;  // over n * L * KC
-  if (idx >= (long)n * L * KC) return;
-  const int kk = idx % KC;
-  const long row = idx / KC;
-  const int p = row % L;
-  const long s = row / L;
-  const int t = kk / C, c = kk % C;
-  const int q = p + dir * (t - 3);
-  col[idx] = (q >= 0 && q < L) ? act[(s * L + q) * C + c] : (uint16_t)0;
-}
-
-// z[r][j] += bias[j]; optional relu output as BF16; z kept for the backward masks.
-__global__ void k_vet_bias_relu(float* __restrict__ z, long rows, int cols, const float* __restrict__ bias,
-                                uint16_t* __restrict__ outb, float* __restrict__ outf) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= rows * cols) return;
-  const float v = z[idx] + bias[idx % cols];
-  z[idx] = v;
-  const float a = v > 0.f ? v : 0.f;
-  if (outb) outb[idx] = f2bf(a);
-  if (outf) outf[idx] = a;
-}
-
-// logit[s] = b6 + sum_j w6[j] a5[s][j]   (a5 = relu(z5), FP32)
-__global__ void k_vet_fc3(const float* __restrict__ a5, int n, const float* __restrict__ theta,
-                          float* __restrict__ logit) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  float v = theta[O_B6];
-  for (int j = 0; j < H; ++j) v += theta[O_W6 + j] * a5[(long)s * H + j];
-  logit[s] = v;
-}
-
-// Loss and the first backward step: dlogit = (sigmoid(logit) - y) / n; loss = mean BCE.
-// dz5[s][j] = dlogit[s] w6[j] (z5 > 0); also dW6, db6 partial sums per block.
-// Head backward over n * H threads: dlogit = (sigmoid(logit) - y) / n, its loss term, and
-// dz5[s][j] = dlogit w6[j] [z5 > 0] (FP32 and BF16).
-__global__ void k_vet_head_backward(const float* __restrict__ logit, const float* __restrict__ y, int n,
-                                    const float* __restrict__ theta, const float* __restrict__ z5,
-                                    float* __restrict__ dz5, uint16_t* __restrict__ dz5b,
-                                    float* __restrict__ dlogit, float* __restrict__ loss_terms) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long)n * H) return;
-  const int s = (int)(idx / H), j = (int)(idx % H);
-  const float l = logit[s];
-  const float sig = 1.f / (1.f + expf(-l));
-  const float d = (sig - y[s]) / (float)n;
-  if (j == 0) {
-    dlogit[s] = d;
-    loss_terms[s] = fmaxf(l, 0.f) - l * y[s] + log1pf(expf(-fabsf(l)));
-  }
-  const float g = z5[idx] > 0.f ? d * theta[O_W6 + j] : 0.f;
-  dz5[idx] = g;
-  dz5b[idx] = f2bf(g);
-}
-
-// dz = dh * (z > 0) in place, BF16 copy.
-__global__ void k_vet_relu_mask(float* __restrict__ dh, const float* __restrict__ z, long count,
-                                uint16_t* __restrict__ outb) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= count) return;
-  const float g = z[idx] > 0.f ? dh[idx] : 0.f;
-  dh[idx] = g;
-  outb[idx] = f2bf(g);
-}
-
-// out[j] = sum over chunks (in order) of part[chunk][j]
-__global__ void k_vet_colsum_final(const float* __restrict__ part, int chunks, int cols, float* __restrict__ out) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= cols) return;
-  float acc = 0.f;
-  for (int c = 0; c < chunks; ++c) acc += part[(long)c * cols + j];
-  out[j] = acc;
-}
-
-// dW6[j] = sum_s dlogit[s] a5[s][j], db6 = sum_s dlogit[s], loss = mean of the loss terms:
-// 1024 threads, eight interleaved partial sums per column added in a fixed order.
-__global__ void __launch_bounds__(1024) k_vet_head_reduce(const float* __restrict__ dlogit,
-                                                          const float* __restrict__ a5,
-                                                          const float* __restrict__ loss_terms, int n,
-                                                          float* __restrict__ grad, float* __restrict__ loss) {
-  constexpr int PARTS = 1024 / H;
-  __shared__ float red[PARTS][H + 2];
-  const int j = threadIdx.x % H, part = threadIdx.x / H;
-  float acc = 0.f, accd = 0.f, accl = 0.f;
-  for (int s = part; s < n; s += PARTS) {
-    const float d = dlogit[s];
-    acc += d * a5[(long)s * H + j];
-    if (j == 0) {
-      accd += d;
-      accl += loss_terms[s];
-    }
-  }
-  red[part][j] = acc;
-  if (j == 0) {
-    red[part][H] = accd;
-    red[part][H + 1] = accl;
-  }
-  __syncthreads();
-  const int t = threadIdx.x;
-  if (t < H + 2) {
-    float sum = 0.f;
-    for (int q = 0; q < PARTS; ++q) sum += red[q][t];
-    if (t < H) grad[O_W6 + t] = sum;
-    else if (t == H) grad[O_B6] = sum;
-    else if (loss) *loss = sum / (float)n;
-  }
-}
-
-// conv1 weight and bias gradients: dW1[c][t] = sum_{s,p} dz1[s][p][c] u[s][p+t-3]; db1[c].
-// Block b sums rows [b rows_per_chunk, ...) with thread (c = t % 32, k = t / 32): tap k < KW
-// or the bias (k = KW), writing part[b][c (KW + 1) + k]; k_vet_colsum_final adds the chunks
-// in order.
-__global__ void __launch_bounds__(256) k_vet_conv1_backward_part(const float* __restrict__ dz1,
-                                                                 const float* __restrict__ u, long rows,
-                                                                 long rows_per_chunk, float* __restrict__ part) {
-  const int c = threadIdx.x % C, k = threadIdx.x / C;
-  const long r0 = (long)blockIdx.x * rows_per_chunk;
-  const long r1 = min(rows, r0 + rows_per_chunk);
-  float acc = 0.f;
-  for (long r = r0; r < r1; ++r) {
-    const float g = dz1[r * C + c];
-    if (k == KW) {
-      acc += g;
-    } else {
-      const int p = r % L;
-      const int q = p + k - 3;
-      if (q >= 0 && q < L) acc += g * u[(r - p) + q];
-    }
-  }
-  part[(long)blockIdx.x * (C * (KW + 1)) + c * (KW + 1) + k] = acc;
-}
-
-// Move the conv1 sums (c * (KW + 1) + t order) into the flat gradient (weights c * KW + t, biases c).
-__global__ void k_vet_conv1_scatter(const float* __restrict__ sums, float* __restrict__ grad) {
-  const int ct = threadIdx.x;
-  if (ct >= C * (KW + 1)) return;
-  const int c = ct / (KW + 1), t = ct % (KW + 1);
-  if (t == KW) grad[O_B1 + c] = sums[ct];
-  else grad[O_W1 + c * KW + t] = sums[ct];
-}
-
-// BF16 weight layouts for the matrix products, from the FP32 master vector:
-//   wf[l][t*C + ci][co] = w_l[co][ci][t]   (forward convolution, [KC][C])
-//   wt[l][t*C + co][ci] = w_l[co][ci][t]   (input-gradient convolution, [KC][C])
-//   w4b[j][k] = w4[j][k], w5b[j][k] = w5[j][k]
-__global__ void k_vet_prepare(const float* __restrict__ theta, uint16_t* __restrict__ wf2,
-                              uint16_t* __restrict__ wt2, uint16_t* __restrict__ wf3, uint16_t* __restrict__ wt3,
-                              uint16_t* __restrict__ w4b, uint16_t* __restrict__ w5b) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < (long)H * X) w4b[idx] = f2bf(theta[O_W4 + idx]);
-  if (idx < H * H) w5b[idx] = f2bf(theta[O_W5 + idx]);
-  if (idx < C * C * KW) {
-    const int co = idx / (C * KW), ci = (idx / KW) % C, t = idx % KW;
-    wf2[(t * C + ci) * C + co] = f2bf(theta[O_W2 + idx]);
-    wt2[(t * C + co) * C + ci] = f2bf(theta[O_W2 + idx]);
-    wf3[(t * C + ci) * C + co] = f2bf(theta[O_W3 + idx]);
-    wt3[(t * C + co) * C + ci] = f2bf(theta[O_W3 + idx]);
-  }
-}
-
-// Gradient of a convolution weight from its matrix-product form dWm[t*C + ci][co]
-// back to the flat layout w[co][ci][t].
-__global__ void k_vet_scatter_conv_grad(const float* __restrict__ dwm, float* __restrict__ gw) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= C * C * KW) return;
-  const int co = idx / (C * KW), ci = (idx / KW) % C, t = idx % KW;
-  gw[idx] = dwm[(t * C + ci) * C + co];
-}
-
-// Adam on the FP32 master vector (bias-corrected step size precomputed on the host).
-__global__ void k_vet_adam(float* __restrict__ theta, const float* __restrict__ g, float* __restrict__ m1,
-                           float* __restrict__ m2, long count, float step, float b1, float b2, float eps) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const float gi = g[i];
-  const float a = b1 * m1[i] + (1.f - b1) * gi;
-  const float b = b2 * m2[i] + (1.f - b2) * gi * gi;
-  m1[i] = a;
-  m2[i] = b;
-  theta[i] -= step * a / (sqrtf(b) + eps);
-}
 
 // Patch capture after the F kernel: for candidate slots [first, last) of the current
 // launch, copy the 256-bin 2F window centred on the candidate's bin from the launch's
@@ -404,16 +97,6 @@ constexpr int KS = KC / 32;             // matrix-core K steps of a convolution 
 // Convolution weights in matrix-core fragment order: [step s][column block nb][lane][8],
 // element j of lane l = w[co = 16 nb + l % 16][ci = 8 (l / 16) + j][t = s].
 constexpr int WQ_ELEMS = KS * 2 * 64 * 8;
-
-__global__ void k_vet_prepare_frag(const float* __restrict__ theta, uint16_t* __restrict__ wq2,
-                                   uint16_t* __restrict__ wq3) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= WQ_ELEMS) return;
-  const int j = idx & 7, l = (idx >> 3) & 63, nb = (idx >> 9) & 1, t = idx >> 10;
-  const int ci = 8 * (l >> 4) + j, co = 16 * nb + (l & 15);
-  wq2[idx] = f2bf(theta[O_W2 + (co * C + ci) * KW + t]);
-  wq3[idx] = f2bf(theta[O_W3 + (co * C + ci) * KW + t]);
-}
 
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v2f __attribute__((ext_vector_type(2)));
