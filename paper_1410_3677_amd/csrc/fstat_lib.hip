@@ -114,7 +114,7 @@ struct fstat_vet_s {
   // training activations and gradients of a batch: input u, BF16 activations of the three
   // convolutions and of the first dense layer, BF16 dz5, dz4, dz3, dz2; FP32 values and parts
   // of the sums over patches; logits
-  float *u, *logit, *loss, *dz2, *sums3, *bsum, *part1, *convp;
+  float *u, *logit, *loss, *dz2, *sums2, *sums3, *part1, *convp;
   vet::HeadOut head;
   uint16_t *a1b, *a2b, *a3b, *a4b, *dz5b, *dz4b, *dz3b, *dz2b;
   float* scratch = nullptr;      // split-K partial tiles, convolution gradient partials
@@ -1279,9 +1279,10 @@ static fstat_status vet_score_all(fstat_vet_t v, const float* patches, long long
 }
 
 // Gradient of the mean loss of n <= max_batch patches into v->grad, loss into v->loss
-// (fstat_vet_train.hpp).
+// (fstat_vet_train.hpp), and into grad_out and loss_out if not null.
 constexpr int TRAIN_CONV_PARTS = 256;   // parts at most of the convolutions' weight gradients
-void vet_gradient(fstat_vet_t v, const float* patches, const float* labels, int n, hipStream_t st) {
+void vet_gradient(fstat_vet_t v, const float* patches, const float* labels, int n, float* loss_out, float* grad_out,
+                  hipStream_t st) {
   using namespace vet;
   FSTAT_LAUNCH(k_train_conv_fwd, dim3(n), dim3(256), 0, st, patches, v->theta, v->wc.f2, v->wc.f3, v->u, v->a1b, v->a2b,
                v->a3b);
@@ -1292,7 +1293,7 @@ void vet_gradient(fstat_vet_t v, const float* patches, const float* labels, int 
   while (splits < 32 && tiles * splits < 256) splits <<= 1;
   FSTAT_LAUNCH(k_gemm_nt_lds, dim3(H / GT, nbp / GT, splits), dim3(256), 0, st, nbp, H, X, v->a3b, v->wc.w4b, v->scratch,
                X / splits);
-  FSTAT_LAUNCH(k_train_head, dim3((n + HP - 1) / HP), dim3(256), 0, st, v->scratch, splits, (long)nbp * H, n, v->theta,
+  FSTAT_LAUNCH(k_train_head, dim3((n + HP - 1) / HP), dim3(HEAD_NT), 0, st, v->scratch, splits, (long)nbp * H, n, v->theta,
                v->wc.w5b, labels, v->a4b, v->dz5b, v->dz4b, v->head);
   // sums over many rows are split into parts of 1024 rows or more: dW5 from 4096 patches on
   // (into the scratch, whose partial tiles the head has read), the convolutions' from 16
@@ -1300,17 +1301,17 @@ void vet_gradient(fstat_vet_t v, const float* patches, const float* labels, int 
   auto rows_per = [](long rows, int p) { return (int)((rows + p - 1) / p + 15) / 16 * 16; };
   const long NL = (long)n * L;
   const int split5 = parts(n, TRAIN_CONV_PARTS), conv = parts(NL, TRAIN_CONV_PARTS);
-  FSTAT_LAUNCH(k_train_dw_dense, dim3(DW_TILES + H / 64 * split5), dim3(256), 0, st, v->dz4b, v->a3b, v->dz5b, v->a4b, n,
-               split5, rows_per(n, split5), v->grad, v->scratch);
-  FSTAT_LAUNCH(k_train_dx, dim3(DW_TILES, (n + 63) / 64), dim3(256), 0, st, v->dz4b, v->wc.w4b, v->a3b, n, v->dz3b,
+  const int ndw = DW_TILES + H / 64 * split5;
+  DwDense dw{v->dz4b, v->a3b, v->dz5b, v->a4b, n, split5, rows_per(n, split5), v->grad, grad_out, v->scratch};
+  FSTAT_LAUNCH(k_train_dense_bwd, dim3(ndw + DW_TILES * ((n + 63) / 64)), dim3(256), 0, st, dw, ndw, v->wc.w4b, v->dz3b,
                v->sums3);
   FSTAT_LAUNCH(k_train_conv_bwd, dim3(n), dim3(256), 0, st, v->u, v->a1b, v->a2b, v->dz3b, v->wc.g3, v->wc.g2, v->dz2b,
                v->dz2, v->part1);
-  FSTAT_LAUNCH(k_train_dw_conv, dim3(4 * conv + 4 * ((n + 15) / 16)), dim3(256), 0, st, v->a1b, v->a2b, v->dz2b, v->dz3b,
-               v->dz2, v->sums3, n, conv, rows_per(NL, conv), v->convp, v->bsum);
-  ReduceArgs ra{v->convp, v->part1, v->bsum, v->scratch, v->head, n, conv, split5};
+  FSTAT_LAUNCH(k_train_dw_conv, dim3(4 * conv + 8 * ((n + 15) / 16)), dim3(256), 0, st, v->a1b, v->a2b, v->dz2b, v->dz3b,
+               v->dz2, n, conv, rows_per(NL, conv), v->convp, v->sums2);
+  ReduceArgs ra{v->convp, v->part1, v->sums2, v->sums3, v->scratch, v->head, n, conv, split5};
   FSTAT_LAUNCH(k_train_reduce, dim3(RD_DB + RD_W6 + RD_BIAS + RD_P1 + RD_CONV + (split5 > 1 ? RD_W5 : 0)), dim3(256), 0,
-               st, ra, v->grad, v->loss);
+               st, ra, v->grad, grad_out, v->loss, loss_out);
 }
 static_assert((long)TRAIN_CONV_PARTS * vet::H * vet::H <= VET_SCRATCH, "parts of dW5 fit the scratch");
 }  // namespace
@@ -1344,7 +1345,7 @@ fstat_status fstat_vet_create(int32_t max_batch, fstat_vet_t* out) {
       {(void**)&v->wc.f3, TF_ELEMS * 2}, {(void**)&v->wc.g2, TF_ELEMS * 2}, {(void**)&v->wc.g3, TF_ELEMS * 2},
       {(void**)&v->u, NL * 4}, {(void**)&v->logit, nb * 4}, {(void**)&v->loss, 4},
       {(void**)&v->dz2, NL * C * 4}, {(void**)&v->sums3, (nb + 15) / 16 * X * 4},
-      {(void**)&v->bsum, (nb + 15) / 16 * 2 * C * 4}, {(void**)&v->part1, nb * P1 * 4},
+      {(void**)&v->sums2, (nb + 15) / 16 * X * 4}, {(void**)&v->part1, nb * P1 * 4},
       {(void**)&v->convp, (size_t)2 * TRAIN_CONV_PARTS * CP_W * 4}, {(void**)&v->head.a5, nb * H * 4},
       {(void**)&v->head.dz5, nb * H * 4}, {(void**)&v->head.dz4, nb * H * 4}, {(void**)&v->head.dlogit, nb * 4},
       {(void**)&v->head.term, nb * 4}, {(void**)&v->scratch, (size_t)VET_SCRATCH * 4},
@@ -1397,14 +1398,28 @@ fstat_status fstat_vet_forward(fstat_vet_t v, const float* patches, int64_t n, f
   return vet_score_all(v, patches, n, st, [&](long long i) { return logits + i; }, (CandEntry*)nullptr);
 }
 
+// is p memory of the current device (not managed, not host, not a peer's)?
+static bool on_this_device(const void* p) {
+  hipPointerAttribute_t a{};
+  int dev = -1;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == dev;
+}
+
 fstat_status fstat_vet_gradient(fstat_vet_t v, const float* patches, const float* labels, int64_t n, float* loss,
                                 float* grad, void* stream) {
   if (!v || !patches || !labels || n < 1 || n > v->max_batch) return vet_fail(v, FSTAT_E_INVAL, "bad arguments");
   hipStream_t st = (hipStream_t)stream;
-  vet_gradient(v, patches, labels, (int)n, st);
+  // results in this device's memory are stored by the kernels; two copies behind them took
+  // 9 us of a step of 115.  Anywhere else (another device, host) they are copied.
+  const bool l = loss && on_this_device(loss), g = grad && on_this_device(grad);
+  vet_gradient(v, patches, labels, (int)n, l ? loss : nullptr, g ? grad : nullptr, st);
   VET_TRY(v, launch_status(), "gradient launch");
-  if (loss) VET_TRY(v, hipMemcpyAsync(loss, v->loss, 4, hipMemcpyDeviceToDevice, st), "loss copy");
-  if (grad) VET_TRY(v, hipMemcpyAsync(grad, v->grad, vet::N_PARAMS * 4, hipMemcpyDeviceToDevice, st), "grad copy");
+  if (loss && !l) VET_TRY(v, hipMemcpyAsync(loss, v->loss, 4, hipMemcpyDeviceToDevice, st), "loss copy");
+  if (grad && !g) VET_TRY(v, hipMemcpyAsync(grad, v->grad, vet::N_PARAMS * 4, hipMemcpyDeviceToDevice, st), "grad copy");
   return FSTAT_OK;
 }
 

@@ -8,10 +8,9 @@
 //   k_train_conv_fwd   input, three convolutions -> BF16 activations a1, a2, x = a3
 //   k_gemm_nt_lds      z4 = x W4^T, split along K (fstat_vet.hpp)
 //   k_train_head       z4 -> a4 -> z5 -> logit, loss terms; back to dz5, dz4
-//   k_train_dw_dense   dW4 = dz4^T x and dW5 = dz5^T a4
-//   k_train_dx         dz3 = (dz4 W4) [a3 > 0]
+//   k_train_dense_bwd  dW4 = dz4^T x and dW5 = dz5^T a4; dz3 = (dz4 W4) [a3 > 0]
 //   k_train_conv_bwd   per patch: dz2, dz1; its share of dW1, db1
-//   k_train_dw_conv    dW3 and dW2 in parts of the positions; db3, db2 per 16 patches
+//   k_train_dw_conv    dW3 and dW2 in parts of the positions
 //   k_train_reduce     the parts and the head's columns added up
 //   k_vet_update       Adam and the BF16 copies of the weights
 //
@@ -20,8 +19,9 @@
 // positions.  It is the order of the im2col products and serial column sums that these
 // kernels replace, bit for bit: Adam's first steps turn the last bit of a gradient into
 // activations that round the other way.
-// 55 launches that moved 900 MB took 740 us at 256 patches; the weights, activations and
-// gradients alone are 60 MB.
+// 256 patches: 740 us with 55 launches, which moved about 600 MB (half of it im2col matrices);
+// 84 us here, with about 120 MB in eight launches.  Now bound by latency: one workgroup per
+// CU or fewer in each launch, 5 to 17 us each.
 #pragma once
 
 #include "fstat_vet.hpp"
@@ -59,28 +59,39 @@ __device__ __forceinline__ v8s read_tr32(const uint16_t* base, int ld, int k0, i
   return v8s{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 }
 
+// A lane's fragments of a convolution's weights, in registers: read before the tiles are ready,
+// as at one wavefront per SIMD nothing else hides their way from L2.
+struct ConvWeights {
+  v4s w[KW * 2][2];
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ frag, int lane) {
+    const v4s* f = reinterpret_cast<const v4s*>(frag) + lane;
+#pragma unroll
+    for (int e = 0; e < KW * 2; ++e) {
+      w[e][0] = f[(2 * e) * 64];
+      w[e][1] = f[(2 * e + 1) * 64];
+    }
+  }
+};
+
 // One wavefront's share of a convolution from the tile `in` (position p at row p + 3): sums
 // over taps t and channels of w times the row r0 + step t, for its 64 positions r0 ..
 // r0 + 63 (rows) and all 32 outer channels.  acc[m][nb]: lane l holds outer channels
 // 16 nb + 4 (l / 16) + i of position 16 m + l % 16.
-__device__ __forceinline__ void conv_rows(const uint16_t* in, const uint16_t* __restrict__ frag, int r0, int step,
-                                          int lane, v4f (&acc)[4][2]) {
+__device__ __forceinline__ void conv_rows(const uint16_t* in, const ConvWeights& cw, int r0, int step, int lane,
+                                          v4f (&acc)[4][2]) {
 #pragma unroll
   for (int m = 0; m < 4; ++m) acc[m][0] = acc[m][1] = v4f{0.f, 0.f, 0.f, 0.f};
-  const v4s* wf = reinterpret_cast<const v4s*>(frag) + lane;
 #pragma unroll
   for (int t = 0; t < KW; ++t)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const v4s w0 = wf[((t * 2 + h) * 2) * 64], w1 = wf[((t * 2 + h) * 2 + 1) * 64];
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
         const v4s x = *reinterpret_cast<const v4s*>(in + (r0 + 16 * m + (lane & 15) + step * t) * TR_LD + 16 * h +
                                                     4 * (lane >> 4));
-        acc[m][0] = mfma16(w0, x, acc[m][0]);
-        acc[m][1] = mfma16(w1, x, acc[m][1]);
+        acc[m][0] = mfma16(cw.w[2 * t + h][0], x, acc[m][0]);
+        acc[m][1] = mfma16(cw.w[2 * t + h][1], x, acc[m][1]);
       }
-    }
 }
 
 __device__ __forceinline__ void zero_halo(uint16_t* buf, int tid) {
@@ -106,6 +117,9 @@ __global__ void __launch_bounds__(256) k_train_conv_fwd(const float* __restrict_
   __shared__ float su[L + 6];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const long s = blockIdx.x;
+  ConvWeights w2, w3;
+  w2.load(f2, lane);
+  w3.load(f3, lane);
   const float uv = vet_u(patches[s * L + tid]);
   u[s * L + tid] = uv;
   su[3 + tid] = uv;
@@ -135,9 +149,9 @@ __global__ void __launch_bounds__(256) k_train_conv_fwd(const float* __restrict_
     }
   }
   __syncthreads();
-  auto layer = [&](const uint16_t* in, const uint16_t* frag, long bias, uint16_t* keep, uint16_t* out) {
+  auto layer = [&](const uint16_t* in, const ConvWeights& cw, long bias, uint16_t* keep, uint16_t* out) {
     v4f acc[4][2];
-    conv_rows(in, frag, 64 * w, 1, lane, acc);
+    conv_rows(in, cw, 64 * w, 1, lane, acc);
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
       const int c = 16 * nb + 4 * (lane >> 4);
@@ -151,9 +165,9 @@ __global__ void __launch_bounds__(256) k_train_conv_fwd(const float* __restrict_
       }
     }
   };
-  layer(b1, f2, O_B2, b2, a2);
+  layer(b1, w2, O_B2, b2, a2);
   __syncthreads();
-  layer(b2, f3, O_B3, nullptr, a3);
+  layer(b2, w3, O_B3, nullptr, a3);
 }
 
 // ---- dense head
@@ -165,21 +179,49 @@ constexpr int HP = 16, HA_LD = H + 4;
 struct HeadOut {
   float *a5, *dz5, *dz4, *dlogit, *term;
 };
-__global__ void __launch_bounds__(256) k_train_head(const float* __restrict__ z4p, int splits, long count, int n,
-                                                    const float* __restrict__ theta,
-                                                    const uint16_t* __restrict__ w5b, const float* __restrict__ y,
-                                                    uint16_t* __restrict__ a4b, uint16_t* __restrict__ dz5b,
-                                                    uint16_t* __restrict__ dz4b, HeadOut out) {
+// 1024 threads for the 32 partial sums of each z4 value: at 256 patches there are only 16
+// workgroups, and what a CU has in flight bounds them.  The products take the first eight
+// wavefronts, 16 outputs each, with their parts of W5 read ahead.
+constexpr int HEAD_NT = 1024;
+__global__ void __launch_bounds__(HEAD_NT) k_train_head(const float* __restrict__ z4p, int splits, long count, int n,
+                                                        const float* __restrict__ theta,
+                                                        const uint16_t* __restrict__ w5b, const float* __restrict__ y,
+                                                        uint16_t* __restrict__ a4b, uint16_t* __restrict__ dz5b,
+                                                        uint16_t* __restrict__ dz4b, HeadOut out) {
   __shared__ __align__(16) uint16_t sa4[HP * HA_LD], sd5[HP * HA_LD];
-  __shared__ float sa5[HP][H + 1], sd[HP];
+  __shared__ float sa5[HP][H + 1], sd[HP], s6[H];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int r0 = blockIdx.x * HP;
-  for (int i = tid; i < HP * H; i += 256) {
-    const int p = i / H, k = i % H, row = r0 + p;
+  const int q4 = 4 * (lane >> 4), r16 = lane & 15, o = 16 * w + r16;
+  const bool prod = w < H / 16;
+  v4s wf[H / 16], wb[H / 16];
+  float b5 = 0.f, w6 = 0.f;
+  if (prod) {
+#pragma unroll
+    for (int k = 0; k < H / 16; ++k) {
+      wf[k] = *reinterpret_cast<const v4s*>(w5b + (long)o * H + 16 * k + q4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) wb[k][i] = (short)w5b[(16 * k + q4 + i) * H + o];
+    }
+    b5 = theta[O_B5 + o];
+    w6 = theta[O_W6 + o];
+    if (lane < 16) s6[o] = w6;
+  }
+#pragma unroll
+  for (int e = 0; e < HP * H / HEAD_NT; ++e) {
+    const int i = tid + HEAD_NT * e, p = i / H, k = i % H, row = r0 + p;
     float acc = 0.f;
     if (row < n) {
-#pragma unroll 8
-      for (int z = 0; z < splits; ++z) acc += z4p[(long)z * count + (long)row * H + k];
+      const float* z = z4p + (long)row * H + k;
+      if (splits == 32) {
+        float v[32];
+#pragma unroll
+        for (int q = 0; q < 32; ++q) v[q] = z[q * count];
+#pragma unroll
+        for (int q = 0; q < 32; ++q) acc += v[q];
+      } else {
+        for (int q = 0; q < splits; ++q) acc += z[q * count];
+      }
       acc += theta[O_B4 + k];
     }
     const uint16_t a = f2bf(acc > 0.f ? acc : 0.f);
@@ -187,22 +229,16 @@ __global__ void __launch_bounds__(256) k_train_head(const float* __restrict__ z4
     if (row < n) a4b[(long)row * H + k] = a;
   }
   __syncthreads();
-  // z5: patches 4 (l / 16) + i, outputs 32 w + 16 b + l % 16
-  const int q4 = 4 * (lane >> 4), r16 = lane & 15;
-  v4f z5[2];
+  // z5: patches 4 (l / 16) + i, outputs 16 w + l % 16
+  v4f z5 = {0.f, 0.f, 0.f, 0.f};
+  if (prod) {
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    v4f acc = {0.f, 0.f, 0.f, 0.f};
-    const int o = 32 * w + 16 * b + r16;
-#pragma unroll
-    for (int k0 = 0; k0 < H; k0 += 16)
-      acc = mfma16(*reinterpret_cast<const v4s*>(sa4 + r16 * HA_LD + k0 + q4),
-                   *reinterpret_cast<const v4s*>(w5b + (long)o * H + k0 + q4), acc);
-    const float b5 = theta[O_B5 + o];
+    for (int k = 0; k < H / 16; ++k)
+      z5 = mfma16(*reinterpret_cast<const v4s*>(sa4 + r16 * HA_LD + 16 * k + q4), wf[k], z5);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      z5[b][i] = acc[i] + b5;
-      const float a = z5[b][i] > 0.f ? z5[b][i] : 0.f;
+      z5[i] += b5;
+      const float a = z5[i] > 0.f ? z5[i] : 0.f;
       sa5[q4 + i][o] = a;
       if (r0 + q4 + i < n) out.a5[(long)(r0 + q4 + i) * H + o] = a;
     }
@@ -210,7 +246,8 @@ __global__ void __launch_bounds__(256) k_train_head(const float* __restrict__ z4
   __syncthreads();
   if (tid < HP) {
     float l = theta[O_B6], d = 0.f;
-    for (int j = 0; j < H; ++j) l += theta[O_W6 + j] * sa5[tid][j];
+#pragma unroll 16
+    for (int j = 0; j < H; ++j) l += s6[j] * sa5[tid][j];
     if (r0 + tid < n) {
       const float yy = y[r0 + tid], sig = 1.f / (1.f + expf(-l));
       d = (sig - yy) / (float)n;
@@ -220,14 +257,11 @@ __global__ void __launch_bounds__(256) k_train_head(const float* __restrict__ z4
     sd[tid] = d;
   }
   __syncthreads();
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    const int o = 32 * w + 16 * b + r16;
-    const float w6 = theta[O_W6 + o];
+  if (prod) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int p = q4 + i;
-      const float g = z5[b][i] > 0.f ? sd[p] * w6 : 0.f;
+      const float g = z5[i] > 0.f ? sd[p] * w6 : 0.f;
       const uint16_t gb = f2bf(g);
       sd5[p * HA_LD + o] = gb;
       if (r0 + p < n) {
@@ -237,50 +271,47 @@ __global__ void __launch_bounds__(256) k_train_head(const float* __restrict__ z4
     }
   }
   __syncthreads();
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    const int k = 32 * w + 16 * b + r16;
+  if (prod) {
     v4f acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j0 = 0; j0 < H; j0 += 16) {
-      v4s wv;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) wv[i] = (short)w5b[(j0 + q4 + i) * H + k];
-      acc = mfma16(*reinterpret_cast<const v4s*>(sd5 + r16 * HA_LD + j0 + q4), wv, acc);
-    }
+    for (int k = 0; k < H / 16; ++k)
+      acc = mfma16(*reinterpret_cast<const v4s*>(sd5 + r16 * HA_LD + 16 * k + q4), wb[k], acc);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int p = q4 + i;
-      const float g = (short)sa4[p * HA_LD + k] > 0 ? acc[i] : 0.f;
+      const float g = (short)sa4[p * HA_LD + o] > 0 ? acc[i] : 0.f;
       if (r0 + p < n) {
-        dz4b[(long)(r0 + p) * H + k] = f2bf(g);
-        out.dz4[(long)(r0 + p) * H + k] = g;
+        dz4b[(long)(r0 + p) * H + o] = f2bf(g);
+        out.dz4[(long)(r0 + p) * H + o] = g;
       }
     }
   }
 }
 
-// ---- dense weight gradients
-// dW[j][c] = sum_s a[s][j] x[s][c] over n patches: 128 x 64 of dW4 (a = dz4, x of 8192 columns)
+// ---- dense layers, backward
+// Weight gradients: dW[j][c] = sum_s a[s][j] x[s][c] over n patches: 128 x 64 of dW4 (a = dz4, x of 8192 columns)
 // per workgroup, then dW5 (a = dz5, x = a4) in `split5` parts of `chunk5` patches, to `part5`
 // if there is more than one.  Stages of 32 patches in LDS
 // as they lie in memory; both operands by transposing reads.
 constexpr int DW_ALD = H + 8, DW_XLD = 64 + 8, DW_TILES = X / 64;
-__global__ void __launch_bounds__(256) k_train_dw_dense(const uint16_t* __restrict__ dz4b,
-                                                        const uint16_t* __restrict__ x,
-                                                        const uint16_t* __restrict__ dz5b,
-                                                        const uint16_t* __restrict__ a4b, int n, int split5,
-                                                        int chunk5, float* __restrict__ grad,
-                                                        float* __restrict__ part5) {
-  __shared__ __align__(16) uint16_t sa[32 * DW_ALD], sx[32 * DW_XLD];
+struct DwDense {
+  const uint16_t *dz4b, *x, *dz5b, *a4b;
+  int n, split5, chunk5;
+  float *grad, *grad_out, *part5;   // grad_out: the caller's copy, or null
+};
+__device__ __forceinline__ void dense_weights(const DwDense& d, int block, uint16_t* lds) {
+  uint16_t *sa = lds, *sx = lds + 32 * DW_ALD;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const bool last = blockIdx.x >= DW_TILES;
-  const uint16_t* a = last ? dz5b : dz4b;
-  const uint16_t* xs = last ? a4b : x;
-  const int tile = last ? (blockIdx.x - DW_TILES) & 1 : blockIdx.x, z = last ? (blockIdx.x - DW_TILES) >> 1 : 0;
+  const bool last = block >= DW_TILES;
+  const uint16_t* a = last ? d.dz5b : d.dz4b;
+  const uint16_t* xs = last ? d.a4b : d.x;
+  const int tile = last ? (block - DW_TILES) & 1 : block, z = last ? (block - DW_TILES) >> 1 : 0;
   const int cols = last ? H : X, c0 = tile * 64;
-  const int beg = last ? z * chunk5 : 0, end = last ? min(n, beg + chunk5) : n;
-  float* out = !last ? grad + O_W4 : split5 > 1 ? part5 + (long)z * H * H : grad + O_W5;
+  const int beg = last ? z * d.chunk5 : 0, end = last ? min(d.n, beg + d.chunk5) : d.n;
+  const long base = last ? O_W5 : O_W4;
+  const bool parts = last && d.split5 > 1;
+  float* out = parts ? d.part5 + (long)z * H * H : d.grad + base;
+  float* copy = parts || !d.grad_out ? nullptr : d.grad_out + base;
   uint4 ra[2], rx;
   // a: rows of 16 16-byte groups, two per thread; x: rows of 8, one per thread
   auto gload = [&](int s0) {
@@ -325,22 +356,33 @@ __global__ void __launch_bounds__(256) k_train_dw_dense(const uint16_t* __restri
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        out[(long)(32 * w + 16 * i + 4 * (lane >> 4) + k) * cols + c0 + 16 * j + (lane & 15)] = acc[i][j][k];
+      for (int k = 0; k < 4; ++k) {
+        const long e = (long)(32 * w + 16 * i + 4 * (lane >> 4) + k) * cols + c0 + 16 * j + (lane & 15);
+        out[e] = acc[i][j][k];
+        if (copy) copy[e] = acc[i][j][k];
+      }
 }
 
-// ---- gradient of the flattened activations
-// dz3[s][c] = (sum_j dz4[s][j] W4[j][c]) [a3 > 0] for 64 patches and 64 columns (two
+// Gradient of the flattened activations: dz3[s][c] = (sum_j dz4[s][j] W4[j][c]) [a3 > 0] for 64 patches and 64 columns (two
 // positions), products transposed (lane: four columns of one patch); sums over each 16 patches
 // to sums[s / 16][c] for the bias gradient.
 constexpr int DX_LD = 64 + 8, DX_FLD = 64 + 4;
-__global__ void __launch_bounds__(256) k_train_dx(const uint16_t* __restrict__ dz4b, const uint16_t* __restrict__ w4b,
-                                                  const uint16_t* __restrict__ a3, int n, uint16_t* __restrict__ dz3,
-                                                  float* __restrict__ sums) {
-  __shared__ __align__(16) uint16_t sw[H * DX_LD];
-  __shared__ __align__(16) float sf[4][16 * DX_FLD];
+constexpr int DENSE_LDS = H * DX_LD * 2 + 64 * DX_FLD * 4;
+static_assert((32 * DW_ALD + 32 * DW_XLD) * 2 <= DENSE_LDS, "both uses fit");
+// The weight gradients' workgroups come first: theirs is the longer chain.
+__global__ void __launch_bounds__(256) k_train_dense_bwd(DwDense dw, int ndw, const uint16_t* __restrict__ w4b,
+                                                         uint16_t* __restrict__ dz3, float* __restrict__ sums) {
+  __shared__ __align__(16) unsigned char lds[DENSE_LDS];
+  if ((int)blockIdx.x < ndw) {
+    dense_weights(dw, blockIdx.x, reinterpret_cast<uint16_t*>(lds));
+    return;
+  }
+  const uint16_t *dz4b = dw.dz4b, *a3 = dw.x;
+  const int n = dw.n, tile = (blockIdx.x - ndw) % DW_TILES, rows = (blockIdx.x - ndw) / DW_TILES;
+  uint16_t* sw = reinterpret_cast<uint16_t*>(lds);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int c0 = blockIdx.x * 64, s = blockIdx.y * 64 + 16 * w + (lane & 15);
+  float* sf = reinterpret_cast<float*>(lds + H * DX_LD * 2) + w * 16 * DX_FLD;
+  const int c0 = tile * 64, s = rows * 64 + 16 * w + (lane & 15);
   for (int e = tid; e < H * 8; e += 256)
     *reinterpret_cast<uint4*>(sw + (e >> 3) * DX_LD + 8 * (e & 7)) =
         *reinterpret_cast<const uint4*>(w4b + (long)(e >> 3) * X + c0 + 8 * (e & 7));
@@ -366,14 +408,14 @@ __global__ void __launch_bounds__(256) k_train_dx(const uint16_t* __restrict__ d
       for (int i = 0; i < 4; ++i) d[i] = a[i] > 0 ? acc[i] : 0.f;
       *reinterpret_cast<uint2*>(dz3 + (long)s * X + c) = make_uint2(bf16_pair(d[0], d[1]), bf16_pair(d[2], d[3]));
     }
-    *reinterpret_cast<v4f*>(&sf[w][(lane & 15) * DX_FLD + 16 * b + 4 * (lane >> 4)]) = d;
+    *reinterpret_cast<v4f*>(&sf[(lane & 15) * DX_FLD + 16 * b + 4 * (lane >> 4)]) = d;
   }
   __syncthreads();
-  if (blockIdx.y * 64 + 16 * w < n) {
+  if (rows * 64 + 16 * w < n) {
     float v = 0.f;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v += sf[w][k * DX_FLD + lane];
-    sums[(long)(blockIdx.y * 4 + w) * X + c0 + lane] = v;
+    for (int k = 0; k < 16; ++k) v += sf[k * DX_FLD + lane];
+    sums[(long)(rows * 4 + w) * X + c0 + lane] = v;
   }
 }
 
@@ -395,6 +437,9 @@ __global__ void __launch_bounds__(256) k_train_conv_bwd(const float* __restrict_
   float* g1 = reinterpret_cast<float*>(tiles);   // dz1[c][position], once the tiles are done with
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r16 = lane & 15;
   const long s = blockIdx.x;
+  ConvWeights w3, w2;
+  w3.load(g3, lane);
+  w2.load(g2, lane);
   load_rows(bd, dz3 + s * X, tid);
   zero_halo(bd, tid);
   zero_halo(be, tid);
@@ -413,7 +458,7 @@ __global__ void __launch_bounds__(256) k_train_conv_bwd(const float* __restrict_
   __syncthreads();
   v4f acc[4][2];
   // da2[p] takes dz3[p - (t - 3)]: row p + 6 - t
-  conv_rows(bd, g3, 64 * w + 6, -1, lane, acc);
+  conv_rows(bd, w3, 64 * w + 6, -1, lane, acc);
 #pragma unroll
   for (int m = 0; m < 4; ++m)
 #pragma unroll
@@ -427,7 +472,7 @@ __global__ void __launch_bounds__(256) k_train_conv_bwd(const float* __restrict_
       *reinterpret_cast<v4f*>(dz2 + at(m, nb)) = d;
     }
   __syncthreads();
-  conv_rows(be, g2, 64 * w + 6, -1, lane, acc);
+  conv_rows(be, w2, 64 * w + 6, -1, lane, acc);
   __syncthreads();   // the tiles have been read
 #pragma unroll
   for (int m = 0; m < 4; ++m)
@@ -453,40 +498,30 @@ __global__ void __launch_bounds__(256) k_train_conv_bwd(const float* __restrict_
 // of 16) of the batch: workgroup (part, layer, taps 0..3 or 4..6), wavefront (half of ci, half
 // of co), to part[layer][part][t 32 + ci][co].  Both operands are read transposed from
 // patches staged as they lie in memory, the next patch's loads in flight meanwhile.
-// The workgroups behind those add the bias gradients' columns per 16 patches: layer 3 from
-// sums[chunk][p][c], layer 2 from its FP32 values, patch after patch; then a tree over the
-// positions (pairs 128 apart, 64, ..): bsum[layer][chunk][c].
+// The workgroups behind those add layer 2's bias gradient over each 16 patches, patch after
+// patch, as k_train_dense_bwd did layer 3's: sums2[chunk][p][c].
 constexpr int CP_W = KC * C;
-__device__ __forceinline__ v4f tree64(v4f v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] += __shfl_down(v[i], o, 64);
-  return v;
-}
 __global__ void __launch_bounds__(256) k_train_dw_conv(const uint16_t* __restrict__ a1, const uint16_t* __restrict__ a2,
                                                        const uint16_t* __restrict__ dz2b,
                                                        const uint16_t* __restrict__ dz3b,
-                                                       const float* __restrict__ dz2, const float* __restrict__ sums3,
-                                                       int n, int splits, int kchunk, float* __restrict__ part,
-                                                       float* __restrict__ bsum) {
+                                                       const float* __restrict__ dz2, int n, int splits,
+                                                       int kchunk, float* __restrict__ part,
+                                                       float* __restrict__ sums2) {
   __shared__ __align__(16) uint16_t ba[TR_ROWS * TR_LD], bd[TR_ROWS * TR_LD];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   int b = blockIdx.x;
   if (b >= 4 * splits) {
     b -= 4 * splits;
-    const int chunks = (n + 15) / 16, chunk = b >> 2, layer = (b >> 1) & 1, c = 4 * (4 * (b & 1) + w);
-    const float* src = layer ? sums3 + (long)chunk * X : dz2 + (long)chunk * 16 * X;
-    const int rows = layer ? 1 : min(16, n - 16 * chunk);
-    v4f v[4];
+    const int chunk = b >> 3, e = 256 * (b & 7) + tid;   // float4 e of the chunk's 8192 values
+    const v4f* src = reinterpret_cast<const v4f*>(dz2 + (long)chunk * 16 * X) + e;
+    const int rows = min(16, n - 16 * chunk);
+    v4f v[16], sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int r = 0; r < rows; ++r)
+    for (int r = 0; r < 16; ++r) v[r] = src[min(r, rows - 1) * (X / 4)];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) v[q] += *reinterpret_cast<const v4f*>(src + (long)r * X + (lane + 64 * q) * C + c);
-    const v4f sum = tree64((v[0] + v[2]) + (v[1] + v[3]));
-    if (lane == 0) *reinterpret_cast<v4f*>(bsum + ((long)layer * chunks + chunk) * C + c) = sum;
+    for (int r = 0; r < 16; ++r)
+      if (r < rows) sum += v[r];
+    reinterpret_cast<v4f*>(sums2 + (long)chunk * X)[e] = sum;
     return;
   }
   const int z = b >> 2, layer = (b >> 1) & 1, t0 = 4 * (b & 1), ci = 16 * (w & 1), co = 16 * (w >> 1);
@@ -537,18 +572,26 @@ __global__ void __launch_bounds__(256) k_train_dw_conv(const uint16_t* __restric
 }
 
 // ---- the parts added up
-// Workgroups by what they add (32 columns each, 16 of four columns for the dense biases):
-// parts one after the other for the convolutions' weights, the first convolution, the biases
-// of the others and, if split, dW5; dW6, db6 and the loss over eight interleaved sums; db4
-// and db5 over 256 interleaved sums and their tree.
+// Workgroups by what they add: 32 columns of the parts of the convolutions' weights, of the
+// first convolution's patches or, if split, of dW5's parts, row after row; four columns of
+// db2 or db3, a tree over the positions (pairs 128 apart, 64, ..) per 16 patches, those row
+// after row; dW6, db6 and the loss, eight interleaved sums; 16 columns of db4 or db5, 256
+// interleaved sums and their tree.
 struct ReduceArgs {
-  const float *conv, *part1, *bsum, *part5;
+  const float *conv, *part1, *sums2, *sums3, *part5;
   HeadOut head;
   int n, splits, split5;
 };
-constexpr int RD_CONV = 2 * CP_W / 32, RD_P1 = P1 / 32, RD_BIAS = 2, RD_W6 = H / 32 + 1, RD_DB = 2 * H / 16,
+constexpr int RD_CONV = 2 * CP_W / 32, RD_P1 = P1 / 32, RD_BIAS = 2 * C / 4, RD_W6 = H / 32 + 1, RD_DB = 2 * H / 16,
               RD_W5 = H * H / 32;
 constexpr int RD_ROWS = 256;
+__device__ __forceinline__ v4f tree64(v4f v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] += __shfl_down(v[i], o, 64);
+  return v;
+}
 // sum over rows, in order, of column tid % 32 of src (row stride `stride`); valid for tid < 32
 __device__ __forceinline__ float column_sum(const float* __restrict__ src, long stride, int rows, int tid,
                                             float (*buf)[33]) {
@@ -579,9 +622,14 @@ __device__ __forceinline__ float column_sum(const float* __restrict__ src, long 
   return sum;
 }
 __global__ void __launch_bounds__(256) k_train_reduce(ReduceArgs a, float* __restrict__ grad,
-                                                      float* __restrict__ loss) {
+                                                      float* __restrict__ grad_out, float* __restrict__ loss,
+                                                      float* __restrict__ loss_out) {
   __shared__ float buf[RD_ROWS][33];
   const int tid = threadIdx.x, n = a.n;
+  auto put = [&](long e, float v) {
+    grad[e] = v;
+    if (grad_out) grad_out[e] = v;
+  };
   int b = blockIdx.x;
   if (b < RD_DB) {
     // db5, then db4: wavefront of four columns, lane the rows lane, + 64, + 128, + 192 modulo 256
@@ -602,7 +650,7 @@ __global__ void __launch_bounds__(256) k_train_reduce(ReduceArgs a, float* __res
     }
     if (lane == 0)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) grad[(col < H ? O_B5 : O_B4) + c + i] = total[i];
+      for (int i = 0; i < 4; ++i) put((col < H ? O_B5 : O_B4) + c + i, total[i]);
     return;
   }
   b -= RD_DB;
@@ -623,23 +671,48 @@ __global__ void __launch_bounds__(256) k_train_reduce(ReduceArgs a, float* __res
     float sum = 0.f;
 #pragma unroll
     for (int q = 0; q < 8; ++q) sum += buf[q][c];
-    if (b < H / 32) grad[O_W6 + 32 * b + c] = sum;
-    else if (c == 0) grad[O_B6] = sum;
-    else if (c == 1) *loss = sum / (float)n;
+    if (b < H / 32) {
+      put(O_W6 + 32 * b + c, sum);
+    } else if (c == 0) {
+      put(O_B6, sum);
+    } else if (c == 1) {
+      *loss = sum / (float)n;
+      if (loss_out) *loss_out = sum / (float)n;
+    }
     return;
   }
   b -= RD_W6;
   if (b < RD_BIAS) {
-    const int chunks = (n + 15) / 16;
-    const float v = column_sum(a.bsum + (long)b * chunks * C, C, chunks, tid, buf);
-    if (tid < C) grad[(b ? O_B3 : O_B2) + tid] = v;
+    const int chunks = (n + 15) / 16, layer = b >= C / 4, c = 4 * (b % (C / 4));
+    const int lane = tid & 63, w = tid >> 6;
+    const float* src = (layer ? a.sums3 : a.sums2) + lane * C + c;
+    float sum = 0.f;
+    for (int k0 = 0; k0 < chunks; k0 += 32) {
+      const int m = min(32, chunks - k0);
+      __syncthreads();
+#pragma unroll 4
+      for (int k = w; k < m; k += 4) {
+        const float* q = src + (long)(k0 + k) * X;
+        v4f v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const v4f*>(q + 64 * i * C);
+        const v4f t = tree64((v[0] + v[2]) + (v[1] + v[3]));
+        if (lane == 0)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) buf[k][i] = t[i];
+      }
+      __syncthreads();
+      if (tid < 4)
+        for (int k = 0; k < m; ++k) sum += buf[k][tid];
+    }
+    if (tid < 4) put((layer ? O_B3 : O_B2) + c + tid, sum);
     return;
   }
   b -= RD_BIAS;
   if (b < RD_P1) {
     const float v = column_sum(a.part1 + 32 * b, P1, n, tid, buf);
     const int e = 32 * b + tid, c = e / (KW + 1), t = e % (KW + 1);
-    if (tid < 32) grad[t == KW ? O_B1 + c : O_W1 + c * KW + t] = v;
+    if (tid < 32) put(t == KW ? O_B1 + c : O_W1 + c * KW + t, v);
     return;
   }
   b -= RD_P1;
@@ -647,12 +720,12 @@ __global__ void __launch_bounds__(256) k_train_reduce(ReduceArgs a, float* __res
     const int layer = b >= RD_CONV / 2, e0 = 32 * (b - layer * (RD_CONV / 2));
     const float v = column_sum(a.conv + (long)layer * a.splits * CP_W + e0, CP_W, a.splits, tid, buf);
     const int ci = (e0 / C) % C, t = e0 / (C * C);
-    if (tid < C) grad[(layer ? O_W3 : O_W2) + (tid * C + ci) * KW + t] = v;
+    if (tid < C) put((layer ? O_W3 : O_W2) + (tid * C + ci) * KW + t, v);
     return;
   }
   b -= RD_CONV;
   const float v = column_sum(a.part5 + 32 * b, H * H, a.split5, tid, buf);
-  if (tid < 32) grad[O_W5 + 32 * b + tid] = v;
+  if (tid < 32) put(O_W5 + 32 * b + tid, v);
 }
 
 // ---- update
