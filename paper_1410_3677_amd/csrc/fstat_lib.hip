@@ -1640,8 +1640,13 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
   // batch sizes: requested or defaults, shrunk to the budget (admission).  Mixed precision:
   // 16 sky positions (8 leave the per-sky kernels too few workgroups: 24 against 14 us a
   // sky position) and 512 templates (256: 3% slower, more launches of the path not taken)
-  int Sb = opt.skies_per_batch ? opt.skies_per_batch : (p->fp64 ? 4 : 16);
-  int B = opt.templates_per_launch ? opt.templates_per_launch : (p->fp64 ? 16 : 512);
+  // FP64: 8 sky positions (4: 15% slower per-sky kernels), and templates for about 2^24 points
+  // of a transform, where the launches' ends no longer count (86164 samples: 4.8 us a template
+  // with 16, 4.3 with 128), 16 at least.
+  int Sb = opt.skies_per_batch ? opt.skies_per_batch : (p->fp64 ? 8 : 16);
+  int B = opt.templates_per_launch ? opt.templates_per_launch
+          : p->fp64                ? (int)std::max(16L, std::min(128L, (1L << 24) / p->TL_max))
+                                   : 512;
   bool tuned = false;
   if (!opt.skies_per_batch && !opt.templates_per_launch && opt.tuning_cache_path) {
     int tb = 0, ts = 0, tv = 0;
