@@ -309,12 +309,12 @@ fstat_status fstat_profile_read(fstat_plan_t plan, int32_t kernel_class, int64_t
  * precision path with P <= 512, other segments use row tiles; with
  * interbinning the mixed-precision second pass with P <= 512 is always a walk
  * of wavefronts over chunks of consecutive rows; FP64 and P = 1024 use row
- * tiles that store the transforms for a separate 2F pass).  In mixed precision a
- * call of enough templates (2^24 transform points) with variant 1, bins below
- * nfft/2 and no vetter attached transforms series decimated to 5/8 of the
- * sampling rate, (5/8) P Q points with the same bins, unless a spindown sweeps
- * the band by more than 0.005 cycles per sample over the segment; results agree
- * to rounding.  Any output pointer may be NULL. */
+ * tiles that store the transforms for a separate 2F pass).  A call of enough
+ * templates (2^24 transform points) with bins below nfft/2 and no vetter
+ * attached, in mixed precision with variant 1 or in FP64 without interbinning,
+ * transforms series decimated to 5/8 of the sampling rate, (5/8) P Q points with
+ * the same bins, unless a spindown sweeps the band by more than 0.005 cycles per
+ * sample over the segment; results agree to rounding.  Any output pointer may be NULL. */
 fstat_status fstat_plan_info(fstat_plan_t plan, int32_t segment, int32_t* nfft, int32_t* p,
                              int32_t* q, int32_t* templates_per_launch, int32_t* skies_per_batch,
                              int32_t* pass_a_variant, int32_t* pass_b_variant);

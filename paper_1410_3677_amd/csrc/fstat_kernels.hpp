@@ -210,7 +210,7 @@ struct TmplArgs {
   // which of two launched paths does the work: one of them returns at once (NULL: no choice)
   const int* route;
   int route_want;
-  float ibpr, ibpi;     // interbinning of decimated transforms: exp(2 pi i DEC_M0 / L)
+  float ibpr, ibpi;     // interbinning of decimated transforms: exp(2 pi i dec_m0 / L)
 };
 
 // Lattice arithmetic shared by the kernels and the host's candidate records, with
@@ -250,25 +250,43 @@ __device__ __forceinline__ void template_chirp(const TmplArgs& ta, int skyl, int
 // to the frequencies a template needs (its band, plus a margin for the spindown chirp's
 // sweep) and sampled every 8/5 samples, and each template transforms 5 L / 8 points
 // instead of L, with the same bins k / L at the same indices k.  The filter is a
-// Kaiser-windowed sinc, centred on a quarter of the sampling rate, of gain 1 within
-// 0.25 + 0.012 and below 1e-8 beyond 0.375 - 0.012 cycles per sample of the centre, so
-// that nothing folds into the searched bins.  Output m = 5 q + p (p < 5) is the filtered
-// series at sample t = 8 (q - DEC_Q0) + 8 p / 5; the transform's bins so carry the phase
-// exp(-2 pi i k DEC_M0 / L'), which |Fa|, |Fb| and Fa Fb* do not see.
+// Kaiser-windowed sinc, centred on a quarter of the sampling rate: gain 1 within 0.25 + 0.006
+// cycles per sample of the centre and 0 beyond 0.375 - 0.006, to 4e-8 (FP32) or 4e-15 (FP64),
+// so that nothing folds into the searched bins.  Output m = 5 q + p (p < 5) is the filtered
+// series at sample t = 8 (q - Q0) + 8 p / 5; the transform's bins so carry the phase
+// exp(-2 pi i k 5 Q0 / L'), which |Fa|, |Fb| and Fa Fb* do not see.
 constexpr int DEC_UP = 5, DEC_DOWN = 8;
-constexpr int DEC_T = 44;                       // filter half-width, samples
-constexpr int DEC_Q0 = 6, DEC_M0 = DEC_UP * DEC_Q0;
-constexpr int DEC_TAPS = 2 * DEC_T + DEC_DOWN;  // inputs of five outputs: 8 q' - 44 .. 8 q' + 51
-constexpr double DEC_BETA = 15.5;               // Kaiser parameter
+template <typename T>
+struct DecFilter;
+template <>
+struct DecFilter<float> {
+  static constexpr int HALF = 44, Q0 = 6;   // half-width in samples
+  static constexpr double BETA = 15.5;      // Kaiser parameter
+};
+template <>
+struct DecFilter<double> {
+  static constexpr int HALF = 92, Q0 = 12;
+  static constexpr double BETA = 32.0;
+};
+template <typename T>
+__host__ __device__ constexpr int dec_m0() { return DEC_UP * DecFilter<T>::Q0; }
+// inputs of five outputs: 8 q' - HALF .. 8 q' + HALF + 7
+template <typename T>
+__host__ __device__ constexpr int dec_taps() { return 2 * DecFilter<T>::HALF + DEC_DOWN; }
+template <typename T>
+constexpr bool dec_ok() { return dec_taps<T>() % 8 == 0 && DecFilter<T>::Q0 * DEC_DOWN >= DecFilter<T>::HALF; }
+static_assert(dec_ok<float>() && dec_ok<double>(), "filter geometry");
 constexpr double DEC_SWEEP = 0.005;             // largest chirp sweep (cycles per sample) the margin takes
-static_assert(DEC_TAPS % 8 == 0 && DEC_Q0 * DEC_DOWN >= DEC_T, "filter geometry");
 constexpr int DEC_NT = 128;                     // groups of five outputs per workgroup
 
 // samples of the decimated series of n samples (whole groups of five)
-inline long dec_samples(long n) { return DEC_UP * (DEC_Q0 + (n - 1 + DEC_T) / DEC_DOWN + 1); }
+template <typename T>
+inline long dec_samples(long n) {
+  return DEC_UP * (DecFilter<T>::Q0 + (n - 1 + DecFilter<T>::HALF) / DEC_DOWN + 1);
+}
 
 // Sky blockIdx.y, both series interleaved [m][a|b]; h[i][p] = filter value of input
-// 8 (q - DEC_Q0) - DEC_T + i in output p.  A thread forms one group of five outputs of one
+// 8 (q - Q0) - HALF + i in output p.  A thread forms one group of five outputs of one
 // series (wavefronts 0, 1: series a, 2, 3: b): 96 staged inputs, 475 taps, sums in double
 // precision (as fast as single on this chip without packed single precision), so that the
 // decimated series carries one rounding.  The taps are uniform (scalar loads); the centre
@@ -279,12 +297,12 @@ template <typename T>
 __global__ void __launch_bounds__(2 * DEC_NT) k_decimate(const cx_pair<T>* __restrict__ zt, long ldzt, int n,
                                                          cx<T>* __restrict__ zd, long ldzd, int nq,
                                                          const double* __restrict__ h) {
-  constexpr int NIN = DEC_DOWN * DEC_NT + DEC_TAPS - DEC_DOWN;
+  constexpr int TAPS = dec_taps<T>(), NIN = DEC_DOWN * DEC_NT + TAPS - DEC_DOWN;
   __shared__ cx<T> sz[2][NIN + NIN / 8 + 1];
   const int s = threadIdx.x / DEC_NT, tid = threadIdx.x % DEC_NT;
   const int q0 = blockIdx.x * DEC_NT;
   const cx<T>* z = reinterpret_cast<const cx<T>*>(zt + (long)blockIdx.y * ldzt) + s;
-  const int j0 = DEC_DOWN * (q0 - DEC_Q0) - DEC_T;
+  const int j0 = DEC_DOWN * (q0 - DecFilter<T>::Q0) - DecFilter<T>::HALF;
   for (int e = tid; e < NIN; e += DEC_NT) {
     const int j = j0 + e;
     sz[s][e + e / 8] = j >= 0 && j < n ? z[2 * j] : mk<T>(0, 0);
@@ -296,7 +314,7 @@ __global__ void __launch_bounds__(2 * DEC_NT) k_decimate(const cx_pair<T>* __res
 #pragma unroll
   for (int p = 0; p < DEC_UP; ++p) acc[p] = mk<double>(0.0, 0.0);
   const cx<T>* in = sz[s] + 9 * tid;
-  for (int g = 0; g < DEC_TAPS / 8; ++g) {
+  for (int g = 0; g < TAPS / 8; ++g) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const cx<T> v = in[9 * g + i];

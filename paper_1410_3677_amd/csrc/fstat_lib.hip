@@ -449,8 +449,9 @@ static double bessel_i0(double x) {
   return sum;
 }
 
+template <typename T>
 static void fill_dec_tables(std::vector<unsigned char>& buf, Tables& tb, const std::vector<int>& logs) {
-  typedef cx<float> C;
+  typedef cx<T> C;
   auto put = [&](size_t bytes) {
     size_t off = align256(buf.size());
     buf.resize(off + bytes);
@@ -459,8 +460,8 @@ static void fill_dec_tables(std::vector<unsigned char>& buf, Tables& tb, const s
   auto wexp = [](long m, long L) {
     const double a = 2.0 * M_PI * (double)m / (double)L;
     C w;
-    w.re = (float)std::cos(a);
-    w.im = (float)(-std::sin(a));
+    w.re = (T)std::cos(a);
+    w.im = (T)(-std::sin(a));
     return w;
   };
   for (int e : logs) {
@@ -480,17 +481,19 @@ static void fill_dec_tables(std::vector<unsigned char>& buf, Tables& tb, const s
           reinterpret_cast<C*>(buf.data() + tb.off_dstage)[dec_tw_offset(ns, rr) + k * (rr - 1) + (r - 1)] =
               wexp((long)k * r, (long)ns * rr);
   // Kaiser-windowed sinc, cutoff half the decimated rate, times the 8/5 that makes sums over
-  // decimated samples sums over samples: tap i of output p, at offset 8 p / 5 + 44 - i
-  tb.off_taps = put(DEC_TAPS * DEC_UP * sizeof(double));
+  // decimated samples sums over samples: tap i of output p, at offset 8 p / 5 + HALF - i
+  constexpr int TAPS = dec_taps<T>(), HALF = DecFilter<T>::HALF;
+  constexpr double BETA = DecFilter<T>::BETA;
+  tb.off_taps = put(TAPS * DEC_UP * sizeof(double));
   double* h = reinterpret_cast<double*>(buf.data() + tb.off_taps);
-  const double rate = (double)DEC_UP / DEC_DOWN, i0b = bessel_i0(DEC_BETA);
-  for (int i = 0; i < DEC_TAPS; ++i)
+  const double rate = (double)DEC_UP / DEC_DOWN, i0b = bessel_i0(BETA);
+  for (int i = 0; i < TAPS; ++i)
     for (int p = 0; p < DEC_UP; ++p) {
-      const double t = p / rate + DEC_T - i, u = t / DEC_T;
+      const double t = p / rate + HALF - i, u = t / HALF;
       double v = 0.0;
       if (std::fabs(u) <= 1.0) {
         const double a = M_PI * rate * t;
-        v = (t == 0.0 ? 1.0 : std::sin(a) / a) * bessel_i0(DEC_BETA * std::sqrt(1.0 - u * u)) / i0b;
+        v = (t == 0.0 ? 1.0 : std::sin(a) / a) * bessel_i0(BETA * std::sqrt(1.0 - u * u)) / i0b;
       }
       h[i * DEC_UP + p] = v;   // rate * (1 / rate)
     }
@@ -712,13 +715,11 @@ static fstat_status run_sky_batch(fstat_plan_t p, const Dev<T>& d, const SegInfo
     FSTAT_LAUNCH((k_spline<T>), dim3((unsigned)((n + spl_out<T>() - 1) / spl_out<T>()), nb), dim3(SPL_NT), 0, st, sc,
                  d.sp(), z, (long)M, o, (long)M, d.zt(), (long)n);
     HIP_TRY(p, launch_status(), "spline launch");
-    if constexpr (sizeof(T) == 4) {
-      if (dec) {
-        const int nq = (int)(si.dn / DEC_UP);
-        FSTAT_LAUNCH((k_decimate<T>), dim3((unsigned)((nq + DEC_NT - 1) / DEC_NT), nb), dim3(2 * DEC_NT), 0, st, d.zt(),
-                     (long)n, n, d.zd(), si.dn, nq, d.taps());
-        HIP_TRY(p, launch_status(), "decimation launch");
-      }
+    if (dec) {
+      const int nq = (int)(si.dn / DEC_UP);
+      FSTAT_LAUNCH((k_decimate<T>), dim3((unsigned)((nq + DEC_NT - 1) / DEC_NT), nb), dim3(2 * DEC_NT), 0, st, d.zt(),
+                   (long)n, n, d.zd(), si.dn, nq, d.taps());
+      HIP_TRY(p, launch_status(), "decimation launch");
     }
   }
   return FSTAT_OK;
@@ -741,14 +742,15 @@ constexpr int STREAM2_NT = 128;
 constexpr int STREAM2_WG_PER_CU = 3 * 256 / STREAM2_NT;
 
 // First pass of the decimated transforms of nt templates.
-static hipError_t launch_dec_a(const Dev<float>& d, const SegInfo& si, const TmplArgs& ta, int nt, cx<float>* tbuf,
+template <typename T>
+static hipError_t launch_dec_a(const Dev<T>& d, const SegInfo& si, const TmplArgs& ta, int nt, cx<T>* tbuf,
                                hipStream_t st) {
   hipError_t err = hipErrorInvalidValue;
   // first-stage inputs r >= rnz are zero for every column when dn <= rnz dL / 5
   const int rnz = (int)std::max<long>(2, (5 * si.dn + si.dL - 1) / si.dL);
   auto go = [&](auto len_c, auto rnz_c) {
     constexpr int LEN = decltype(len_c)::value, RZ = decltype(rnz_c)::value;
-    FSTAT_LAUNCH((k_tmpl_a_dec<float, LEN, RZ>), dim3((unsigned)(si.tP / dec_tw<LEN>() * nt)), dim3(DEC_A_NT), 0, st,
+    FSTAT_LAUNCH((k_tmpl_a_dec<T, LEN, RZ>), dim3((unsigned)(si.tP / dec_tw<T, LEN>() * nt)), dim3(dec_nt<T>()), 0, st,
                  ta, d.zd(), tbuf, d.dec_stage(), d.dec_lo(si.tlog), d.dec_hi(si.tlog));
     err = launch_status();
   };
@@ -825,14 +827,14 @@ static hipError_t launch_stream_b(const Dev<float>& d, const SegInfo& si, const 
 }
 
 // Whether a call's templates of segment si run as decimated transforms.  They save 3/8 of
-// a template's memory traffic and arithmetic (0.93 against 1.47 us at 2^18 points) and cost
-// the filter, once a sky position (2.2 us), and the launches of the path not taken (10 us a
+// a template's memory traffic and arithmetic (0.93 against 1.47 us at 2^18 points; FP64 2.8
+// against 4.65) and cost the filter, once a sky position (2.2 us; FP64 2.9), and the launches of the path not taken (10 us a
 // launch pair); where those weigh more, with few spindowns or in small calls, the full-rate
 // transforms stay.  The patch capture stores the rows of the full-rate second pass.
 constexpr long DEC_MIN_POINTS = 1L << 24;   // templates times transform points
 constexpr int DEC_MIN_FDOT = 5;             // spindowns per sky position
 static bool use_dec(fstat_plan_t p, const SegInfo& si, const Grid& g, int mode) {
-  return si.dec && p->dn_max && p->variant_b == 1 && !(mode == 0 && p->vet) && g.nfdot >= DEC_MIN_FDOT &&
+  return si.dec && p->dn_max && (p->fp64 || p->variant_b == 1) && !(mode == 0 && p->vet) && g.nfdot >= DEC_MIN_FDOT &&
          (long)g.nsky * g.nfdot * si.tL >= DEC_MIN_POINTS;
 }
 
@@ -873,8 +875,8 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
     td.Q = si.dQ;
     td.L = si.dL;
     td.ldzt = si.dn;
-    td.ibpr = (float)std::cos(2.0 * M_PI * DEC_M0 / si.dL);
-    td.ibpi = (float)std::sin(2.0 * M_PI * DEC_M0 / si.dL);
+    td.ibpr = (float)std::cos(2.0 * M_PI * dec_m0<T>() / si.dL);
+    td.ibpi = (float)std::sin(2.0 * M_PI * dec_m0<T>() / si.dL);
   }
   const int total = nb * nfdot;
   cx<T>* tbuf = d.tmpl();
@@ -889,9 +891,7 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
     hipError_t err = hipSuccess;
     {
       ProfScope ps(p, FSTAT_KERNEL_TEMPLATE_A, st);
-      if constexpr (sizeof(T) == 4) {
-        if (dec) err = launch_dec_a(d, si, td, nt, tbuf, st);
-      }
+      if (dec) err = launch_dec_a(d, si, td, nt, tbuf, st);
       if (err == hipSuccess) with_len(si.tQ, [&](auto c) {
         constexpr int QQ = decltype(c)::value;
         if constexpr (QQ >= 64) {
@@ -952,6 +952,7 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
         }
         if constexpr (PP >= 64) {
           const int ntiles = si.tQ / tw_b<T, PP>();
+          ta.nblk = ntiles * nt;
           if (si.ibw != 0.0) {
             // interbinning through the tiled pass (FP64, or P > 512): it stores the
             // transforms, then an epilogue forms the interbinned 2F of the launch's templates
@@ -973,15 +974,23 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
             err = launch_status();
             return;
           }
-          if (capture)
-            FSTAT_LAUNCH((k_tmpl_b<T, PP, 2>), dim3(ntiles * nt), dim3(tmpl_nt_b<T, PP>()), 0, st, ta, d.sp(),
-                               tbuf, oa, d.twst);
-          else if (mode == 0)
-            FSTAT_LAUNCH((k_tmpl_b<T, PP, 0>), dim3(ntiles * nt), dim3(tmpl_nt_b<T, PP>()), 0, st, ta, d.sp(),
-                               tbuf, oa, d.twst);
-          else
-            FSTAT_LAUNCH((k_tmpl_b<T, PP, 1>), dim3(ntiles * nt), dim3(tmpl_nt_b<T, PP>()), 0, st, ta, d.sp(),
-                               tbuf, oa, d.twst);
+          const auto go = [&](auto mode_c) {
+            constexpr int MD = decltype(mode_c)::value;
+            if constexpr (sizeof(T) == 8 && MD != 2) {
+              if (dec) {
+                FSTAT_LAUNCH((k_tmpl_b<T, PP, MD>), dim3(si.dQ / tw_b<T, PP>() * nt), dim3(tmpl_nt_b<T, PP>()), 0, st,
+                             td, d.sp(), tbuf, oa, d.twst);
+                FSTAT_LAUNCH((k_tmpl_b<T, PP, MD, true>), dim3(std::min(ta.nblk, 2 * p->n_cu)),
+                             dim3(tmpl_nt_b<T, PP>()), 0, st, ta, d.sp(), tbuf, oa, d.twst);
+                return;
+              }
+            }
+            FSTAT_LAUNCH((k_tmpl_b<T, PP, MD>), dim3(ta.nblk), dim3(tmpl_nt_b<T, PP>()), 0, st, ta, d.sp(), tbuf, oa,
+                         d.twst);
+          };
+          if (capture) go(std::integral_constant<int, 2>{});
+          else if (mode == 0) go(std::integral_constant<int, 0>{});
+          else go(std::integral_constant<int, 1>{});
           err = launch_status();
         } else {
           err = hipErrorInvalidValue;
@@ -1621,9 +1630,11 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
     // series, filter tails included, within the transform
     si.dQ = 5 * si.tQ / 8;
     si.dL = 5 * (si.tL / 8);
-    si.dn = dec_samples(s.n);
-    si.dec = !p->fp64 && si.tQ >= 64 && si.kmax <= si.nfft / 2 && si.dn <= si.dL &&
-             !(opt.interbinning && si.tP > 512);
+    si.dn = p->fp64 ? dec_samples<double>(s.n) : dec_samples<float>(s.n);
+    si.dec = si.tQ >= 64 && si.kmax <= si.nfft / 2 && si.dn <= si.dL;
+    // interbinning: not through the tiled second pass (FP64, or P > 512).  FP64: whole row tiles
+    if (opt.interbinning && (p->fp64 || si.tP > 512)) si.dec = false;
+    if (p->fp64 && si.dQ % (2048 / si.tP) != 0) si.dec = false;
     if (si.kmax > si.nfft) {
       std::snprintf(msg, sizeof msg, "segment %d: k_max=%d beyond nfft=%d", i, si.kmax, si.nfft);
       delete p;
@@ -1711,10 +1722,11 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
     }
     if (p->fp64) {
       fill_tables<double>(tb, p->tab, 1, logs);
+      if (!dec.empty()) fill_dec_tables<double>(tb, p->tab, dec);
     } else {
       fill_tables<float>(tb, p->tab, 0, logs);
       fill_full_tables(tb, p->tab);
-      if (!dec.empty()) fill_dec_tables(tb, p->tab, dec);
+      if (!dec.empty()) fill_dec_tables<float>(tb, p->tab, dec);
     }
   }
   p->tab.bytes = tb.size();

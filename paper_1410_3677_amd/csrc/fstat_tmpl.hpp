@@ -494,7 +494,7 @@ __global__ void __launch_bounds__((tmpl_nt_a<T, Q>())) k_tmpl_a_pair(TmplArgs ta
 // ---------------------------------------------------------------- pass A of the decimated transforms
 // L' = 5 L / 8 points (fstat_kernels.hpp, "decimated series"): P columns as in the general
 // first pass, of LEN = 5 Q / 8 points each: radix 5, then 8s, then 4 or 2.  A workgroup
-// takes 2560 / LEN columns (eight of 320 points: one 128-byte (a, b) line per row of the
+// takes 2560 / LEN columns in FP32 (eight of 320 points: one 128-byte (a, b) line per row of the
 // intermediate) of both series; its 320 threads hold one radix-8 butterfly each per stage
 // and 1.6 radix-5 ones in the first, of whose five inputs only the first RNZ can be
 // nonzero (n' <= RNZ L' / 5).  The LDS tile holds the two series of a position side by
@@ -504,9 +504,14 @@ __global__ void __launch_bounds__((tmpl_nt_a<T, Q>())) k_tmpl_a_pair(TmplArgs ta
 // template of L = 2^18 (2.62 MB, 5.3 TB/s), against 0.74 us for the general first pass's
 // 4.19 MB; separate, padded series planes (three workgroups per compute unit) took 0.67, a
 // loop over four templates per workgroup (137 registers) 0.69.
-constexpr int DEC_A_NT = 320;
-template <int LEN>
-__host__ __device__ constexpr int dec_tw() { return 2560 / LEN; }
+// FP64: half the columns (four of 320 points, one 128-byte line again) and 160 threads, for
+// the same 40 KB and four workgroups per CU: 1.27 us per template of L = 2^18 (5.24 MB
+// written, 4.1 TB/s) against 1.73 with the FP32 split (80 KB, two workgroups) and 2.3 for
+// the general first pass's 8.39 MB; the second pass takes 1.5 us against 2.35.
+template <typename T>
+__host__ __device__ constexpr int dec_nt() { return sizeof(T) == 4 ? 320 : 160; }
+template <typename T, int LEN>
+__host__ __device__ constexpr int dec_tw() { return 8 * dec_nt<T>() / LEN; }
 template <int LEN, int NS>
 __host__ __device__ constexpr int dec_radix() { return NS == 1 ? 5 : (LEN / NS >= 8 ? 8 : LEN / NS); }
 // Stage twiddles exp(-2 pi i k r / (NS R)), [k][r - 1], NS in {5, 40, 320} and R in {2, 4, 8}.
@@ -555,7 +560,7 @@ __device__ __forceinline__ void dft5(cx<T>* v) {
 template <typename T, int LEN, int NS>
 __device__ __forceinline__ void dec_stage(cx<T>* va, cx<T>* vb, const cx_pair<T>* p, int j,
                                           const cx<T>* __restrict__ tw5) {
-  constexpr int R = dec_radix<LEN, NS>(), TW = dec_tw<LEN>(), NB = LEN / R;
+  constexpr int R = dec_radix<LEN, NS>(), TW = dec_tw<T, LEN>(), NB = LEN / R;
   const cx<T>* tw = tw5 + dec_tw_offset(NS, R) + (j % NS) * (R - 1);
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -577,19 +582,19 @@ template <typename T, int LEN, int NS>
 __device__ __forceinline__ void dec_middle(cx_pair<T>* lds, const cx<T>* __restrict__ tw5) {
   constexpr int R = dec_radix<LEN, NS>();
   if constexpr (NS * R < LEN) {
-    constexpr int TW = dec_tw<LEN>(), NB = LEN / R, TB = TW * NB;
-    constexpr int PER = TB / DEC_A_NT;
-    static_assert(TB % DEC_A_NT == 0, "whole butterflies per thread");
+    constexpr int TW = dec_tw<T, LEN>(), NB = LEN / R, TB = TW * NB;
+    constexpr int PER = TB / dec_nt<T>();
+    static_assert(TB % dec_nt<T>() == 0, "whole butterflies per thread");
     cx<T> va[PER][R], vb[PER][R];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int b = (int)threadIdx.x + i * DEC_A_NT;   // index j, column c: b = TW j + c
+      const int b = (int)threadIdx.x + i * dec_nt<T>();   // index j, column c: b = TW j + c
       dec_stage<T, LEN, NS>(va[i], vb[i], lds + b, b / TW, tw5);
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int b = (int)threadIdx.x + i * DEC_A_NT, c = b % TW, j = b / TW;
+      const int b = (int)threadIdx.x + i * dec_nt<T>(), c = b % TW, j = b / TW;
       cx_pair<T>* p = lds + ((j / NS) * NS * R + j % NS) * TW + c;
 #pragma unroll
       for (int r = 0; r < R; ++r) p[r * NS * TW] = cx_pair<T>{va[i][r], vb[i][r]};
@@ -606,11 +611,11 @@ __host__ __device__ constexpr int dec_last_ns() {
 }
 
 template <typename T, int LEN, int RNZ>
-__global__ void __launch_bounds__(DEC_A_NT) k_tmpl_a_dec(TmplArgs ta, const cx<T>* __restrict__ zd,
+__global__ void __launch_bounds__(dec_nt<T>()) k_tmpl_a_dec(TmplArgs ta, const cx<T>* __restrict__ zd,
                                                          cx<T>* __restrict__ tbuf, const cx<T>* __restrict__ tw5,
                                                          const cx<T>* __restrict__ twlo,
                                                          const cx<T>* __restrict__ twhi) {
-  constexpr int TW = dec_tw<LEN>();
+  constexpr int TW = dec_tw<T, LEN>();
   typedef cx_pair<T> pair;
   __shared__ pair lds[LEN * TW];
   const int go = *ta.route;   // tested once the loads are on their way
@@ -620,18 +625,18 @@ __global__ void __launch_bounds__(DEC_A_NT) k_tmpl_a_dec(TmplArgs ta, const cx<T
   const int skyl = t / ta.nfdot, sidx = t % ta.nfdot;
   {
     // first stage: the chirp in units of decimated samples, one radix-5 butterfly
-    constexpr int NB = LEN / 5, TB = TW * NB, PER = (TB + DEC_A_NT - 1) / DEC_A_NT;
+    constexpr int NB = LEN / 5, TB = TW * NB, PER = (TB + dec_nt<T>() - 1) / dec_nt<T>();
     const pair* z = reinterpret_cast<const pair*>(zd + (long)(2 * skyl) * ta.ldzt);
     cx<T> va[PER][5], vb[PER][5];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int b = (int)threadIdx.x + i * DEC_A_NT;   // column b % TW, index b / TW
+      const int b = (int)threadIdx.x + i * dec_nt<T>();   // column b % TW, index b / TW
       const unsigned m0 = (unsigned)(tile * TW + b % TW) + (unsigned)ta.P * (unsigned)(b / TW);
 #pragma unroll
       for (int r = 0; r < RNZ; ++r) {
         const unsigned m = m0 + (unsigned)(NB * r) * (unsigned)ta.P;
         va[i][r] = vb[i][r] = mk<T>(0, 0);
-        if ((TB % DEC_A_NT == 0 || b < TB) && m < (unsigned)ta.n) {
+        if ((TB % dec_nt<T>() == 0 || b < TB) && m < (unsigned)ta.n) {
           const pair v = z[m];
           va[i][r] = v.a;
           vb[i][r] = v.b;
@@ -645,9 +650,9 @@ __global__ void __launch_bounds__(DEC_A_NT) k_tmpl_a_dec(TmplArgs ta, const cx<T
     c1 *= (double)DEC_DOWN / DEC_UP;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int b = (int)threadIdx.x + i * DEC_A_NT, c = b % TW, j = b / TW;
-      if (TB % DEC_A_NT == 0 || b < TB) {
-        const int m0 = tile * TW + c + ta.P * j - DEC_M0;
+      const int b = (int)threadIdx.x + i * dec_nt<T>(), c = b % TW, j = b / TW;
+      if (TB % dec_nt<T>() == 0 || b < TB) {
+        const int m0 = tile * TW + c + ta.P * j - dec_m0<T>();
 #pragma unroll
         for (int r = 0; r < RNZ; ++r) {
           const double x = (double)(m0 + NB * r * ta.P);
@@ -677,12 +682,12 @@ __global__ void __launch_bounds__(DEC_A_NT) k_tmpl_a_dec(TmplArgs ta, const cx<T
   dec_middle<T, LEN, 5>(lds, tw5);
   // last stage, times W^(j1 k2) for its outputs k2 = j + NSL r
   constexpr int NSL = dec_last_ns<LEN, 1>(), RL = dec_radix<LEN, NSL>(), NB = LEN / RL;
-  constexpr int TB = TW * NB, PER = TB / DEC_A_NT;
-  static_assert(TB % DEC_A_NT == 0, "whole butterflies per thread");
+  constexpr int TB = TW * NB, PER = TB / dec_nt<T>();
+  static_assert(TB % dec_nt<T>() == 0, "whole butterflies per thread");
   cx<T>* out = tbuf + (long)(2 * item) * ta.L;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
-    const int b = (int)threadIdx.x + i * DEC_A_NT, j = b / TW, j1 = tile * TW + b % TW;
+    const int b = (int)threadIdx.x + i * dec_nt<T>(), j = b / TW, j1 = tile * TW + b % TW;
     cx<T> va[RL], vb[RL];
     dec_stage<T, LEN, NSL>(va, vb, lds + b, j, tw5);
     const cx<T> step = twiddle_L<T, false>(twlo, twhi, j1 * NSL);
@@ -718,7 +723,9 @@ __device__ __forceinline__ double two_f_value(cx<double> fa, cx<double> fb, doub
 
 // ---------------------------------------------------------------- pass B
 // Workgroup: TW adjacent rows k2 of one template; thread (c = t / G, g = t % G).
-template <typename T, int P, int MODE>
+// WALK: a grid smaller than ta.nblk walks the tiles (the path that a call with decimated
+// transforms may not take).
+template <typename T, int P, int MODE, bool WALK = false>
 __global__ void __launch_bounds__((tmpl_nt_b<T, P>())) k_tmpl_b(TmplArgs ta, const SkyParams* __restrict__ sp,
                                                            const cx<T>* __restrict__ tbuf, OutArgs oa,
                                                            const cx<T>* __restrict__ twst) {
@@ -731,133 +738,138 @@ __global__ void __launch_bounds__((tmpl_nt_b<T, P>())) k_tmpl_b(TmplArgs ta, con
   static_assert(TW * G == NTB, "one butterfly group per thread");
   __shared__ cx<T> lds[2 * TW * ST];
   __shared__ unsigned long long sbase;
-  int tile, item;
-  xcd_tile_item(blockIdx.x, ta.Q / TW, tile, item);
-  const int c = threadIdx.x / G, g = threadIdx.x % G;
-  const int t = ta.t0 + item;
-  const int skyl = t / ta.nfdot, sidx = t % ta.nfdot;
-  const int k2 = tile * TW + c;
-  const cx<T>* in = tbuf + (long)(2 * item) * ta.L + 2 * (long)k2 * ta.P;
-  cx<T>* cola = lds + c * ST;
-  cx<T>* colb = lds + (TW + c) * ST;
-  {
-    cx<T> va[PB1][R1], vb[PB1][R1];
+  if (ta.route && *ta.route != ta.route_want) return;
+  int blk = blockIdx.x;
+  do {
+    if (WALK && blk != (int)blockIdx.x) __syncthreads();  // the previous tile has been read
+    int tile, item;
+    xcd_tile_item(blk, ta.Q / TW, tile, item);
+    const int c = threadIdx.x / G, g = threadIdx.x % G;
+    const int t = ta.t0 + item;
+    const int skyl = t / ta.nfdot, sidx = t % ta.nfdot;
+    const int k2 = tile * TW + c;
+    const cx<T>* in = tbuf + (long)(2 * item) * ta.L + 2 * (long)k2 * ta.P;
+    cx<T>* cola = lds + c * ST;
+    cx<T>* colb = lds + (TW + c) * ST;
+    {
+      cx<T> va[PB1][R1], vb[PB1][R1];
 #pragma unroll
-    for (int b = 0; b < PB1; ++b) {
-      const int j = g + G * b;
+      for (int b = 0; b < PB1; ++b) {
+        const int j = g + G * b;
 #pragma unroll
-      for (int r = 0; r < R1; ++r) {
-        va[b][r] = in[2 * (j + NB1 * r)];
-        vb[b][r] = in[2 * (j + NB1 * r) + 1];
+        for (int r = 0; r < R1; ++r) {
+          va[b][r] = in[2 * (j + NB1 * r)];
+          vb[b][r] = in[2 * (j + NB1 * r) + 1];
+        }
+        dftr<T, R1, false>(va[b]);
+        dftr<T, R1, false>(vb[b]);
       }
-      dftr<T, R1, false>(va[b]);
-      dftr<T, R1, false>(vb[b]);
+      stage_to_lds<T, P, G, 1, R1, PB1>(va, cola, g);
+      stage_to_lds<T, P, G, 1, R1, PB1>(vb, colb, g);
+      stage_sync<rows_in_wave<P>()>();
     }
-    stage_to_lds<T, P, G, 1, R1, PB1>(va, cola, g);
-    stage_to_lds<T, P, G, 1, R1, PB1>(vb, colb, g);
-    stage_sync<rows_in_wave<P>()>();
-  }
-  middle_stages<T, P, G, R1, false, rows_in_wave<P>()>(cola, colb, g, twst);
-  constexpr int NSL = last_ns<P, 1>();
-  constexpr int RL = stage_radix<P, NSL>();
-  constexpr int PBL = (P / RL) / G;
-  constexpr int NOUT = PBL * RL;
-  static_assert(NOUT <= 32, "output mask");
-  cx<T> va[PBL][RL], vb[PBL][RL];
-  stage_from_lds<T, P, G, NSL, RL, PBL, false>(va, cola, g, twst);
-  stage_from_lds<T, P, G, NSL, RL, PBL, false>(vb, colb, g, twst);
-  if constexpr (MODE == 3) {
-    // the transform itself, for an epilogue of its own: oa.spectrum as [item][k][a|b]
-    cx<T>* xs = (cx<T>*)oa.spectrum + (long)(2 * item) * ta.L;
+    middle_stages<T, P, G, R1, false, rows_in_wave<P>()>(cola, colb, g, twst);
+    constexpr int NSL = last_ns<P, 1>();
+    constexpr int RL = stage_radix<P, NSL>();
+    constexpr int PBL = (P / RL) / G;
+    constexpr int NOUT = PBL * RL;
+    static_assert(NOUT <= 32, "output mask");
+    cx<T> va[PBL][RL], vb[PBL][RL];
+    stage_from_lds<T, P, G, NSL, RL, PBL, false>(va, cola, g, twst);
+    stage_from_lds<T, P, G, NSL, RL, PBL, false>(vb, colb, g, twst);
+    if constexpr (MODE == 3) {
+      // the transform itself, for an epilogue of its own: oa.spectrum as [item][k][a|b]
+      cx<T>* xs = (cx<T>*)oa.spectrum + (long)(2 * item) * ta.L;
 #pragma unroll
-    for (int b = 0; b < PBL; ++b) {
+      for (int b = 0; b < PBL; ++b) {
 #pragma unroll
-      for (int r = 0; r < RL; ++r) {
-        const int k = ta.Q * (g + G * b + NSL * r) + k2;
-        xs[2 * k] = va[b][r];
-        xs[2 * k + 1] = vb[b][r];
-      }
-    }
-    return;
-  }
-  const SkyParams& pr = sp[skyl];
-  const T cfa = (T)pr.cfa, cfb = (T)pr.cfb, cfab = (T)pr.cfab;
-  if constexpr (MODE == 2) {
-    // the launch's 2F rows for the patch capture that follows (template-major, FP32)
-    float* out = (float*)oa.spectrum + (long)item * (long)(oa.k_max - oa.k_min);
-#pragma unroll
-    for (int b = 0; b < PBL; ++b) {
-#pragma unroll
-      for (int r = 0; r < RL; ++r) {
-        const int klo = ta.Q * (G * b + NSL * r) + k2;
-        if (klo < oa.k_max && klo + ta.Q * (G - 1) >= oa.k_min) {
+        for (int r = 0; r < RL; ++r) {
           const int k = ta.Q * (g + G * b + NSL * r) + k2;
-          if (k >= oa.k_min && k < oa.k_max) {
-            const cx<T> fa = va[b][r], fb = vb[b][r];
-            out[k - oa.k_min] = (float)two_f_value(fa, fb, cfa, cfb, cfab);
+          xs[2 * k] = va[b][r];
+          xs[2 * k + 1] = vb[b][r];
+        }
+      }
+      continue;
+    }
+    const SkyParams& pr = sp[skyl];
+    const T cfa = (T)pr.cfa, cfb = (T)pr.cfb, cfab = (T)pr.cfab;
+    if constexpr (MODE == 2) {
+      // the launch's 2F rows for the patch capture that follows (template-major, FP32)
+      float* out = (float*)oa.spectrum + (long)item * (long)(oa.k_max - oa.k_min);
+#pragma unroll
+      for (int b = 0; b < PBL; ++b) {
+#pragma unroll
+        for (int r = 0; r < RL; ++r) {
+          const int klo = ta.Q * (G * b + NSL * r) + k2;
+          if (klo < oa.k_max && klo + ta.Q * (G - 1) >= oa.k_min) {
+            const int k = ta.Q * (g + G * b + NSL * r) + k2;
+            if (k >= oa.k_min && k < oa.k_max) {
+              const cx<T> fa = va[b][r], fb = vb[b][r];
+              out[k - oa.k_min] = (float)two_f_value(fa, fb, cfa, cfb, cfab);
+            }
           }
         }
       }
     }
-  }
-  if constexpr (MODE == 1) {
-    T* out = (T*)oa.spectrum + ((long)(ta.sky0 + skyl) * ta.nfdot + sidx) * (long)(oa.k_max - oa.k_min);
+    if constexpr (MODE == 1) {
+      T* out = (T*)oa.spectrum + ((long)(ta.sky0 + skyl) * ta.nfdot + sidx) * (long)(oa.k_max - oa.k_min);
 #pragma unroll
-    for (int b = 0; b < PBL; ++b) {
+      for (int b = 0; b < PBL; ++b) {
 #pragma unroll
-      for (int r = 0; r < RL; ++r) {
-        const int k = ta.Q * (g + G * b + NSL * r) + k2;
-        if (k >= oa.k_min && k < oa.k_max) {
-          const cx<T> fa = va[b][r], fb = vb[b][r];
-          out[k - oa.k_min] = two_f_value(fa, fb, cfa, cfb, cfab);
-        }
-      }
-    }
-  } else {  // MODE 0 and 2: threshold and compaction
-    uint32_t mask = 0;
-    T val[NOUT];
-#pragma unroll
-    for (int b = 0; b < PBL; ++b) {
-#pragma unroll
-      for (int r = 0; r < RL; ++r) {
-        val[b * RL + r] = (T)0;
-        // bins of this output group: k = Q (G b + NSL r + g') + k2 over the G lanes g'
-        const int klo = ta.Q * (G * b + NSL * r) + k2;
-        if (klo < oa.k_max && klo + ta.Q * (G - 1) >= oa.k_min) {
+        for (int r = 0; r < RL; ++r) {
           const int k = ta.Q * (g + G * b + NSL * r) + k2;
-          const cx<T> fa = va[b][r], fb = vb[b][r];
-          const T v = two_f_value(fa, fb, cfa, cfb, cfab);
-          val[b * RL + r] = v;
-          if (k >= oa.k_min && k < oa.k_max && v > (T)oa.threshold) mask |= 1u << (b * RL + r);
+          if (k >= oa.k_min && k < oa.k_max) {
+            const cx<T> fa = va[b][r], fb = vb[b][r];
+            out[k - oa.k_min] = two_f_value(fa, fb, cfa, cfb, cfab);
+          }
         }
       }
-    }
-    int total;
-    const int off = block_exclusive_scan_n<NTB>(__popc(mask), &total);
-    if (total == 0) return;
-    if (threadIdx.x == 0) sbase = atomicAdd(oa.count, (unsigned long long)total);
-    __syncthreads();
-    const int search = oa.search_next[0] - 1;
-    unsigned long long slot = sbase + (unsigned long long)off;
+    } else {  // MODE 0 and 2: threshold and compaction
+      uint32_t mask = 0;
+      T val[NOUT];
 #pragma unroll
-    for (int i = 0; i < NOUT; ++i) {
-      if (mask & (1u << i)) {
-        if (slot < (unsigned long long)oa.capacity) {
-          const int b = i / RL, r = i % RL;
-          CandEntry ce;
-          ce.search = search;
-          ce.segment = oa.segment;
-          ce.sky = ta.sky0 + skyl;
-          ce.fdot_idx = sidx;
-          ce.bin = ta.Q * (g + G * b + NSL * r) + k2;
-          ce.pad = 0;
-          ce.twoF = (double)val[i];
-          oa.cand[slot] = ce;
+      for (int b = 0; b < PBL; ++b) {
+#pragma unroll
+        for (int r = 0; r < RL; ++r) {
+          val[b * RL + r] = (T)0;
+          // bins of this output group: k = Q (G b + NSL r + g') + k2 over the G lanes g'
+          const int klo = ta.Q * (G * b + NSL * r) + k2;
+          if (klo < oa.k_max && klo + ta.Q * (G - 1) >= oa.k_min) {
+            const int k = ta.Q * (g + G * b + NSL * r) + k2;
+            const cx<T> fa = va[b][r], fb = vb[b][r];
+            const T v = two_f_value(fa, fb, cfa, cfb, cfab);
+            val[b * RL + r] = v;
+            if (k >= oa.k_min && k < oa.k_max && v > (T)oa.threshold) mask |= 1u << (b * RL + r);
+          }
         }
-        ++slot;
+      }
+      int total;
+      const int off = block_exclusive_scan_n<NTB>(__popc(mask), &total);
+      if (total == 0) continue;
+      if (threadIdx.x == 0) sbase = atomicAdd(oa.count, (unsigned long long)total);
+      __syncthreads();
+      const int search = oa.search_next[0] - 1;
+      unsigned long long slot = sbase + (unsigned long long)off;
+#pragma unroll
+      for (int i = 0; i < NOUT; ++i) {
+        if (mask & (1u << i)) {
+          if (slot < (unsigned long long)oa.capacity) {
+            const int b = i / RL, r = i % RL;
+            CandEntry ce;
+            ce.search = search;
+            ce.segment = oa.segment;
+            ce.sky = ta.sky0 + skyl;
+            ce.fdot_idx = sidx;
+            ce.bin = ta.Q * (g + G * b + NSL * r) + k2;
+            ce.pad = 0;
+            ce.twoF = (double)val[i];
+            oa.cand[slot] = ce;
+          }
+          ++slot;
+        }
       }
     }
-  }
+  } while (WALK && (blk += gridDim.x) < ta.nblk);
 }
 
 // ------------------------------------------------ interbinned 2F from stored transforms (FP64)
