@@ -2123,8 +2123,8 @@ static fstat_status order_on_device(fstat_plan_t p, long long stored, const Drai
   size_t o = 0;
   auto put = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return at; };
   const size_t o_grp = put((size_t)stored * sizeof(CandEntry)), o_rank = put((size_t)stored * 4),
-               o_cnt = put((size_t)ntpl * 4), o_off = put((size_t)(ntpl + 1) * 8), o_sums = put((size_t)ntiles * 8),
-               o_tab = put((size_t)nsearch * (sizeof(DrainSearch) + sizeof(DrainList))), o_flag = put(2 * 4);
+               o_cnt = put((size_t)ntpl * 4 + 2 * sizeof(unsigned)), o_off = put((size_t)(ntpl + 1) * 8), o_sums = put((size_t)ntiles * 8),
+               o_tab = put((size_t)nsearch * (sizeof(DrainSearch) + sizeof(DrainList)));
   if (o > p->drain_bytes) {
     if (p->drain_ws) (void)hipFree(p->drain_ws);
     p->drain_ws = nullptr;
@@ -2139,7 +2139,7 @@ static fstat_status order_on_device(fstat_plan_t p, long long stored, const Drai
   unsigned long long* off = (unsigned long long*)(w + o_off);
   unsigned long long* sums = (unsigned long long*)(w + o_sums);
   DrainSearch* ds = (DrainSearch*)(w + o_tab);
-  unsigned* flags = (unsigned*)(w + o_flag);   // [0] key outside its search, [1] repeated bin of a template
+  unsigned* flags = counts + ntpl;   // cleared with them; [0] key outside its search, [1] repeated bin of a template
   // the searches, then their lists, in one copy
   std::vector<unsigned char> tab(hs.size() * (sizeof(DrainSearch) + sizeof(DrainList)));
   std::memcpy(tab.data(), hs.data(), hs.size() * sizeof(DrainSearch));
@@ -2152,21 +2152,24 @@ static fstat_status order_on_device(fstat_plan_t p, long long stored, const Drai
   *bad = flags;
   const hipStream_t st = nullptr;
   const unsigned gblk = (unsigned)std::min<long long>((stored + DRAIN_NT - 1) / DRAIN_NT, 1LL << 20);
-  FSTAT_LAUNCH(k_drain_zero, dim3((unsigned)std::min<long long>((ntpl + DRAIN_NT - 1) / DRAIN_NT, 1LL << 20)),
-               dim3(DRAIN_NT), 0, st, counts, ntpl);
-  FSTAT_LAUNCH(k_drain_zero, dim3(1), dim3(DRAIN_NT), 0, st, flags, 2LL);
+  FSTAT_LAUNCH(k_drain_zero, dim3((unsigned)std::min<long long>((ntpl + 2 + DRAIN_NT - 1) / DRAIN_NT, 1LL << 20)),
+               dim3(DRAIN_NT), 0, st, counts, ntpl + 2);
   FSTAT_LAUNCH(k_drain_count, dim3(gblk), dim3(DRAIN_NT), 0, st, p->d_cand, stored, ds, nsearch, search0, nseg, counts,
                rank, flags);
   HIP_TRY(p, launch_status(), "drain count launch");
-  FSTAT_LAUNCH(k_scan_tile_sums, dim3((unsigned)ntiles), dim3(DRAIN_NT), 0, st, counts, ntpl, sums);
-  FSTAT_LAUNCH(k_scan_sums, dim3(1), dim3(DRAIN_NT), 0, st, sums, ntiles);
-  FSTAT_LAUNCH(k_scan_apply, dim3((unsigned)ntiles), dim3(DRAIN_NT), 0, st, counts, ntpl, sums, off);
+  if (ntiles > 1) {
+    FSTAT_LAUNCH(k_scan_tile_sums, dim3((unsigned)ntiles), dim3(DRAIN_NT), 0, st, counts, ntpl, sums);
+    FSTAT_LAUNCH(k_scan_sums, dim3(1), dim3(DRAIN_NT), 0, st, sums, ntiles);
+  }
+  FSTAT_LAUNCH(k_scan_apply, dim3((unsigned)ntiles), dim3(DRAIN_NT), 0, st, counts, ntpl,
+               ntiles > 1 ? sums : nullptr, off);
   FSTAT_LAUNCH(k_drain_scatter, dim3(gblk), dim3(DRAIN_NT), 0, st, p->d_cand, stored, ds, nsearch, search0, nseg, off,
                rank, grouped, flags);
   FSTAT_LAUNCH(k_drain_order, dim3((unsigned)std::min<long long>(ntpl, 1LL << 18)), dim3(DRAIN_NT), 0, st, grouped, off,
                ntpl, p->d_cand, flags);
-  FSTAT_LAUNCH(k_drain_order_long, dim3((unsigned)std::min<long long>(ntpl, 2LL * p->n_cu)), dim3(DRAIN_LONG_NT), 0,
-               st, grouped, off, ntpl, p->d_cand, flags + 1);
+  if (stored > DRAIN_SEG_MAX)   // no range can be longer otherwise
+    FSTAT_LAUNCH(k_drain_order_long, dim3((unsigned)std::min<long long>(ntpl, 2LL * p->n_cu)), dim3(DRAIN_LONG_NT), 0,
+                 st, grouped, off, ntpl, p->d_cand, flags + 1);
   HIP_TRY(p, launch_status(), "drain ordering launch");
   return FSTAT_OK;
 }
