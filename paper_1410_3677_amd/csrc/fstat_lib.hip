@@ -1252,6 +1252,10 @@ void vet_prepare(fstat_vet_t v, hipStream_t st) {
 constexpr int INFER_SPLITS = 4;
 static_assert((long)INFER_SPLITS * 8192 * vet::H <= VET_SCRATCH, "split-K partials of a full batch fit the scratch");
 static_assert(vet::X % (INFER_SPLITS * vet::GW_K) == 0, "K splits of whole stages");
+static_assert(vet::X % (INFER_SPLITS * 32 * vet::GR_DEPTH) == 0, "K splits of whole rounds");
+// patches up to which the product takes wavefronts of their own (k_gemm_nt_rows) instead of
+// 128-row tiles: 16 against 24 us at 512, 30 against 25 at 1024
+constexpr int DENSE_ROWS_MAX = 512;
 void vet_conv_stage(fstat_vet_t v, const float* patches, int n, uint16_t* x, hipStream_t st) {
   using namespace vet;
   const long items = (long)n * CV_ITEMS;
@@ -1262,8 +1266,12 @@ void vet_conv_stage(fstat_vet_t v, const float* patches, int n, uint16_t* x, hip
 void vet_dense_stage(fstat_vet_t v, const uint16_t* x, int n, float* out, hipStream_t st, CandEntry* cand) {
   using namespace vet;
   const int nbp = (n + GW_M - 1) / GW_M * GW_M;
-  FSTAT_LAUNCH(k_gemm_nt_wide, dim3(1, nbp / GW_M, INFER_SPLITS), dim3(GW_NT), 0, st, nbp, X, x, v->wc.w4b, v->scratch,
-               X / INFER_SPLITS);
+  if (n <= DENSE_ROWS_MAX)
+    FSTAT_LAUNCH(k_gemm_nt_rows, dim3(H / 64, (n + 15) / 16, INFER_SPLITS), dim3(256), 0, st, nbp, X, x, v->wc.w4b,
+                 v->scratch, X / INFER_SPLITS);
+  else
+    FSTAT_LAUNCH(k_gemm_nt_wide, dim3(1, nbp / GW_M, INFER_SPLITS), dim3(GW_NT), 0, st, nbp, X, x, v->wc.w4b, v->scratch,
+                 X / INFER_SPLITS);
   const long count = (long)nbp * H;
   // the split-K sum, the two small layers and the score in one launch
   FSTAT_LAUNCH(k_vet_head_infer<INFER_SPLITS>, dim3((unsigned)((n + HD_NP - 1) / HD_NP)), dim3(256), 0, st,

@@ -413,6 +413,40 @@ __global__ void __launch_bounds__(GW_NT) k_gemm_nt_wide(int M, int K, const uint
       for (int i = 0; i < 4; ++i) Cz[(long)(m0 + wm + 16 * a + kq + i) * H + wn + 16 * c + r16] = acc[a][c][i];
 }
 
+// The same product for few rows, with the same sums: a wavefront forms one 16 x 16 tile of a
+// split straight from global memory, GR_DEPTH steps of K ahead; a workgroup's four wavefronts
+// share their rows of A.  The tiled kernel takes 24 us however few its rows are (a workgroup
+// covers 128, and the LDS traffic of its 32 stages bounds it); this one 16 us up to 512 rows,
+// bound by the latency of rows 16 KB apart (17 us eight steps ahead), 30 at 1024 and 59 at 2048.
+constexpr int GR_DEPTH = 16;
+__global__ void __launch_bounds__(256) k_gemm_nt_rows(int M, int K, const uint16_t* __restrict__ A,
+                                                      const uint16_t* __restrict__ B, float* __restrict__ Cm,
+                                                      int kchunk) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, r16 = lane & 15, k8 = 8 * (lane >> 4);
+  const int m0 = 16 * blockIdx.y, n0 = 16 * (4 * blockIdx.x + w);
+  const uint16_t* a = A + (long)(m0 + r16) * K + (long)blockIdx.z * kchunk + k8;
+  const uint16_t* b = B + (long)(n0 + r16) * K + (long)blockIdx.z * kchunk + k8;
+  v8s fa[GR_DEPTH], fb[GR_DEPTH];
+#pragma unroll
+  for (int d = 0; d < GR_DEPTH; ++d) {
+    fa[d] = *reinterpret_cast<const v8s*>(a + 32 * d);
+    fb[d] = *reinterpret_cast<const v8s*>(b + 32 * d);
+  }
+  v4f acc = {0.f, 0.f, 0.f, 0.f};
+  for (int k0 = 0; k0 < kchunk; k0 += 32 * GR_DEPTH) {
+#pragma unroll
+    for (int d = 0; d < GR_DEPTH; ++d) {
+      acc = mfma32(fa[d], fb[d], acc);
+      const int k = min(k0 + 32 * (GR_DEPTH + d), kchunk - 32);   // past the end: the last step again, unused
+      fa[d] = *reinterpret_cast<const v8s*>(a + k);
+      fb[d] = *reinterpret_cast<const v8s*>(b + k);
+    }
+  }
+  float* c = Cm + (long)blockIdx.z * M * H;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) c[(long)(m0 + 4 * (lane >> 4) + i) * H + n0 + r16] = acc[i];
+}
+
 // The dense layers after the 8192 -> 128 product, for HD_NP patches per workgroup: the
 // split-K partial sums added in split order, bias, ReLU and BF16 rounding (a4), the
 // 128 -> 128 layer on the matrix cores (BF16 a4 and w5, FP32 accumulation), bias and ReLU
