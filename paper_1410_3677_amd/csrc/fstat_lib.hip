@@ -833,7 +833,21 @@ static hipError_t launch_stream_b(const Dev<float>& d, const SegInfo& si, const 
 // transforms stay.  The patch capture stores the rows of the full-rate second pass.
 constexpr long DEC_MIN_POINTS = 1L << 24;   // templates times transform points
 constexpr int DEC_MIN_FDOT = 5;             // spindowns per sky position
+// points per launch at least, mixed precision and FP64: the launch pair of the path not taken
+// costs 10 us, 20 mixed or 6 FP64 templates' gain at 2^18 points (one template per launch:
+// 17 us decimated, 13 at the full rate)
+constexpr long DEC_LAUNCH_POINTS = 1L << 23, DEC_LAUNCH_POINTS_FP64 = 1L << 21;
+
+// The plan's B templates per launch are sized for its longest transform; when the library
+// chose B, a segment with a shorter transform fits proportionally more templates in the
+// same intermediate memory (and in the launch-sized 2F rows of the patch capture), so it
+// takes fewer, fuller launches.
+static int launch_templates(fstat_plan_t p, const SegInfo& si) {
+  return p->scale_B ? (int)std::min<long>((long)p->B * (p->TL_max / si.tL), 4096L) : p->B;
+}
 static bool use_dec(fstat_plan_t p, const SegInfo& si, const Grid& g, int mode) {
+  const long nt = std::min<long>(launch_templates(p, si), (long)std::min(p->Sb, g.nsky) * g.nfdot);
+  if (nt * si.tL < (p->fp64 ? DEC_LAUNCH_POINTS_FP64 : DEC_LAUNCH_POINTS)) return false;
   return si.dec && p->dn_max && (p->fp64 || p->variant_b == 1) && !(mode == 0 && p->vet) && g.nfdot >= DEC_MIN_FDOT &&
          (long)g.nsky * g.nfdot * si.tL >= DEC_MIN_POINTS;
 }
@@ -880,11 +894,7 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
   }
   const int total = nb * nfdot;
   cx<T>* tbuf = d.tmpl();
-  // the plan's B templates per launch are sized for its longest transform; when the
-  // library chose B, a segment with a shorter transform fits proportionally more templates
-  // in the same intermediate memory (and in the launch-sized 2F rows of the patch capture),
-  // so it takes fewer, fuller launches
-  const int Bs = p->scale_B ? (int)std::min<long>((long)p->B * (p->TL_max / si.tL), 4096L) : p->B;
+  const int Bs = launch_templates(p, si);
   for (int t0 = 0; t0 < total; t0 += Bs) {
     const int nt = std::min(Bs, total - t0);
     ta.t0 = td.t0 = t0;

@@ -1,13 +1,13 @@
-// Kernels of the candidate-vetting network (forward, backward, Adam) and of the
-// patch capture that follows the F-statistic kernel.
+// Kernels of the candidate-vetting network's scoring (training: fstat_vet_train.hpp) and
+// of the patch capture that follows the F-statistic kernel.
 //
 // Network: u = log(1 + 2F) - log 5 over a 256-bin patch; three "same" convolutions
 // of width 7 (1 -> 32 -> 32 -> 32 channels, ReLU); flatten position-major
 // (x[p*32 + c]); dense 8192 -> 128 -> 128 -> 1 (ReLU, ReLU, logit).  Activations
 // are stored position-major [n][256][32].  Convolutions 2 and 3, the dense layers
 // and all their gradients are products of BF16 matrices with FP32 accumulation on
-// the matrix cores (v_mfma_f32_16x16x16_bf16); the first convolution (one input
-// channel) and the last dense layer are plain FP32 loops.
+// the matrix cores; the last dense layer, and in training the first convolution (one
+// input channel), are plain FP32 loops.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -19,7 +19,7 @@ namespace vet {
 constexpr int L = 256;        // patch length
 constexpr int C = 32;         // channels
 constexpr int KW = 7;         // kernel width
-constexpr int KC = KW * C;    // im2col width (224)
+constexpr int KC = KW * C;    // inputs of one convolution output (224)
 constexpr int H = 128;        // hidden units
 constexpr int X = L * C;      // flattened conv output (8192)
 
@@ -47,7 +47,6 @@ __device__ __forceinline__ v8s lds8(const uint16_t* p) {
 
 // FP32 -> BF16, round to nearest even (the hardware conversion of gfx950)
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
 // Network input u = log(1 + 2F) - log 5, with the hardware logarithm (absolute error
 // about 1e-7, far below the BF16 rounding of the layers that follow).

@@ -118,7 +118,7 @@ def test_candidates_follow_the_spectra(torch, ib):
     want = torch.nonzero(spec > 20.0).cpu().numpy()
     near = int(((spec - 20.0).abs() < 20.0 * TOL).sum())
     for bad in (None, HUGE, -HUGE, math.inf, math.nan):
-        plan = make_plan([seg], interbinning=ib, threshold_2F=20.0, templates_per_launch=50, skies_per_batch=3)
+        plan = make_plan([seg], interbinning=ib, threshold_2F=20.0, templates_per_launch=150, skies_per_batch=3)
         plan.search_batch(0, dev(al), dev(de), dev(fd if bad is None else np.append(fd, bad)))
         recs, keys, _ = plan.candidates()
         m = keys["fdot_idx"] < len(fd)
