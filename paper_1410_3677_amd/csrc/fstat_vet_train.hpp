@@ -20,8 +20,8 @@
 // kernels replace, bit for bit: Adam's first steps turn the last bit of a gradient into
 // activations that round the other way.
 // 256 patches: 740 us with 55 launches, which moved about 600 MB (half of it im2col matrices);
-// 84 us here, with about 120 MB in eight launches.  Now bound by latency: one workgroup per
-// CU or fewer in each launch, 5 to 17 us each.
+// 79 us here, with about 120 MB in eight launches.  Now bound by latency: one workgroup per
+// CU or fewer in each launch, 5 to 14 us each.
 #pragma once
 
 #include "fstat_vet.hpp"
@@ -554,8 +554,25 @@ __global__ void __launch_bounds__(256) k_train_dw_conv(const uint16_t* __restric
     __syncthreads();
     if ((s + 1) * L < end) gload(s + 1);
     const int p0 = (int)(max(beg, s * L) - s * L), p1 = (int)(min(end, (s + 1) * L) - s * L);
-#pragma unroll 4
-    for (int p = p0; p < p1; p += 16) {
+    int p = p0;
+    for (; p + 64 <= p1; p += 64) {
+      // four steps' operands on their way before the first product (17 us for the launch at 256
+      // patches with each step's reads before its products, 12 like this)
+      v4s fd[4], fa[4][4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        fd[q] = read_tr(bd + (p + 16 * q + 3 + tr) * TR_LD + co + tc);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          fa[q][t] = read_tr(ba + (p + 16 * q + min(t0 + t, KW - 1) + tr) * TR_LD + ci + tc);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = mfma16(fa[q][t], fd[q], acc[t]);
+    }
+    for (; p < p1; p += 16) {
       const v4s fd = read_tr(bd + (p + 3 + tr) * TR_LD + co + tc);
 #pragma unroll
       for (int t = 0; t < 4; ++t)
