@@ -283,7 +283,8 @@ __global__ void __launch_bounds__(DRAIN_LONG_NT) k_drain_order_long(const CandEn
   }
 }
 
-// 5. the records and keys of the ordered entries, formed as the host would form them (the
+// 5. the records and keys of the ordered entries (none if the ordering refused one: bad, which
+// goes to page-locked `flags` for the host), formed as the host would form them (the
 // paper's five numbers from the search's lists, the integer key, the vetting score), for a
 // copy straight into the caller's arrays
 struct DrainList {
@@ -348,7 +349,14 @@ __device__ __forceinline__ fstat_candidate drain_record(const CandEntry& c, cons
 
 __global__ void k_drain_records(const CandEntry* __restrict__ ent, long long n, const DrainList* __restrict__ lists,
                                 int search0, const DrainSeg* __restrict__ segs, int scored,
-                                fstat_candidate* __restrict__ out, fstat_candidate_key* __restrict__ keys) {
+                                fstat_candidate* __restrict__ out, fstat_candidate_key* __restrict__ keys,
+                                const unsigned* __restrict__ bad, unsigned* flags) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    flags[0] = bad[0];
+    flags[1] = bad[1];
+    __threadfence_system();
+  }
+  if (bad[0]) return;   // an entry outside its search has no list to form a record from
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
     const CandEntry c = ent[i];
     if (keys) keys[i] = drain_key(c, scored);
@@ -375,10 +383,7 @@ struct SmallHead {
   unsigned flags[2], pad[2];                   // the general drain's flags
 };
 
-// The count of a general drain, unless its flags say that it failed.
-__global__ void k_drain_reset(unsigned long long* __restrict__ count, const unsigned* __restrict__ bad) {
-  if (!bad[0] && !bad[1]) *count = 0ull;
-}
+__global__ void k_drain_reset(unsigned long long* __restrict__ count) { *count = 0ull; }
 
 __global__ void __launch_bounds__(SMALL_NT) k_drain_small(SmallDrain a, const CandEntry* __restrict__ cand,
                                                           unsigned long long* __restrict__ count,

@@ -2166,8 +2166,6 @@ static fstat_status order_on_device(fstat_plan_t p, long long stored, const Drai
     std::memcpy(tab.data() + hs.size() * sizeof(DrainSearch) + (size_t)i * sizeof l, &l, sizeof l);
   }
   HIP_TRY(p, hipMemcpy(ds, tab.data(), tab.size(), hipMemcpyHostToDevice), "drain tables");
-  *lists = (const DrainList*)(ds + nsearch);
-  *bad = flags;
   const hipStream_t st = nullptr;
   const unsigned gblk = (unsigned)std::min<long long>((stored + DRAIN_NT - 1) / DRAIN_NT, 1LL << 20);
   FSTAT_LAUNCH(k_drain_zero, dim3((unsigned)std::min<long long>((ntpl + 2 + DRAIN_NT - 1) / DRAIN_NT, 1LL << 20)),
@@ -2189,6 +2187,8 @@ static fstat_status order_on_device(fstat_plan_t p, long long stored, const Drai
     FSTAT_LAUNCH(k_drain_order_long, dim3((unsigned)std::min<long long>(ntpl, 2LL * p->n_cu)), dim3(DRAIN_LONG_NT), 0,
                  st, grouped, off, ntpl, p->d_cand, flags + 1);
   HIP_TRY(p, launch_status(), "drain ordering launch");
+  *lists = (const DrainList*)(ds + nsearch);
+  *bad = flags;
   return FSTAT_OK;
 }
 
@@ -2212,25 +2212,24 @@ static fstat_status form_on_device(fstat_plan_t p, long long nout, const DrainLi
   fstat_candidate* drec = out ? (fstat_candidate*)(w + o_rec) : nullptr;
   fstat_candidate_key* dkey = keys ? (fstat_candidate_key*)(w + o_key) : nullptr;
   const unsigned blk = (unsigned)std::min<long long>((nout + DRAIN_NT - 1) / DRAIN_NT, 1LL << 20);
-  FSTAT_LAUNCH(k_drain_records, dim3(blk), dim3(DRAIN_NT), 0, (hipStream_t)nullptr, p->d_cand, nout, dl, search0, p->d_segs,
-               p->scored ? 1 : 0, drec, dkey);
-  HIP_TRY(p, launch_status(), "drain records launch");
-  // copies, the ordering's flags and the count's reset (none where the flags are set), waited
-  // for once
   const hipStream_t st = nullptr;
-  unsigned* hf = p->small->flags;
+  FSTAT_LAUNCH(k_drain_records, dim3(blk), dim3(DRAIN_NT), 0, st, p->d_cand, nout, dl, search0, p->d_segs,
+               p->scored ? 1 : 0, drec, dkey, bad, p->small->flags);
+  HIP_TRY(p, launch_status(), "drain records launch");
+  // the ordering's flags before anything reaches the caller's arrays
+  HIP_TRY(p, hipStreamSynchronize(st), "drain ordering");
+  const unsigned* hf = p->small->flags;
+  if (hf[0]) return fail(p, FSTAT_E_STATE, "a stored candidate's key lies outside its search");
+  if (hf[1]) return fail(p, FSTAT_E_STATE, "a template's candidates repeat a bin");
   if (out)
     HIP_TRY(p, hipMemcpyAsync(out, drec, (size_t)nout * sizeof(fstat_candidate), hipMemcpyDeviceToHost, st),
             "record copy");
   if (keys)
     HIP_TRY(p, hipMemcpyAsync(keys, dkey, (size_t)nout * sizeof(fstat_candidate_key), hipMemcpyDeviceToHost, st),
             "key copy");
-  HIP_TRY(p, hipMemcpyAsync(hf, bad, 2 * sizeof(unsigned), hipMemcpyDeviceToHost, st), "drain flags");
-  FSTAT_LAUNCH(k_drain_reset, dim3(1), dim3(1), 0, st, p->d_count, bad);
+  FSTAT_LAUNCH(k_drain_reset, dim3(1), dim3(1), 0, st, p->d_count);
   HIP_TRY(p, launch_status(), "count reset");
   HIP_TRY(p, hipStreamSynchronize(st), "drain");
-  if (hf[0]) return fail(p, FSTAT_E_STATE, "a stored candidate's key lies outside its search");
-  if (hf[1]) return fail(p, FSTAT_E_STATE, "a template's candidates repeat a bin");
   return FSTAT_OK;
 }
 
