@@ -184,6 +184,7 @@ struct fstat_plan_s {
   bool profiling = false;
   // every launch on the caller's stream (no sky stream, no events): the static-scratch call
   bool single_stream = false;
+  bool capturing = false;        // launches go into the plan's graph, not to the device
   // this device's copy of the static scratch (address taken when the plan was made)
   void* static_ws = nullptr;
   std::string static_err;
@@ -1098,7 +1099,9 @@ static fstat_status search_impl(fstat_plan_t p, int segment, const Grid& g, int 
   return FSTAT_OK;
 }
 
-// All launches of one search call (begin-search marker first).
+// All launches of one search call (begin-search marker first).  A search is counted
+// (search_count, the host's copy of the device's index) once its marker is on its way: here,
+// or where the graph that holds the marker is launched.
 static fstat_status enqueue_search(fstat_plan_t p, int segment, const Grid& g, int mode, void* spectrum,
                                    hipStream_t st) {
   if (!p->sstream && !p->single_stream) {
@@ -1112,6 +1115,7 @@ static fstat_status enqueue_search(fstat_plan_t p, int segment, const Grid& g, i
   if (mode == 0) {
     FSTAT_LAUNCH(k_begin_search, dim3(1), dim3(1), 0, st, p->d_search_next);
     HIP_TRY(p, launch_status(), "search marker launch");
+    if (!p->capturing) p->search_count++;
   }
   return p->fp64 ? search_impl<double>(p, segment, g, mode, spectrum, st)
                  : search_impl<float>(p, segment, g, mode, spectrum, st);
@@ -1149,7 +1153,9 @@ static fstat_status run_search(fstat_plan_t p, int segment, const Grid& grid, in
     g.profiled = p->profiling;
     const size_t nprof = p->prof.size();
     HIP_TRY(p, hipStreamBeginCapture(p->gstream, hipStreamCaptureModeThreadLocal), "graph capture");
+    p->capturing = true;
     fstat_status r = enqueue_search(p, segment, grid, mode, spectrum, p->gstream);
+    p->capturing = false;
     hipError_t ec = hipStreamEndCapture(p->gstream, &g.graph);
     // the event pairs recorded during capture belong to the graph's nodes
     g.events.assign(p->prof.begin() + nprof, p->prof.end());
@@ -1179,6 +1185,7 @@ static fstat_status run_search(fstat_plan_t p, int segment, const Grid& grid, in
     ge = &p->graphs.back();
   }
   HIP_TRY(p, hipGraphLaunch(ge->exec, p->gstream), "graph launch");
+  if (mode == 0) p->search_count++;
   // the graph re-records its own event pairs on every replay: report this replay's
   // durations (copies of the handles, which the graph entry owns)
   for (const auto& pr : ge->events) p->prof.push_back({pr.cls, pr.a, pr.b, true});
@@ -1837,6 +1844,15 @@ static fstat_status record_search(fstat_plan_t plan, const Grid& g, hipStream_t 
   return FSTAT_OK;
 }
 
+// A recorded search, run.  One that failed before its marker is no search of the device's,
+// and its record goes.
+static fstat_status run_recorded(fstat_plan_t plan, int segment, const Grid& g, hipStream_t st) {
+  const int before = plan->search_count;
+  const fstat_status r = run_search(plan, segment, g, 0, nullptr, st);
+  if (plan->search_count == before) plan->searches.pop_back();
+  return r;
+}
+
 // The searches since the last drain are done with.
 static void forget_searches(fstat_plan_t plan) {
   plan->searches.clear();
@@ -1864,9 +1880,7 @@ fstat_status fstat_search_batch(fstat_plan_t plan, int32_t segment, const double
   if ((r = record_search(plan, g, st)) != FSTAT_OK) return r;
   plan->last_stream = st;
   plan->used_stream = true;
-  r = run_search(plan, segment, g, 0, nullptr, st);
-  plan->search_count++;
-  return r;
+  return run_recorded(plan, segment, g, st);
 }
 
 fstat_status fstat_twoF_spectrum(fstat_plan_t plan, int32_t segment, const double* alpha, const double* delta,
@@ -2062,9 +2076,7 @@ fstat_status fstat_search_lattice(fstat_plan_t plan, int32_t segment, const fsta
   plan->used_stream = true;
   if (spectrum) return run_search(plan, segment, g, 1, spectrum, st);
   if ((r = record_search(plan, g, st)) != FSTAT_OK) return r;
-  r = run_search(plan, segment, g, 0, nullptr, st);
-  plan->search_count++;
-  return r;
+  return run_recorded(plan, segment, g, st);
 }
 
 template <typename T>

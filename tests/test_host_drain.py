@@ -58,3 +58,49 @@ assert r == F.OK and n == found
 assert H.names()[-2:] == ["k_drain_records", "k_drain_reset"]
 assert (out == 0x11).all() and (keys == 0x11).all()
 """)
+
+
+@pytest.mark.parametrize("failing,use_graph,begun", [
+    ("hipStreamBeginCapture", 1, False), ("hipStreamEndCapture", 1, False), ("hipGraphInstantiate", 1, False),
+    ("hipGraphLaunch", 1, False), ("k_sky_setup", 1, False), ("k_begin_search", 0, False), ("k_sky_setup", 0, True)])
+def test_a_search_that_never_began_is_not_counted(stub, failing, use_graph, begun):
+    """The drain's first search index is the device's: a call that fails before its marker
+    reaches the device is neither numbered nor recorded, one that fails after it is both."""
+    hip_stub.run(stub, f"""
+import ctypes
+F, failing = H.F, {failing!r}
+plan = H.plan([4096], use_graph={use_graph})
+device, pending, drained = 0, [], []          # the device's index; launches of the plan's graph; drains
+def begin(args):
+    global device
+    if {use_graph}: pending[:] = [1]
+    else: device += 1
+def launched(args):
+    global device
+    device += sum(pending)
+def small(args):                              # SmallDrain: nsearch, search0; head: count, bad, done
+    a = ctypes.cast(args[0], ctypes.POINTER(ctypes.c_int))
+    drained.append((a[0], a[1]))
+    head = ctypes.cast(ctypes.cast(args[4], ctypes.POINTER(ctypes.c_void_p))[0], ctypes.POINTER(ctypes.c_ulonglong))
+    head[0], head[1] = 0, 1 << 32
+H.on.update(k_begin_search=begin, hipGraphLaunch=launched, k_drain_small=small)
+assert H.search(plan, 3, 4) == F.OK
+ok = H.on.get(failing)
+if failing.startswith("hip"):
+    H.on[failing] = lambda args: 1
+else:                                         # a launch that fails shows at the next look at the errors
+    def launch(args):
+        if failing == "k_begin_search": pass
+        else: (ok or (lambda a: 0))(args)
+        H.on["hipGetLastError"] = lambda a: 1
+    H.on[failing] = launch
+assert H.search(plan, 5, 6) == F.E_DEVICE     # other lists: a graph of its own
+H.on.pop("hipGetLastError", None)
+if ok: H.on[failing] = ok
+else: del H.on[failing]
+assert H.search(plan, 7, 8) == F.OK
+out, n = ctypes.create_string_buffer(64 * 1024), ctypes.c_longlong()
+assert H.lib.fstat_candidates(plan, out, None, 16, ctypes.byref(n)) == F.OK
+assert device == {2 + begun}
+assert drained == [(device, 0)], (drained, device)
+""")
