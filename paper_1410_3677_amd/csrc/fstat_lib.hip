@@ -2466,6 +2466,9 @@ fstat_status fstat_autotune(fstat_plan_t plan, int32_t segment, double budget_ms
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   (void)hipFree(dl);
+  // captured searches hold the batch sizes and the workspace of before, whose address the next
+  // one may have again
+  drop_graphs(plan);
   plan->opt.use_graph = graph0;
   plan->profiling = prof0;
   plan->B = bestc.B;

@@ -12,7 +12,7 @@
 
 namespace {
 std::map<const void*, std::string> kernels;
-std::map<size_t, void*> freed;          // the last block given back of each size
+std::multimap<size_t, void*> freed;     // blocks given back
 std::map<void*, size_t> sizes;
 dim3 cfg_grid, cfg_block;
 size_t cfg_lds;
@@ -54,22 +54,22 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
 hipError_t hipMalloc(void** p, size_t n) {
   const hipError_t e = call("hipMalloc");
   if (e != hipSuccess) return e;
-  // a block of a size given back before comes at the same address again
-  auto it = freed.find(n);
+  // the smallest block given back that is large enough comes at the same address again
+  auto it = freed.lower_bound(n);
   if (it != freed.end()) {
     *p = it->second;
+    sizes[*p] = it->first;
     freed.erase(it);
   } else {
-    *p = std::aligned_alloc(4096, (n + 4095) & ~(size_t)4095);   // untouched pages take no memory
+    sizes[*p = std::aligned_alloc(4096, (n + 4095) & ~(size_t)4095)] = n;   // untouched pages take no memory
   }
-  sizes[*p] = n;
   return hipSuccess;
 }
 hipError_t hipFree(void* p) {
   if (!p) return hipSuccess;
   auto it = sizes.find(p);
   if (it == sizes.end()) return hipErrorInvalidValue;
-  freed[it->second] = p;
+  freed.insert({it->second, p});
   sizes.erase(it);
   return hipSuccess;
 }
