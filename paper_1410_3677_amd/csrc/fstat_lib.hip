@@ -831,7 +831,8 @@ static hipError_t launch_stream_b(const Dev<float>& d, const SegInfo& si, const 
 // a template's memory traffic and arithmetic (0.93 against 1.47 us at 2^18 points; FP64 2.8
 // against 4.65) and cost the filter, once a sky position (2.2 us; FP64 2.9), and the launches of the path not taken (10 us a
 // launch pair); where those weigh more, with few spindowns or in small calls, the full-rate
-// transforms stay.  The patch capture stores the rows of the full-rate second pass.
+// transforms stay.  With a vetter attached everything does: the patch capture stores the rows
+// of the full-rate second pass, and windows of a spectrum of the same plan score like them.
 constexpr long DEC_MIN_POINTS = 1L << 24;   // templates times transform points
 constexpr int DEC_MIN_FDOT = 5;             // spindowns per sky position
 // points per launch at least, mixed precision and FP64: the launch pair of the path not taken
@@ -846,10 +847,10 @@ constexpr long DEC_LAUNCH_POINTS = 1L << 23, DEC_LAUNCH_POINTS_FP64 = 1L << 21;
 static int launch_templates(fstat_plan_t p, const SegInfo& si) {
   return p->scale_B ? (int)std::min<long>((long)p->B * (p->TL_max / si.tL), 4096L) : p->B;
 }
-static bool use_dec(fstat_plan_t p, const SegInfo& si, const Grid& g, int mode) {
+static bool use_dec(fstat_plan_t p, const SegInfo& si, const Grid& g) {
   const long nt = std::min<long>(launch_templates(p, si), (long)std::min(p->Sb, g.nsky) * g.nfdot);
   if (nt * si.tL < (p->fp64 ? DEC_LAUNCH_POINTS_FP64 : DEC_LAUNCH_POINTS)) return false;
-  return si.dec && p->dn_max && (p->fp64 || p->variant_b == 1) && !(mode == 0 && p->vet) && g.nfdot >= DEC_MIN_FDOT &&
+  return si.dec && p->dn_max && (p->fp64 || p->variant_b == 1) && !p->vet && g.nfdot >= DEC_MIN_FDOT &&
          (long)g.nsky * g.nfdot * si.tL >= DEC_MIN_POINTS;
 }
 
@@ -1059,7 +1060,7 @@ static fstat_status search_impl(fstat_plan_t p, int segment, const Grid& g, int 
     // profiling on, the sky stage stays on `st`, so that each timed kernel runs alone.
     const int nbatch = (nsky + p->Sb - 1) / p->Sb;
     hipStream_t sst = (p->profiling || p->single_stream) ? st : p->sstream;
-    const bool dec = use_dec(p, si, g, mode);
+    const bool dec = use_dec(p, si, g);
     if (dec) {
       FSTAT_LAUNCH(k_route, dim3(1), dim3(1024), 0, st, g.fdot, g.nfdot, si.s.dt, g.w_spin, g.nsky, g.s_lo, g.m11,
                    (int)si.s.n, d.route());

@@ -1,11 +1,13 @@
 // The upsampling and spline of full-rate calls in mixed precision (single-precision series):
-// searches with a vetting network attached, and the small calls whose templates are not
-// decimated, spectra of single templates above all.  The network scores 2F windows of both,
-// and its three layers of BF16 roundings turn another rounding of 2F's last place into up to
-// 2e-3 of a score; so that the scores of a captured window and of the same window read from a
-// spectrum stay equal, and what they were bit for bit, these calls share the transforms (four
-// passes, one series per LDS column) and the spline (by its moments, a 33-tap filter) that
-// fstat_sky.hpp replaces with faster ones of another rounding everywhere else.
+// every call of a plan with a vetting network attached, and the small calls of other plans
+// whose templates are not decimated, spectra of single templates above all.  The network
+// scores 2F windows of both, and its three layers of BF16 roundings turn another rounding of
+// 2F's last place into up to 2e-3 of a score; so that a captured window and the same window
+// read from a spectrum (of a plan with a vetter, or a small one of any plan) stay equal, and
+// what they were bit for bit, these calls share the transforms (four passes, one series per
+// LDS column) and the spline (by its moments, a 33-tap filter) that fstat_sky.hpp replaces
+// with faster ones of another rounding everywhere else.  A large spectrum of a plan without a
+// vetter is decimated, and agrees to rounding.
 #pragma once
 
 #include "fstat_sky.hpp"

@@ -1,0 +1,31 @@
+"""Which kernels a call launches, on the stand-in HIP runtime (tests/hip_stub.py)."""
+import pytest
+
+from tests import hip_stub
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    return hip_stub.build(tmp_path_factory.mktemp("stub"))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_a_plan_with_a_vetter_stays_at_the_full_rate(stub, precision):
+    """Windows captured by a search and windows of a spectrum of the same plan come from the
+    same transforms, however large the spectrum."""
+    hip_stub.run(stub, f"""
+import ctypes
+F = H.F
+plan = H.plan([86164], precision={precision}, use_graph=0)
+def decimated(call):
+    H.launches.clear()
+    assert call(plan, 64, 64) == F.OK
+    return any(n.startswith("k_tmpl_a_dec") for n in H.names())
+vet = ctypes.c_void_p()
+assert H.lib.fstat_vet_create(512, ctypes.byref(vet)) == F.OK
+assert decimated(H.search) and decimated(H.spectrum)
+assert H.lib.fstat_plan_attach_vetter(plan, vet, 100) == F.OK
+assert not decimated(H.search) and not decimated(H.spectrum)
+assert H.lib.fstat_plan_attach_vetter(plan, None, 0) == F.OK
+assert decimated(H.search) and decimated(H.spectrum)
+""")
