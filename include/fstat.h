@@ -215,6 +215,10 @@ fstat_status fstat_twoF_spectrum_static(fstat_plan_t plan, int32_t segment, cons
  *   za, zb n complex: amplitude- and phase-demodulated series
  *   ua, ub nfft complex: 2x upsampled series
  *   zta, ztb n complex: resampled series on the barycentric grid
+ * The kernels are those of the plan's calls with decimated template transforms (see
+ * fstat_plan_info).  A mixed-precision plan that never decimates this segment's (a vetter
+ * attached, bins beyond nfft/2, a workspace budget without room) shows those of its
+ * full-rate calls, which round differently in the last place; FP64 has one set.
  * Synchronous: waits for `stream`, runs the sky stage on it and returns once the
  * outputs are written.  Uses the plan's workspace (allocating it on first use). */
 fstat_status fstat_sky_stages(fstat_plan_t plan, int32_t segment, double alpha, double delta,

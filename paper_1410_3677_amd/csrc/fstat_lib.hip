@@ -847,11 +847,14 @@ constexpr long DEC_LAUNCH_POINTS = 1L << 23, DEC_LAUNCH_POINTS_FP64 = 1L << 21;
 static int launch_templates(fstat_plan_t p, const SegInfo& si) {
   return p->scale_B ? (int)std::min<long>((long)p->B * (p->TL_max / si.tL), 4096L) : p->B;
 }
+// Whether the plan's large calls on segment si do.
+static bool can_dec(fstat_plan_t p, const SegInfo& si) {
+  return si.dec && p->dn_max && (p->fp64 || p->variant_b == 1) && !p->vet;
+}
 static bool use_dec(fstat_plan_t p, const SegInfo& si, const Grid& g) {
   const long nt = std::min<long>(launch_templates(p, si), (long)std::min(p->Sb, g.nsky) * g.nfdot);
   if (nt * si.tL < (p->fp64 ? DEC_LAUNCH_POINTS_FP64 : DEC_LAUNCH_POINTS)) return false;
-  return si.dec && p->dn_max && (p->fp64 || p->variant_b == 1) && !p->vet && g.nfdot >= DEC_MIN_FDOT &&
-         (long)g.nsky * g.nfdot * si.tL >= DEC_MIN_POINTS;
+  return can_dec(p, si) && g.nfdot >= DEC_MIN_FDOT && (long)g.nsky * g.nfdot * si.tL >= DEC_MIN_POINTS;
 }
 
 template <typename T>
@@ -2084,14 +2087,20 @@ template <typename T>
 static fstat_status sky_stages_impl(fstat_plan_t plan, const SegInfo& si, const double* ad, double* abc, void* za,
                                     void* zb, void* ua, void* ub, void* zta, void* ztb, hipStream_t st) {
   Dev<T> d(plan);
-  fstat_status r = run_sky_batch<T>(plan, d, si, ad, ad + 1, 0, 1, false, false, st, true);
+  // the stage of the plan's large calls; of the full-rate ones in a mixed-precision plan that
+  // has no others
+  const bool full_rate = sizeof(T) == 4 && !can_dec(plan, si);
+  fstat_status r = run_sky_batch<T>(plan, d, si, ad, ad + 1, 0, 1, false, full_rate, st, true);
   if (r != FSTAT_OK) return r;
   const int n = (int)si.s.n, L = si.nfft;
+  const long M = si.M;
   const cx_pair<T>* z = d.sky();
-  const cx_pair<T>* o = z + si.M;
+  // the odd samples: pairs behind the series, or (full rate) the last of three arrays of planes
+  const cx<T>* o = (const cx<T>*)(z + M) + (full_rate ? 4 * M : 0);
   const dim3 gn((unsigned)((n + NT - 1) / NT)), gl((unsigned)((L + NT - 1) / NT));
   FSTAT_LAUNCH((k_unpair<T>), gn, dim3(NT), 0, st, z, n, (cx<T>*)za, (cx<T>*)zb);
-  FSTAT_LAUNCH((k_upsampled<T>), gl, dim3(NT), 0, st, z, o, n, L, (cx<T>*)ua, (cx<T>*)ub);
+  FSTAT_LAUNCH((k_upsampled<T>), gl, dim3(NT), 0, st, z, o, full_rate ? o + M : o + 1, full_rate ? 1 : 2, n, L,
+               (cx<T>*)ua, (cx<T>*)ub);
   FSTAT_LAUNCH((k_unpair<T>), gn, dim3(NT), 0, st, (const cx_pair<T>*)d.zt(), n, (cx<T>*)zta, (cx<T>*)ztb);
   HIP_TRY(plan, launch_status(), "stage copy");
   if (abc) {

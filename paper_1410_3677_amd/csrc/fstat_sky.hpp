@@ -258,12 +258,16 @@ __global__ void __launch_bounds__(NT) k_unpair(const cx_pair<T>* __restrict__ in
   if (a) a[j] = in[j].a;
   if (b) b[j] = in[j].b;
 }
+// The upsampled series of both, odd samples h of a and b at oa[step h], ob[step h].
 template <typename T>
-__global__ void __launch_bounds__(NT) k_upsampled(const cx_pair<T>* __restrict__ z, const cx_pair<T>* __restrict__ o,
-                                                  int n, int L, cx<T>* __restrict__ a, cx<T>* __restrict__ b) {
-  const int q = blockIdx.x * NT + threadIdx.x;
+__global__ void __launch_bounds__(NT) k_upsampled(const cx_pair<T>* __restrict__ z, const cx<T>* __restrict__ oa,
+                                                  const cx<T>* __restrict__ ob, int step, int n, int L,
+                                                  cx<T>* __restrict__ a, cx<T>* __restrict__ b) {
+  const int q = blockIdx.x * NT + threadIdx.x, h = q >> 1;
   if (q >= L) return;
-  const cx_pair<T> v = upsampled(z, o, q, n);
+  cx_pair<T> v = {mk<T>(0, 0), mk<T>(0, 0)};
+  if (q & 1) v = cx_pair<T>{oa[(long)step * h], ob[(long)step * h]};
+  else if (h < n) v = z[h];
   if (a) a[q] = v.a;
   if (b) b[q] = v.b;
 }

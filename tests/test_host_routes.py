@@ -29,3 +29,22 @@ assert not decimated(H.search) and not decimated(H.spectrum)
 assert H.lib.fstat_plan_attach_vetter(plan, None, 0) == F.OK
 assert decimated(H.search) and decimated(H.spectrum)
 """)
+
+
+def test_sky_stages_are_those_of_the_plans_calls(stub):
+    """The stage-by-stage entry runs the per-sky kernels that the plan's searches run."""
+    hip_stub.run(stub, """
+F = H.F
+def kernels(plan, call):
+    H.launches.clear()
+    assert call() == F.OK
+    return {n for n in H.names() if "k_spline" in n or "fft_pass" in n or "k_sky_cols" in n or "k_sky_rows" in n}
+def stages(plan):
+    return kernels(plan, lambda: H.lib.fstat_sky_stages(plan, 0, 0.1, 0.2, None, H.ptr, H.ptr, *[None] * 5))
+for n, opts in ((30011, {}), (30011, dict(k_max=65536)), (30011, dict(precision=0)), (86164, dict(interbinning=1)),
+                (300007, {}), (300007, dict(interbinning=1))):
+    plan = H.plan([n], use_graph=0, **opts)
+    want = kernels(plan, lambda: H.search(plan, 64, 64))
+    assert want and stages(plan) == want, (n, opts, want)
+    assert any("full::" in k for k in want) == (opts == dict(k_max=65536) or n == 300007 and "interbinning" in opts)
+""")
