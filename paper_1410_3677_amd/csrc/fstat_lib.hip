@@ -143,7 +143,8 @@ struct fstat_plan_s {
   size_t off_xs = 0;   // FP64 with interbinning: the second pass's transforms [B][tL][2]
   long n_max = 0, L_max = 0, M_max = 0;
   long TL_max = 0;             // longest template FFT
-  long dn_max = 0;             // longest decimated series (0: no segment has one)
+  long dn_max = 0;             // longest decimated series (0: no segment has one, or no room for it)
+  int Sb_first = 0, B_first = 0;   // batch sizes that a limit shrinks the library's choice to first
   // tables and candidates
   Tables tab;
   CandEntry* d_cand = nullptr;
@@ -844,16 +845,43 @@ constexpr long DEC_LAUNCH_POINTS = 1L << 23, DEC_LAUNCH_POINTS_FP64 = 1L << 21;
 // chose B, a segment with a shorter transform fits proportionally more templates in the
 // same intermediate memory (and in the launch-sized 2F rows of the patch capture), so it
 // takes fewer, fuller launches.
-static int launch_templates(fstat_plan_t p, const SegInfo& si) {
-  return p->scale_B ? (int)std::min<long>((long)p->B * (p->TL_max / si.tL), 4096L) : p->B;
+static int launch_templates(fstat_plan_t p, const SegInfo& si, int B) {
+  return p->scale_B ? (int)std::min<long>((long)B * (p->TL_max / si.tL), 4096L) : B;
+}
+static long dec_launch_points(fstat_plan_t p) { return p->fp64 ? DEC_LAUNCH_POINTS_FP64 : DEC_LAUNCH_POINTS; }
+
+// Batch sizes shrunk until the workspace fits `limit`: the library's choice to its
+// first sizes (half the sky positions of its defaults, fewer templates), then all in turn.
+// Where the launches that result are too small to decimate (use_dec), the decimated series
+// take no room (dn_max = 0): at 64 MiB and one sky position of 86164 samples they would halve
+// the templates per launch (FP64: 4 to 2).
+static void fit_batches(fstat_plan_t p, size_t limit, int& Sb, int& B) {
+  const int Sb0 = Sb, B0 = B;
+  auto shrink = [&] {
+    while (layout(p, Sb, B, false) > limit && (Sb > 1 || B > 1)) {
+      if (B > p->B_first) B = std::max((B + 1) / 2, p->B_first);
+      else if (Sb > p->Sb_first) Sb = std::max((Sb + 1) / 2, p->Sb_first);
+      else if (B > 1 && (B >= 2 * Sb || Sb == 1)) B = (B + 1) / 2;
+      else Sb = (Sb + 1) / 2;
+    }
+  };
+  shrink();
+  bool dec = false;
+  for (auto& si : p->segs) dec |= si.dec && (long)launch_templates(p, si, B) * si.tL >= dec_launch_points(p);
+  if (p->dn_max && !dec) {
+    p->dn_max = 0;
+    Sb = Sb0;
+    B = B0;
+    shrink();
+  }
 }
 // Whether the plan's large calls on segment si do.
 static bool can_dec(fstat_plan_t p, const SegInfo& si) {
   return si.dec && p->dn_max && (p->fp64 || p->variant_b == 1) && !p->vet;
 }
 static bool use_dec(fstat_plan_t p, const SegInfo& si, const Grid& g) {
-  const long nt = std::min<long>(launch_templates(p, si), (long)std::min(p->Sb, g.nsky) * g.nfdot);
-  if (nt * si.tL < (p->fp64 ? DEC_LAUNCH_POINTS_FP64 : DEC_LAUNCH_POINTS)) return false;
+  const long nt = std::min<long>(launch_templates(p, si, p->B), (long)std::min(p->Sb, g.nsky) * g.nfdot);
+  if (nt * si.tL < dec_launch_points(p)) return false;
   return can_dec(p, si) && g.nfdot >= DEC_MIN_FDOT && (long)g.nsky * g.nfdot * si.tL >= DEC_MIN_POINTS;
 }
 
@@ -899,7 +927,7 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
   }
   const int total = nb * nfdot;
   cx<T>* tbuf = d.tmpl();
-  const int Bs = launch_templates(p, si);
+  const int Bs = launch_templates(p, si, p->B);
   for (int t0 = 0; t0 < total; t0 += Bs) {
     const int nt = std::min(Bs, total - t0);
     ta.t0 = td.t0 = t0;
@@ -1687,24 +1715,25 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
   int B = opt.templates_per_launch ? opt.templates_per_launch
           : p->fp64                ? (int)std::max(16L, std::min(128L, (1L << 24) / p->TL_max))
                                    : 512;
-  bool tuned = false;
+  p->Sb_first = opt.skies_per_batch ? Sb : Sb / 2;
+  p->B_first = opt.templates_per_launch ? B : p->fp64 ? 16 : 256;
   if (!opt.skies_per_batch && !opt.templates_per_launch && opt.tuning_cache_path) {
     int tb = 0, ts = 0, tv = 0;
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) == hipSuccess && ndev > 0 &&
         cache_lookup(opt.tuning_cache_path, device_tag(), p->L_max, cache_precision(opt), &tb, &ts, &tv)) {
-      B = tb;
-      Sb = ts;
+      B = p->B_first = tb;
+      Sb = p->Sb_first = ts;
       p->variant_a = tv & 1;
       p->variant_b = tv >> 1;
-      tuned = true;
     }
   }
-  (void)tuned;
+  p->scale_B = (opt.templates_per_launch == 0);
   const size_t budget = opt.workspace_budget_bytes;
   if (budget) {
-    // a budget that only the full-rate transforms fit is served by them
-    if (layout(p, 1, 1, false) > budget) p->dn_max = 0;
+    // admission: one sky position and one full-rate template
+    const long dn = p->dn_max;
+    p->dn_max = 0;
     if (layout(p, 1, 1, false) > budget) {
       char msg[200];
       std::snprintf(msg, sizeof msg, "largest segment needs %zu workspace bytes with one sky and one template; budget %zu",
@@ -1712,14 +1741,11 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
       delete p;
       return fail(nullptr, FSTAT_E_ADMISSION, msg);
     }
-    while (layout(p, Sb, B, false) > budget && (Sb > 1 || B > 1)) {
-      if (B > 1 && (B >= 2 * Sb || Sb == 1)) B = (B + 1) / 2;
-      else Sb = (Sb + 1) / 2;
-    }
+    p->dn_max = dn;
+    fit_batches(p, budget, Sb, B);
   }
   p->Sb = Sb;
   p->B = B;
-  p->scale_B = (opt.templates_per_launch == 0);
   layout(p, Sb, B, true);
 
   // device resources
@@ -1913,18 +1939,19 @@ fstat_status fstat_twoF_spectrum_static(fstat_plan_t plan, int32_t segment, cons
   if (hipGetDevice(&cur) != hipSuccess || cur != plan->device)
     return fail(plan, FSTAT_E_STATE, "the plan's device is not the current device");
   const size_t cap = FSTAT_STATIC_SCRATCH_BYTES;
+  const long dn0 = plan->dn_max;
+  plan->dn_max = 0;
   if (layout(plan, 1, 1, false) > cap) {
     char msg[200];
     std::snprintf(msg, sizeof msg, "the plan's largest segment needs %zu workspace bytes with one sky and one "
                   "template; the static scratch holds %zu", layout(plan, 1, 1, false), cap);
+    plan->dn_max = dn0;
     return fail(plan, FSTAT_E_INVAL, msg);
   }
   // the plan's batch sizes, shrunk as by admission until the workspace fits the scratch
+  plan->dn_max = dn0;
   int Sb = std::min(plan->Sb, (int)nsky), B = plan->B;
-  while (layout(plan, Sb, B, false) > cap && (Sb > 1 || B > 1)) {
-    if (B > 1 && (B >= 2 * Sb || Sb == 1)) B = (B + 1) / 2;
-    else Sb = (Sb + 1) / 2;
-  }
+  fit_batches(plan, cap, Sb, B);
   // run on the scratch, every launch on `stream`, then restore the plan's own workspace,
   // batch sizes and layout (the enqueued kernels hold their arguments by value)
   void* const ws0 = plan->ws;
@@ -1943,6 +1970,7 @@ fstat_status fstat_twoF_spectrum_static(fstat_plan_t plan, int32_t segment, cons
   plan->ws = ws0;
   plan->Sb = Sb0;
   plan->B = B0;
+  plan->dn_max = dn0;
   layout(plan, Sb0, B0, true);
   plan->last_stream = st;
   plan->used_stream = true;

@@ -48,3 +48,38 @@ for n, opts in ((30011, {}), (30011, dict(k_max=65536)), (30011, dict(precision=
     assert want and stages(plan) == want, (n, opts, want)
     assert any("full::" in k for k in want) == (opts == dict(k_max=65536) or n == 300007 and "interbinning" in opts)
 """)
+
+
+# segment, precision, workspace budget in MiB, sky positions and templates a launch that fit it
+# at the full rate
+@pytest.mark.parametrize("n,precision,mib,skies,templates", [
+    (30011, 1, 40, 8, 8), (30011, 1, 64, 8, 32), (30011, 1, 100, 8, 64), (86164, 1, 40, 2, 2), (86164, 1, 100, 4, 8),
+    (30011, 0, 40, 4, 4), (30011, 0, 64, 4, 16), (86164, 0, 40, 1, 1), (86164, 0, 100, 2, 4)])
+def test_decimated_series_take_no_room_where_launches_are_too_small(stub, n, precision, mib, skies, templates):
+    """Budgets under which no launch is large enough to decimate leave the full-rate calls the
+    batch sizes that they would have without the decimated series."""
+    hip_stub.run(stub, f"""
+import ctypes
+plan = H.plan([{n}], precision={precision}, workspace_budget_bytes={mib} << 20, use_graph=0)
+v = [ctypes.c_int() for _ in range(7)]
+assert H.lib.fstat_plan_info(plan, 0, *[ctypes.byref(x) for x in v]) == 0
+assert v[3].value >= {templates} and v[4].value >= {skies}, (v[3].value, v[4].value)
+assert H.workspace(plan) <= {mib} << 20
+assert H.search(plan, 64, 64) == 0 and not any("dec" in k for k in H.names())
+""")
+
+
+@pytest.mark.parametrize("n,precision,templates", [(86164, 0, 4), (120011, 0, 4), (131072, 0, 2), (30011, 0, 16),
+                                                   (169509, 1, 4), (200000, 1, 4), (86164, 1, 8), (30011, 1, 32)])
+def test_templates_per_launch_on_the_static_scratch(stub, n, precision, templates):
+    """One sky position on the static scratch; then the plan's own calls decimate as before."""
+    hip_stub.run(stub, f"""
+plan = H.plan([{n}], precision={precision}, use_graph=0)
+need = H.workspace(plan)
+H.launches.clear()
+assert H.spectrum(plan, 1, 64, static=True) == 0
+a = [k for k in H.names() if k.startswith("k_tmpl_a")]
+assert 0 < len(a) <= 64 // {templates} and not any("dec" in k for k in H.names()), a
+assert H.workspace(plan) == need
+assert H.search(plan, 64, 64) == 0 and any("k_tmpl_a_dec" in k for k in H.names())
+""")
