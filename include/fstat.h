@@ -195,7 +195,7 @@ fstat_status fstat_twoF_spectrum(fstat_plan_t plan, int32_t segment,
  * to `stream` in order (no graph, no second stream, no timing events), with the
  * plan's batch sizes shrunk until the workspace of the plan's largest segment fits
  * the scratch.  FSTAT_E_INVAL when even one sky position and one template do not fit
- * (mixed precision fits nfft <= 2^19, FP64 nfft <= 2^18), or for the arguments
+ * (mixed precision fits nfft <= 2^19, and 2^20 up to 524272 samples; FP64 nfft <= 2^19), or for the arguments
  * fstat_twoF_spectrum rejects; FSTAT_E_STATE when the plan's device is not current.
  * Every call on one GPU uses that GPU's one scratch, whatever the plan: calls that
  * overlap on one GPU (on different streams, threads or plans) race on it and give

@@ -349,10 +349,10 @@ static size_t layout(fstat_plan_t p, int Sb, int B, bool commit) {
     o_zt[k] = off;
     off = align256(off + (size_t)Sb * 2 * p->n_max * cx);
   }
-  // per-sky scratch: the demodulated series and three more arrays of [M] pairs (full-rate
-  // calls use them all)
+  // per-sky scratch: the demodulated series and two more arrays of [M] pairs, three in mixed
+  // precision, whose full-rate calls use another (run_sky_batch)
   const size_t o_sky = off;
-  off = align256(off + (size_t)Sb * (4 * p->M_max + 4 * p->L_max) * cx);
+  off = align256(off + (size_t)Sb * (p->fp64 ? 3 : 4) * 2 * p->M_max * cx);
   // template intermediate [B][tL][2]
   const size_t o_tmpl = off;
   off = align256(off + (size_t)B * 2 * p->TL_max * cx);

@@ -83,3 +83,29 @@ assert 0 < len(a) <= 64 // {templates} and not any("dec" in k for k in H.names()
 assert H.workspace(plan) == need
 assert H.search(plan, 64, 64) == 0 and any("k_tmpl_a_dec" in k for k in H.names())
 """)
+
+
+@pytest.mark.parametrize("n,precision,opts,arrays,used", [
+    (30011, 0, {}, 3, 3), (30011, 1, {}, 4, 3), (30011, 1, dict(k_max=65536), 4, 4), (2048, 1, dict(k_max=4096), 4, 4),
+    (300007, 0, dict(interbinning=1), 3, 3)])
+def test_per_sky_scratch_is_what_the_stage_uses(stub, n, precision, opts, arrays, used):
+    """The per-sky arrays lie between the resampled series and the templates' intermediate,
+    with no room beyond them."""
+    hip_stub.run(stub, f"""
+import ctypes
+nb, n, used, size = 5, {n}, {used}, {8 if precision else 16}
+M = 1024
+while M < n: M *= 2
+seen = {{}}
+def at(args, i): return ctypes.cast(args[i], ctypes.POINTER(ctypes.c_ulonglong))[0]
+H.on.update({{"k_sky_demod": lambda a: seen.__setitem__("z", at(a, 3)),
+              "k_sky_rows": lambda a: seen.__setitem__("last", at(a, 0)),                 # in place, behind the odd samples
+              "full::k_spline": lambda a: seen.__setitem__("last", at(a, 3)),            # the odd samples, last of all
+              "k_tmpl_a": lambda a: seen.__setitem__("tmpl", at(a, 2)),
+              "k_tmpl_a_pair": lambda a: seen.__setitem__("tmpl", at(a, 2))}})
+plan = H.plan([n], precision={precision}, skies_per_batch=nb, templates_per_launch=256, use_graph=0, **{opts!r})
+assert H.search(plan, nb, 64) == 0
+one = nb * M * 2 * size                  # an array of pairs
+assert seen["last"] + one == seen["z"] + used * one, seen
+assert seen["z"] + {arrays} * one <= seen["tmpl"] < seen["z"] + {arrays} * one + 256, (seen, one)
+""")
