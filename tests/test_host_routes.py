@@ -109,3 +109,24 @@ one = nb * M * 2 * size                  # an array of pairs
 assert seen["last"] + one == seen["z"] + used * one, seen
 assert seen["z"] + {arrays} * one <= seen["tmpl"] < seen["z"] + {arrays} * one + 256, (seen, one)
 """)
+
+
+@pytest.mark.parametrize("lengths,opts,nsky,nfdot,first,second", [
+    ([2048], dict(templates_per_launch=4096, skies_per_batch=64), 64, 64, "40", "k_tmpl_b_stream<float, 64, 1, 2, 4>"),
+    ([4096], dict(templates_per_launch=4096, skies_per_batch=64), 32, 64, "40", "k_tmpl_b_stream<float, 128, 1, 2, 4>"),
+    ([5000], dict(templates_per_launch=4096, skies_per_batch=64, interbinning=1), 32, 64, "40", "k_tmpl_b_ib<128, 1, 2>"),
+    ([2048, 60001], dict(), 40, 200, "40", "k_tmpl_b_stream<float, 64, 1, 2, 1>"),
+    ([30011], dict(templates_per_launch=300, skies_per_batch=7), 17, 67, "160", "k_tmpl_b_stream<float, 256, 1, 2, 4>"),
+    ([30011], dict(templates_per_launch=300, skies_per_batch=7, interbinning=1), 17, 67, "80", "k_tmpl_b_ib<256, 1, 2>"),
+    ([4097], {}, 16, 64, "80", None), ([12001], {}, 8, 64, "80", None), ([16384], {}, 8, 64, "80", None),
+    ([30011], {}, 4, 64, "160", None), ([86164], {}, 2, 32, "320", None), ([131072], {}, 2, 32, "320", None),
+    ([150001], {}, 2, 16, "320", None), ([262144], {}, 2, 16, "320", None), ([300007], {}, 2, 8, "640", None),
+    ([524288], {}, 2, 8, "640", None), ([262000], dict(interbinning=1), 2, 32, "320", None)])
+def test_which_spectra_decimate(stub, lengths, opts, nsky, nfdot, first, second):
+    """The grids of the decimated transforms' tests reach every first pass."""
+    out = hip_stub.run(stub, f"""
+plan = H.plan({lengths!r}, use_graph=0, **{opts!r})
+assert H.spectrum(plan, {nsky}, {nfdot}) == 0
+print("\\n".join(sorted(set(H.names()))))
+""")
+    assert f"k_tmpl_a_dec<float, {first}, " in out and (second is None or second in out), out
