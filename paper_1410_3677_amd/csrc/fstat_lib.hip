@@ -750,11 +750,15 @@ static hipError_t launch_dec_a(const Dev<T>& d, const SegInfo& si, const TmplArg
   hipError_t err = hipErrorInvalidValue;
   // first-stage inputs r >= rnz are zero for every column when dn <= rnz dL / 5
   const int rnz = (int)std::max<long>(2, (5 * si.dn + si.dL - 1) / si.dL);
+  // more than three of them only with interbinning (mixed precision, up to 320 points), 40 points
+  // only in mixed precision (fstat_plan)
   auto go = [&](auto len_c, auto rnz_c) {
     constexpr int LEN = decltype(len_c)::value, RZ = decltype(rnz_c)::value;
-    FSTAT_LAUNCH((k_tmpl_a_dec<T, LEN, RZ>), dim3((unsigned)(si.tP / dec_tw<T, LEN>() * nt)), dim3(dec_nt<T>()), 0, st,
-                 ta, d.zd(), tbuf, d.dec_stage(), d.dec_lo(si.tlog), d.dec_hi(si.tlog));
-    err = launch_status();
+    if constexpr (sizeof(T) == 4 ? RZ <= 3 || LEN <= 320 : RZ <= 3 && LEN >= 80) {
+      FSTAT_LAUNCH((k_tmpl_a_dec<T, LEN, RZ>), dim3((unsigned)(si.tP / dec_tw<T, LEN>() * nt)), dim3(dec_nt<T>()), 0, st,
+                   ta, d.zd(), tbuf, d.dec_stage(), d.dec_lo(si.tlog), d.dec_hi(si.tlog));
+      err = launch_status();
+    }
   };
   auto len = [&](auto len_c) {
     switch (rnz) {
@@ -1019,7 +1023,7 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
           }
           const auto go = [&](auto mode_c) {
             constexpr int MD = decltype(mode_c)::value;
-            if constexpr (sizeof(T) == 8 && MD != 2) {
+            if constexpr (sizeof(T) == 8 && MD != 2 && PP >= 128) {   // FP64 decimates from rows of 128 points on
               if (dec) {
                 FSTAT_LAUNCH((k_tmpl_b<T, PP, MD>), dim3(si.dQ / tw_b<T, PP>() * nt), dim3(tmpl_nt_b<T, PP>()), 0, st,
                              td, d.sp(), tbuf, oa, d.twst);

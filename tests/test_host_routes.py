@@ -130,3 +130,27 @@ assert H.spectrum(plan, {nsky}, {nfdot}) == 0
 print("\\n".join(sorted(set(H.names()))))
 """)
     assert f"k_tmpl_a_dec<float, {first}, " in out and (second is None or second in out), out
+
+
+def test_decimated_first_passes_are_those_that_calls_reach(stub):
+    """Over every precision, transform length and share of it that the data fill, calls launch
+    a kernel each time, and together every instantiation in the library."""
+    import re
+    import subprocess
+    from paper_1410_3677_amd import fstat as F
+    out = hip_stub.run(stub, """
+F = H.F
+for precision in (0, 1):
+    for ib in (0, 1):
+        for e in range(12 + ib, 21):
+            half = 1 << (e - 1)
+            for n in sorted({max(2048, v) for v in (half // 2 + 1, 3 * half // 4, 5 * half // 7, half - 100, half)}):
+                plan = H.plan([n], precision=precision, interbinning=ib, nfft=2 * half, templates_per_launch=4096,
+                              skies_per_batch=8, use_graph=0)
+                assert H.search(plan, 8, 512) == F.OK, (precision, ib, e, n, H.lib.fstat_last_error(plan))
+                H.lib.fstat_destroy(plan)
+print("\\n".join(sorted(set(H.names()))))
+""")
+    syms = subprocess.run(["nm", "-DC", "--defined-only", F.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    built = set(re.findall(r"\bk_tmpl_a_dec<[^>]*>", syms))
+    assert built and built == set(re.findall(r"\bk_tmpl_a_dec<[^>]*>", out))
