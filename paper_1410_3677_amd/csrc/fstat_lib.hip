@@ -913,8 +913,14 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
   ta.nfft = si.nfft;
   ta.nblk = 0;
   // with decimated transforms both paths are launched and the flag that the call's k_route
-  // left says which one works; the other's launches hold one resident round of workgroups,
-  // which return at once (about 5 us each against 470 us for the 512 templates of both passes)
+  // left says which one works; the other's workgroups return at once.  The full-rate first
+  // pass walks its tiles on DEC_WALK workgroups a CU then: few enough to return in about 5 us
+  // (470 us for the 512 templates of both passes), and enough that its walk costs nothing when
+  // it does work: one resident round (2) fell out of step, 100.8 ms for 65536 templates of
+  // 86164 samples with a spindown beyond the margin, 94.9 with 8 (97.4 without decimation).
+  // Columns of 1024 points lie four to a tile, half a line, which neighbours fill only while
+  // they stay in step: 9.2 ms with 2, 9.0 with 8, 8.4 with 32 for 1024 templates of 300007
+  // samples.  FP64: 18.5 ms with 2, 19.2 with 32 for 4096 templates.
   ta.route = dec ? d.route() : nullptr;
   ta.route_want = 0;
   ta.ibpr = 1.f;
@@ -944,7 +950,8 @@ static fstat_status run_templates(fstat_plan_t p, const Dev<T>& d, const SegInfo
         if constexpr (QQ >= 64) {
           const int ntiles = si.tP / tw_a<T, QQ>();
           ta.nblk = ntiles * nt;
-          const dim3 grid(dec ? std::min(ta.nblk, 2 * p->n_cu) : ta.nblk);
+          constexpr int DEC_WALK = sizeof(T) == 8 ? 2 : QQ < 1024 ? 8 : 32;
+          const dim3 grid(dec ? std::min(ta.nblk, DEC_WALK * p->n_cu) : ta.nblk);
           // first-stage inputs r >= rnz are zero for every column when n <= rnz tL / 8
           int rnz = 8;
           for (int r = 7; r >= 3; --r)
