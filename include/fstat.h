@@ -85,10 +85,15 @@ typedef struct {
   int64_t candidate_capacity;     /* entries of the device candidate buffer, >= 1 */
   size_t workspace_budget_bytes;  /* admission limit for the workspace; 0 = no limit */
   int32_t templates_per_launch;   /* spindown templates per FFT launch; 1 = one template per
-                                     launch; 0 = the library's choice (sized for the plan's
+                                     launch; 0 = the library's choice (512, in FP64 16 to 128
+                                     by length; sized for the plan's
                                      longest transform: a segment with a shorter one takes
-                                     proportionally more per launch, at most 4096) */
-  int32_t skies_per_batch;        /* sky positions prepared together; 0 = the library's choice */
+                                     proportionally more per launch, at most 4096).  The
+                                     batch sizes, the workspace budget and the tuning cache
+                                     also decide which calls are decimated (fstat_plan_info)
+                                     and with it 2F's last digits */
+  int32_t skies_per_batch;        /* sky positions prepared together; 0 = the library's choice
+                                     (16, in FP64 8) */
   int32_t use_graph;              /* 1: capture each search call as a HIP graph and replay it while
                                      the call's arguments are unchanged */
   const char* tuning_cache_path;  /* autotuner results file (read by fstat_plan when both batch
@@ -134,7 +139,9 @@ fstat_status fstat_plan(const fstat_segment* segs, int32_t nseg, const fstat_opt
                         fstat_plan_t* out_plan);
 
 /* Workspace bytes the plan needs (its chosen batch sizes; memory of the search
- * loop of Sect. 2 held between calls). */
+ * loop of Sect. 2 held between calls).  With the library's choice at nfft = 2^18 2.4 GB, in
+ * proportion to nfft (interbinning half of it below nfft = 2^20); FP64 0.7 GB (interbinning
+ * 1.2).  A smaller workspace_budget_bytes shrinks the batches. */
 fstat_status fstat_plan_workspace_size(fstat_plan_t plan, size_t* bytes);
 
 /* Hand the plan a caller-owned device workspace of at least
@@ -181,14 +188,17 @@ fstat_status fstat_candidates(fstat_plan_t plan, fstat_candidate* out, fstat_can
  * Enqueue 2F over bins [k_min, k_max) of every template of one segment into
  * the device array out, laid out [sky][fdot][bin - k_min], float for MIXED
  * and double for FP64.  Same kernels as the search, with the threshold
- * stage replaced by a store.  Asynchronous on `stream`. */
+ * stage replaced by a store.  A large call is decimated (fstat_plan_info): 2F of one of its
+ * templates and of the same template in a small call, or from a plan with a vetter, agree
+ * to rounding, not in every bit.  Asynchronous on `stream`. */
 fstat_status fstat_twoF_spectrum(fstat_plan_t plan, int32_t segment,
                                  const double* alpha, const double* delta, int32_t nsky,
                                  const double* fdot, int32_t nfdot, void* out, void* stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation): fstat_twoF_spectrum with
- * the same arguments, layout and results, run on a static device scratch of
+ * the same arguments, layout and results (to rounding where that call is decimated: the
+ * launches of this one are never large enough), run on a static device scratch of
  * FSTAT_STATIC_SCRATCH_BYTES instead of the plan's workspace.  Each GPU the library
  * runs on holds its own such scratch, from when the library's device code is loaded
  * on it until the process ends.  The call allocates nothing and creates nothing: every launch goes
@@ -313,12 +323,16 @@ fstat_status fstat_profile_read(fstat_plan_t plan, int32_t kernel_class, int64_t
  * precision path with P <= 512, other segments use row tiles; with
  * interbinning the mixed-precision second pass with P <= 512 is always a walk
  * of wavefronts over chunks of consecutive rows; FP64 and P = 1024 use row
- * tiles that store the transforms for a separate 2F pass).  A call of enough
- * templates (2^24 transform points) with bins below nfft/2 and no vetter
- * attached, in mixed precision with variant 1 or in FP64 without interbinning,
- * transforms series decimated to 5/8 of the sampling rate, (5/8) P Q points with
- * the same bins, unless a spindown sweeps the band by more than 0.005 cycles per
- * sample over the segment; results agree to rounding.  Any output pointer may be NULL. */
+ * tiles that store the transforms for a separate 2F pass).  A call, search
+ * or spectrum, transforms each segment's series decimated to 5/8 of the sampling rate, (5/8) P Q
+ * points with the same bins, when: its templates times P Q reach 2^24; it has five spindowns
+ * or more per sky position; a launch (templates per launch, of one sky batch) holds 2^23
+ * points, FP64 2^21; the bins lie below nfft/2; the decimated series with its filter's tails
+ * fits (5/8) P Q points (all but interbinned segments that nearly fill nfft/2); mixed precision
+ * has second-pass variant 1 and, interbinned, P <= 512; FP64 is not interbinned and has nfft
+ * >= 2^14; no vetter is attached; the workspace budget has room for the series; and no
+ * spindown sweeps the band by more than 0.005 cycles per sample over the segment (looked at
+ * on the device).  Otherwise the full rate.  The two agree to rounding.  Any output pointer may be NULL. */
 fstat_status fstat_plan_info(fstat_plan_t plan, int32_t segment, int32_t* nfft, int32_t* p,
                              int32_t* q, int32_t* templates_per_launch, int32_t* skies_per_batch,
                              int32_t* pass_a_variant, int32_t* pass_b_variant);
@@ -386,7 +400,9 @@ fstat_status fstat_vet_destroy(fstat_vet_t vet);
 
 /* Attach a network to a plan: from now on every search also stores, right after
  * each F kernel launch, the 256-bin 2F window of each new crossing (up to
- * patch_capacity <= candidate_capacity crossings per drain).  NULL detaches.
+ * patch_capacity <= candidate_capacity crossings per drain), in 1 KiB per crossing and
+ * the 2F of one launch's templates (0.5 GB for 512 templates at nfft = 2^18).  While attached,
+ * no call of the plan is decimated.  NULL detaches.
  * The plan keeps using the network until it is detached or the plan destroyed. */
 fstat_status fstat_plan_attach_vetter(fstat_plan_t plan, fstat_vet_t vet, int64_t patch_capacity);
 

@@ -287,12 +287,12 @@ inline long dec_samples(long n) {
 
 // Sky blockIdx.y, both series interleaved [m][a|b]; h[i][p] = filter value of input
 // 8 (q - Q0) - HALF + i in output p.  A thread forms one group of five outputs of one
-// series (wavefronts 0, 1: series a, 2, 3: b): 96 staged inputs, 475 taps, sums in double
-// precision (as fast as single on this chip without packed single precision), so that the
-// decimated series carries one rounding.  The taps are uniform (scalar loads); the centre
-// frequency's rotation of the inputs, (-i)^i, only swaps and negates parts, and that of
-// the outputs is a constant per p.  LDS index e sits at e + e / 8: lanes read eight inputs
-// apart, and the padding spreads them over the banks.
+// series (wavefronts 0, 1: series a, 2, 3: b): 96 staged inputs and 480 taps in single
+// precision, 192 and 960 in double, sums in double precision (as fast as single on this chip
+// without packed single precision), so that the decimated series carries one rounding.  The
+// taps are uniform (scalar loads); the centre frequency's rotation of the inputs, (-i)^i, only
+// swaps and negates parts, and that of the outputs is a constant per p.  LDS index e sits at
+// e + e / 8: lanes read eight inputs apart, and the padding spreads them over the banks.
 template <typename T>
 __global__ void __launch_bounds__(2 * DEC_NT) k_decimate(const cx_pair<T>* __restrict__ zt, long ldzt, int n,
                                                          cx<T>* __restrict__ zd, long ldzd, int nq,

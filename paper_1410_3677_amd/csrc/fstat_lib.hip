@@ -834,15 +834,25 @@ static hipError_t launch_stream_b(const Dev<float>& d, const SegInfo& si, const 
 
 // Whether a call's templates of segment si run as decimated transforms.  They save 3/8 of
 // a template's memory traffic and arithmetic (0.93 against 1.47 us at 2^18 points; FP64 2.8
-// against 4.65) and cost the filter, once a sky position (2.2 us; FP64 2.9), and the launches of the path not taken (10 us a
-// launch pair); where those weigh more, with few spindowns or in small calls, the full-rate
-// transforms stay.  With a vetter attached everything does: the patch capture stores the rows
-// of the full-rate second pass, and windows of a spectrum of the same plan score like them.
+// against 4.65) and cost the filter, once a sky position (1.75 us; FP64 2.9), and the launches
+// of the path not taken (10 us a launch pair); where those weigh more, in small calls, the
+// full-rate transforms stay.  With a vetter attached everything does: the patch capture stores
+// the rows of the full-rate second pass, and windows of a spectrum of the same plan score like
+// them.
 constexpr long DEC_MIN_POINTS = 1L << 24;   // templates times transform points
-constexpr int DEC_MIN_FDOT = 5;             // spindowns per sky position
-// points per launch at least, mixed precision and FP64: the launch pair of the path not taken
-// costs 10 us, 20 mixed or 6 FP64 templates' gain at 2^18 points (one template per launch:
-// 17 us decimated, 13 at the full rate)
+// Spindowns per sky position: five filters' worth of gain, where the line was drawn when both
+// routes shared one per-sky stage.  That still holds in FP64 within two (a search of 256 sky
+// positions of 86164 samples with 1, 2, 4 spindowns: 15.1, 17.5, 27.9 us a sky position at the
+// full rate, 17.0, 18.5, 22.1 decimated).  In mixed precision full-rate calls have since kept
+// the slower stage of the two, and the line lies too high: 512 sky positions with 1, 2, 3, 4
+// spindowns take 11.4, 12.8, 14.0, 15.2 us each and would take 7.9, 8.5, 9.2, 9.8 decimated.
+constexpr int DEC_MIN_FDOT = 5;
+// Points per launch at least, mixed precision and FP64: the launch pair of the path not taken
+// costs 10 us, 20 mixed or 6 FP64 templates' gain at 2^18 points.  86164 samples, us a template
+// at the full rate and decimated: 13 and 17 with one template per launch, 2.94 and 3.05 with
+// 8, 2.20 and 1.93 with 16; the line is one doubling above the crossing.  Plans whose longest
+// transform is 2^13 points or less never reach it with the library's 512 templates: 64 x 64
+// templates of 2048 or 4096 samples take 371 or 448 us, and would take 330 or 350 decimated.
 constexpr long DEC_LAUNCH_POINTS = 1L << 23, DEC_LAUNCH_POINTS_FP64 = 1L << 21;
 
 // The plan's B templates per launch are sized for its longest transform; when the library
