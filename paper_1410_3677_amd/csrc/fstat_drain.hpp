@@ -324,7 +324,7 @@ __device__ __forceinline__ fstat_candidate_key drain_key(const CandEntry& c, int
   k.sky = c.sky;
   k.fdot_idx = c.fdot_idx;
   k.bin = c.bin;
-  k.vet_score = scored ? __int_as_float(c.pad) : __builtin_nanf("");
+  k.vet_score = __int_as_float(scored ? c.score : NO_SCORE);
   return k;
 }
 

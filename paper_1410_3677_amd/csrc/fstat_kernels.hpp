@@ -58,11 +58,13 @@ struct SegConst {
   const double* r;  // 3 n, component-major
 };
 
-// Candidate entry as written by the threshold stage.
+// Candidate entry as written by the threshold stage; score: bits of the vetting score, not a
+// number until there is one.
 struct CandEntry {
-  int32_t search, segment, sky, fdot_idx, bin, pad;
+  int32_t search, segment, sky, fdot_idx, bin, score;
   double twoF;
 };
+constexpr int32_t NO_SCORE = 0x7fc00000;
 
 // ------------------------------------------------------------------ sky stage
 // <p q> over the samples of two antenna functions p_0 cos 2x + p_1 sin 2x + p_2 cos x +

@@ -861,7 +861,7 @@ __global__ void __launch_bounds__((tmpl_nt_b<T, P>())) k_tmpl_b(TmplArgs ta, con
             ce.sky = ta.sky0 + skyl;
             ce.fdot_idx = sidx;
             ce.bin = ta.Q * (g + G * b + NSL * r) + k2;
-            ce.pad = 0;
+            ce.score = NO_SCORE;
             ce.twoF = (double)val[i];
             oa.cand[slot] = ce;
           }
@@ -936,7 +936,7 @@ __global__ void __launch_bounds__(256) k_interbin_2f(TmplArgs ta, const SkyParam
         ce.sky = ta.sky0 + skyl;
         ce.fdot_idx = sidx;
         ce.bin = 2 * kc + e;
-        ce.pad = 0;
+        ce.score = NO_SCORE;
         ce.twoF = (double)v[e];
         oa.cand[slot] = ce;
       }
@@ -1106,7 +1106,7 @@ struct WaveStage {
       ce.sky = ta.sky0 + skyl;
       ce.fdot_idx = t - skyl * ta.nfdot;
       ce.bin = b;
-      ce.pad = 0;
+      ce.score = NO_SCORE;
       ce.twoF = (double)v;
       oa.cand[slot] = ce;
     }

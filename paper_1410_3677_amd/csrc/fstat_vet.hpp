@@ -512,7 +512,7 @@ __global__ void __launch_bounds__(256) k_vet_head_infer(const float* __restrict_
     float v = theta[O_B6];
     for (int j = 0; j < H; ++j) v += sp[tid][j];
     logit[r0 + tid] = v;
-    if (cand) cand[r0 + tid].pad = __float_as_int(1.f / (1.f + expf(-v)));
+    if (cand) cand[r0 + tid].score = __float_as_int(1.f / (1.f + expf(-v)));
   }
 }
 
